@@ -14,10 +14,11 @@ typedef unsigned short bf16_t;  // raw bf16 bits
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) u32 u32x4_t;  // 16 bytes in registers
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 
 constexpr int kThreads = 256;       // every kernel here runs 4 wavefronts per workgroup
 constexpr int kPermBlock = 64;      // tokens per permutation block (one bit each in a 64-bit mask)
-constexpr int kRouteTokens = 16;    // tokens per gate task
+constexpr int kRouteTokens = 16;    // tokens per gate task, at most
 constexpr int kMaxExperts = 256;    // gate / plan limits
 constexpr int kMaxDest = 1024;
 constexpr u64 kWaitTicks = 400000000ull;  // 4 s of the 100 MHz wall clock: default bound of every in-kernel wait
@@ -67,7 +68,8 @@ struct KArgs {
     int dtype, tile_m, tile_n, signal_mode, fence_scope;
     int group_size;  // flags per fence group of the per-destination mode, 0 = all flags of a destination
     int scheduler;   // moe_scheduler_t
-    int gate_split;  // gate tasks per block of 16 tokens: each takes a slice of the reduction (1 = the whole)
+    int gate_tok;    // tokens per gate task: 16, 8 or 4
+    int gate_split;  // fp32: gate tasks per block of 16 tokens: each takes a slice of the reduction (1 = the whole)
     int capacity;    // rows every expert owns in the sorted order, 0 = ragged layout (see moe_problem_t)
     int NP;          // rows of the sorted order: N (ragged) or E * capacity
     u32 epoch;

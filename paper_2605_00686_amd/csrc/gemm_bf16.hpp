@@ -25,7 +25,6 @@
 namespace moe {
 
 typedef __attribute__((ext_vector_type(8))) short s16x8_t;
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 // MB x NB MFMA blocks (32 x 32) per wavefront, WM x WN wavefronts (WM*WN = 4),

@@ -20,10 +20,12 @@ __global__ __launch_bounds__(kThreads) void k_zero(u32 *p, size_t n) {
         p[i] = 0u;
 }
 
-template <typename ET>
-__global__ __launch_bounds__(kThreads) void k_route(KArgs a, int do_hist) {
+template <typename ET, int V>
+__global__ __launch_bounds__(kThreads, 1) void k_route(KArgs a, int do_hist) {
     extern __shared__ __align__(16) char smem[];
-    route_task<ET>(a, blockIdx.x, smem, do_hist != 0);
+    __shared__ int s_slot;
+    if constexpr (V > 0) gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
+    route_task<ET, V, false>(a, kernel_args_address(), blockIdx.x, smem, do_hist != 0, &s_slot, [] { return false; });
 }
 
 __global__ __launch_bounds__(kThreads) void k_plan(KArgs a) {
@@ -179,17 +181,26 @@ __global__ __launch_bounds__(kThreads) void k_combine(KArgs a) {
     combine_task<ET, false, STREAM>(a, blockIdx.x);
 }
 
-// Front tasks of the megakernel from their counter, in this order:
-// [gate-weight transposition tiles | gate tasks | plan | permutation blocks].  Returns nonzero if a wait failed or
-// the routing was found invalid.
-template <typename ET>
-__device__ __forceinline__ int front_stage(const KArgs &a, char *smem) {
+// Front tasks of the megakernel from their counter, in this order: [gate-weight transposition tiles | gate tasks | plan |
+// permutation blocks].  Returns
+// nonzero if a wait failed or the routing was found invalid.  A real call, like the GEMM stages (see there), so that the
+// gate's registers are its own.
+template <typename ET, int V>
+static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 smem_off, volatile int *caller_local) {
+    KArgs a = load_kernel_args(args);
+    mark_global(a);
+    char *smem = lds_at((u32)uniform((int)smem_off));
     const int tid = threadIdx.x;
     Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const u64 t0 = kernel_start_ticks(c);
+    *caller_local = 5;  // (see the call sites of tile_stage)
     __syncthreads();
     if (tid == 0) sl->next = (int)atomicAdd(&c->next_task, 1u);
+    if constexpr (V > 0) {
+        gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
     __syncthreads();
     int task = uniform(sl->next);
     bool seen_plan = false, seen_wgt = false, bad = false;
@@ -199,27 +210,22 @@ __device__ __forceinline__ int front_stage(const KArgs &a, char *smem) {
         int phase;
         if (task < a.t_gate) {
             phase = 0;
-            wgt_task(a, task, smem);
+            if constexpr (V > 0) wgt_task(a, task, smem);
             sync_stores();
             if (tid == 0) {
                 fence_release(0);
                 atomicAdd(&c->wgt_done, 1u);
             }
-#ifdef MOE_TILE_TIMING
-            if (tid == 0) atomicMax(&c->dbg[46], now_ticks() - c->t0);
-#endif
         } else if (task < a.t_plan) {
             phase = 0;
-            if (a.t_gate > 0 && !seen_wgt) {  // the transposed gate weights are complete
-                if (tid == 0) sl->ok = wait_ge(c, &c->wgt_done, (u32)a.t_gate, a.wait_ticks) ? 1 : 0;
-                __syncthreads();
-                seen_wgt = true;
-                bad = bad || !sl->ok;
-#ifdef MOE_TILE_TIMING
-                if (tid == 0) atomicMax(&c->dbg[45], now_ticks() - c->t0);
-#endif
-            }
-            if (!bad) route_task<ET>(a, task - a.t_gate, smem, true);
+            route_task<ET, V, true>(a, args, task - a.t_gate, smem, true, &sl->pick, [&]() __attribute__((always_inline)) {
+                if (!seen_wgt) {  // the transposed gate weights are complete
+                    if (tid == 0) sl->ok = wait_ge(c, &c->wgt_done, (u32)a.t_gate, a.wait_ticks) ? 1 : 0;
+                    __syncthreads();
+                    seen_wgt = sl->ok != 0;
+                }
+                return seen_wgt;
+            });
             sync_stores();
             if (tid == 0) {
                 fence_release(0);
@@ -296,8 +302,29 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
         atomicAdd(&c->stats[15], 1ull);
     }
 
+    // The stage functions get the address of a local of this kernel.  That keeps the compiler from
+    // marking the calls as tail calls, which is what lets it drop the saving and restoring of
+    // callee-saved registers in these functions (they have one caller, which keeps nothing in them):
+    // some 270 registers per lane through scratch memory, per call, otherwise.
+    volatile int stage_mark = 0;
+    const u32 lds = lds_offset_opaque(smem);
+
     // ---- stage 1: gate, plan, permutation
-    bool bad = front_stage<ET>(a, smem) != 0;
+    int front = 0;
+    if constexpr (sizeof(ET) == 2) {  // (one function per gate: each has registers of its own)
+        switch (a.Wg ? gate_variant(a.E, a.d) : 0) {
+            case 1: front = front_stage<ET, 1>(kargs, lds, &stage_mark); break;
+            case 2: front = front_stage<ET, 2>(kargs, lds, &stage_mark); break;
+            case 3: front = front_stage<ET, 3>(kargs, lds, &stage_mark); break;
+            case 4: front = front_stage<ET, 4>(kargs, lds, &stage_mark); break;
+            case 5: front = front_stage<ET, 5>(kargs, lds, &stage_mark); break;
+            case 6: front = front_stage<ET, 6>(kargs, lds, &stage_mark); break;
+            default: front = front_stage<ET, 0>(kargs, lds, &stage_mark); break;
+        }
+    } else {
+        front = front_stage<ET, 0>(kargs, lds, &stage_mark);
+    }
+    bool bad = uniform(front) != 0;
 
     // ---- wait for the plan and the permutation (and with them for every gate task); copy
     // the decode tables to LDS
@@ -333,12 +360,6 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
     if (!bad) {
         // ---- stage 2: GEMM tiles, one call per kind, this XCD's lists first
         const int home = xcd_id() % kTileQueues;
-        const u32 lds = lds_offset_opaque(smem);
-        // The stage functions get the address of a local of this kernel.  That keeps the compiler from
-        // marking the calls as tail calls, which is what lets it drop the saving and restoring of
-        // callee-saved registers in these functions (they have one caller, which keeps nothing in them):
-        // some 270 registers per lane through scratch memory, per call, otherwise.
-        volatile int stage_mark = 0;
         if constexpr (P::FUSED) {
             // ---- stage 2, fused: row blocks through both GEMMs, then combine
             fused_stage<P>(kargs, lds, home, n_rb, &stage_mark);
@@ -424,7 +445,9 @@ struct Plan {
     size_t o_gate_partial;
     size_t o_rq_slots, init_zero_bytes;  // the ready queues empty themselves: zeroed by moe_workspace_init only
     int rq_cap;
-    size_t o_blk_base, o_seg_begin, o_flag_base, o_dest_flag_begin, o_dest_group_begin, o_rb_base, o_rb_expert, o_rbs_base, o_rbs_expert, o_h, o_wgt, total;
+    size_t o_blk_base, o_seg_begin, o_flag_base, o_dest_flag_begin, o_dest_group_begin, o_rb_base, o_rb_expert, o_rbs_base, o_rbs_expert, o_h, total;
+    size_t o_wgt;
+    int gate_tok;  // tokens per gate task
 };
 
 static int make_plan(const moe_problem_t *p, Plan *pl) {
@@ -457,7 +480,8 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->per_dest = p->T / p->R;
     pl->ncb = (p->d + tn - 1) / tn;
     pl->nPB = (p->T + kPermBlock - 1) / kPermBlock;
-    pl->nRT = (p->T + kRouteTokens - 1) / kRouteTokens;
+    pl->gate_tok = p->dtype == MOE_DT_BF16 ? gate_tokens(p->T) : kRouteTokens;
+    pl->nRT = (p->T + pl->gate_tok - 1) / pl->gate_tok;
     pl->comb_tokens = p->T >= 16384 ? 16 : p->T >= 8192 ? 8 : p->T >= 2048 ? 4 : 1;
     // the ready-queue scheduler enqueues combine tasks per destination: none may span two
     if (p->scheduler == MOE_SCHED_READY_QUEUE && pl->per_dest % pl->comb_tokens != 0) pl->comb_tokens = 1;
@@ -555,7 +579,8 @@ static void fill_args(const Plan &pl, void *workspace, KArgs *a) {
     a->seg_from_blocks = (pl.per_dest % kPermBlock == 0) ? 1 : 0;
     a->disp_tokens = scatter_tokens(p.T);
     a->tl = pl.tl;
-    a->t_gate = 0;  // the megakernel adds the transposition tasks when it has a gate to compute
+    a->gate_tok = pl.gate_tok;
+    a->t_gate = 0;  // the megakernel adds the transposition tasks when it has a bf16 gate to compute
     a->t_plan = pl.nRT;
     a->t_perm = a->t_plan + 1;
     a->t_g1 = a->t_perm + pl.nPB;
@@ -639,9 +664,8 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
         smem = a.fused_h_off + (size_t)P::BM * pl.p.f * elem_size(pl.p.dtype);
         if (smem + sizeof(StageLds) + 16 > kLdsBudget) return MOE_ERR_UNSUPPORTED;
     }
-    const size_t rsm = route_smem_bytes(pl.p.E, elem_size(pl.p.dtype));
+    const size_t rsm = gate_task_smem_bytes(pl.p.E, pl.p.d, elem_size(pl.p.dtype));
     if (a_in.Wg && rsm > smem) smem = rsm;
-    if (a_in.WgT && screen_smem_bytes(pl.p.E) > smem) smem = screen_smem_bytes(pl.p.E);
     if (plan_smem(pl) > smem) smem = plan_smem(pl);
     // decode tables live behind everything else, for the life of the workgroup
     const size_t tab_bytes = (size_t)(4 * (pl.p.E + 1) + pl.tl.maxRB + pl.p.E) * 4;
@@ -761,16 +785,23 @@ int moe_route(const moe_problem_t *p, const void *x, const void *Wg, const float
     KArgs a;
     fill_args(pl, nullptr, &a);
     a.x = x; a.Wg = Wg; a.bias = gate_bias; a.idx = topk_idx; a.w = topk_w;
-    const size_t smem = route_smem_bytes(p->E, elem_size(p->dtype));
+    const size_t smem = gate_task_smem_bytes(p->E, p->d, elem_size(p->dtype));
     hipStream_t st = (hipStream_t)stream;
-    if (p->dtype == MOE_DT_F32) {
-        if ((rc = set_smem(k_route<float>, smem))) return rc;
-        hipLaunchKernelGGL(k_route<float>, dim3(pl.nRT), dim3(kThreads), smem, st, a, 0);
-    } else {
-        if ((rc = set_smem(k_route<bf16_t>, smem))) return rc;
-        hipLaunchKernelGGL(k_route<bf16_t>, dim3(pl.nRT), dim3(kThreads), smem, st, a, 0);
+    auto launch = [&](auto kern) {
+        const int rc2 = set_smem(kern, smem);
+        if (rc2) return rc2;
+        hipLaunchKernelGGL(kern, dim3(pl.nRT), dim3(kThreads), smem, st, a, 0);
+        return hip_ok(hipGetLastError());
+    };
+    if (p->dtype == MOE_DT_F32) return launch(k_route<float, 0>);
+    switch (gate_variant(p->E, p->d)) {
+        case 1: return launch(k_route<bf16_t, 1>);
+        case 2: return launch(k_route<bf16_t, 2>);
+        case 3: return launch(k_route<bf16_t, 3>);
+        case 4: return launch(k_route<bf16_t, 4>);
+        case 6: return launch(k_route<bf16_t, 6>);
+        default: return launch(k_route<bf16_t, 5>);
     }
-    return hip_ok(hipGetLastError());
 }
 
 // The launches of a dispatch, shared by moe_dispatch (scratch in the caller's workspace) and
@@ -824,11 +855,11 @@ static int dispatch_launches(const Plan &pl, const KArgs &a, bool short_only, hi
     if ((rc = set_smem(k_plan, psmem))) return rc;
     // histogram (gate task without the gate), plan, permutation, row gather, clean-up
     if (p->dtype == MOE_DT_F32) {
-        hipLaunchKernelGGL(k_route<float>, dim3(pl.nRT), dim3(kThreads), (size_t)p->E * 4, st, a, 1);
+        hipLaunchKernelGGL((k_route<float, 0>), dim3(pl.nPB), dim3(kThreads), kMaxExperts * 4, st, a, 1);
         hipLaunchKernelGGL(k_plan, dim3(1), dim3(kThreads), psmem, st, a);
         hipLaunchKernelGGL(k_perm<float>, dim3(pl.nPB), dim3(kThreads), (size_t)p->E * 8, st, a);
     } else {
-        hipLaunchKernelGGL(k_route<bf16_t>, dim3(pl.nRT), dim3(kThreads), (size_t)p->E * 4, st, a, 1);
+        hipLaunchKernelGGL((k_route<float, 0>), dim3(pl.nPB), dim3(kThreads), kMaxExperts * 4, st, a, 1);
         hipLaunchKernelGGL(k_plan, dim3(1), dim3(kThreads), psmem, st, a);
         hipLaunchKernelGGL(k_perm<bf16_t>, dim3(pl.nPB), dim3(kThreads), (size_t)p->E * 8, st, a);
     }
@@ -893,29 +924,28 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     a.idx = topk_idx; a.w = topk_w; a.counts = counts; a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
     a.slot_flag = slot_flag; a.staging = staging; a.flags = flags; a.out = out;
     a.stats = (u64 *)stats;
-    // few tokens (at most kGateSplitBlocks blocks of 16): split every gate task over the reduction, so that
-    // the gate runs on all workgroups instead of a handful
-    int S = 1;
-    if (Wg && pl.nRT <= kGateSplitBlocks) {
-        S = kGateSplitTasks / pl.nRT;
+    // gate tasks: whole permutation blocks when the routing is an input; fp32 problems of few tokens (at most
+    // kGateSplitBlocks blocks of 16) split every gate task over the reduction, so that the gate runs on all workgroups
+    // instead of a handful
+    int gate_tasks = Wg ? pl.nRT : pl.nPB;
+    if (Wg && p->dtype == MOE_DT_F32 && pl.nRT <= kGateSplitBlocks) {
+        int S = kGateSplitTasks / pl.nRT;
         if (S > kGateSplitMax) S = kGateSplitMax;
         if (S > route_max_slices(p->d)) S = route_max_slices(p->d);
+        if (S > 1) {
+            a.gate_split = S;
+            gate_tasks = pl.nRT * S;
+            a.gate_partial = (double *)((char *)workspace + pl.o_gate_partial);
+            a.gate_parts = (u32 *)((char *)workspace + pl.o_gate_parts);
+        }
     }
-    if (S > 1) {
-        const int extra = pl.nRT * (S - 1);
-        a.gate_split = S;
-        a.nRT = pl.nRT * S;
-        a.gate_partial = (double *)((char *)workspace + pl.o_gate_partial);
-        a.gate_parts = (u32 *)((char *)workspace + pl.o_gate_parts);
-        a.t_plan += extra; a.t_perm += extra; a.t_g1 += extra; a.t_end += extra;
-    } else if (Wg && p->dtype == MOE_DT_BF16 && p->E >= 64) {
-        // bf16 gate with one task or more per workgroup: screen on the bf16 matrix cores, exact fp64 logits for
-        // the candidates only; this needs the gate weights transposed, which the first front tasks of the kernel write
+    if (Wg && p->dtype == MOE_DT_BF16) {
         a.WgT = (char *)workspace + pl.o_wgt;
-        const int ntt = wgt_tasks(p->d, p->E);
-        a.t_gate = ntt;
-        a.t_plan += ntt; a.t_perm += ntt; a.t_g1 += ntt; a.t_end += ntt;
+        a.t_gate = wgt_tasks(p->d, p->E);
     }
+    const int extra = gate_tasks - pl.nRT + a.t_gate;
+    a.nRT = gate_tasks;
+    a.t_plan += extra; a.t_perm += extra; a.t_g1 += extra; a.t_end += extra;
     hipStream_t st = (hipStream_t)stream;
     switch (pl.kind) {
         case TK_F32: return launch_mega<F32Policy, F32Policy>(pl, a, st);

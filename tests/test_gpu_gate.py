@@ -1,0 +1,39 @@
+"""GPU test of the gate's code variants at the edges of their ranges: numbers of experts around the multiples at which
+another variant takes over (and odd ones, whose weight rows are unaligned), reductions of one chunk and of many, tokens
+per task of 4, 8 and 16 with a remainder; standalone and inside the megakernel, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_00686_amd import workloads as W
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+# (T, d, E, k)
+CASES = [(5, 64, 1, 1), (37, 128, 7, 3), (1030, 192, 16, 2), (16, 256, 17, 2), (2050, 128, 32, 4), (65, 320, 33, 6),
+         (1025, 128, 64, 8), (40, 2880, 65, 4), (4100, 64, 128, 8), (33, 192, 129, 8), (130, 128, 192, 8), (70, 256, 200, 8),
+         (2049, 64, 255, 5), (64, 1024, 256, 8)]
+
+
+@pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])
+def test_gate_variants(T, d, E, k):
+    from paper_2605_00686_amd import binding as B
+    print(f"case gate T={T} d={d} E={E} k={k}", flush=True)
+    inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=64, R=1, dtype="bf16", seed=T + E, bias_std=0.3))
+    cfg = inp["cfg"]
+    p = B.problem(T, d, E, k, 64, 1, "bf16", tile_m=cfg["tile_m"], tile_n=cfg["tile_n"])
+    dev = {n: inp[n].cuda() for n in ("x", "Wg", "gate_bias", "W1", "W3", "W2")}
+    ridx, rw, margin = parity.oracle_routing(inp)
+    idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.full((T, k), float("nan"), dtype=torch.float32, device="cuda")
+    B.moe_route(p, dev["x"], dev["Wg"], dev["gate_bias"], idx, w)
+    buf = B.Buffers(p)
+    B.forward(p, buf, dev["x"], dev["Wg"], dev["gate_bias"], dev["W1"], dev["W3"], dev["W2"])
+    torch.cuda.synchronize()
+    assert int(buf.stats[7].item()) == 0
+    # logits and softmax are fp64 on both sides and rounded once: one unit in the last place of fp32 (2^-23) and a little
+    for i2, w2 in ((idx, w), (buf.topk_idx, buf.topk_w)):
+        assert np.array_equal(i2.cpu().numpy(), ridx), f"min margin {margin.min()}"
+        np.testing.assert_allclose(w2.cpu().numpy(), rw, rtol=1.5e-7, atol=0)
+    assert np.array_equal(buf.counts.cpu().numpy(), np.bincount(ridx.reshape(-1), minlength=E))
