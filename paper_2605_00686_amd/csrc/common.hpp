@@ -123,6 +123,7 @@ struct KArgs {
     int rq_cap;                // entries per ready queue: all GEMM2 tiles plus all combine tasks
     size_t zero_bytes;         // bytes from ctrl that must be zero between calls
     int tab_lds_off;           // megakernel: LDS offset of the cached decode tables, 0 = none
+    int plan_all;              // megakernel: every workgroup derives the plan by itself (see PlanAll); needs the cached tables
     int sched_lds_off;         // megakernel: LDS offset of the task loops' broadcast slots (StageLds)
 };
 

@@ -39,6 +39,179 @@ __device__ __forceinline__ int wave_exclusive_scan(const int32_t *src, int32_t *
     return carry;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wavefront (DPP: no trips through LDS).
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+// Exclusive prefix sum by one wavefront over n LDS values in place; returns start + total.
+__device__ __forceinline__ int wave_scan_lds(int *v, int n, int start) {
+    const int lane = threadIdx.x & 63;
+    int carry = start;
+    for (int base = 0; base < n; base += 64) {
+        const int i = base + lane;
+        const int x = i < n ? v[i] : 0;
+        const int inc = wave_inclusive_sum(x);
+        if (i < n) v[i] = carry + inc - x;
+        carry += __builtin_amdgcn_readlane(inc, 63);
+    }
+    return carry;
+}
+
+// ---- the plan in every workgroup (a.plan_all): once all gate tasks are done, each workgroup derives what it needs from
+// the block histograms by itself, in LDS.  The histograms are a few KB to tens of KB that every XCD's L2 serves; a single
+// planning workgroup, whose tables the others wait for and then fetch, took 20 to 25 us instead (cfg2: gate end to last
+// permutation block 37 us, now 15).  What is needed outside (counts, offsets, the flag ranges of the destinations) is
+// written by the one workgroup that drew the plan task.
+// LDS: hist [nPB][E] | segb [R][E] | nfl [R][E] | dest [R+1] | grp [R+1]; the decode tables go to their permanent place.
+constexpr size_t kPlanAllHist = 64 * 1024, kPlanAllSeg = 32 * 1024;
+__host__ __device__ inline bool plan_all_fits(int E, int R, int nPB) {
+    return (size_t)nPB * E * 4 <= kPlanAllHist && (size_t)2 * E * R * 4 <= kPlanAllSeg;
+}
+__host__ __device__ inline size_t plan_all_smem_bytes(int E, int R, int nPB) {
+    return ((size_t)nPB * E + 2 * (size_t)E * R + 2 * (R + 1) + 4) * 4 + (size_t)E * 12 + 64;  // (+ a permutation block's masks and bases)
+}
+struct PlanAll {  // pointers into LDS
+    int *hist, *segb, *nfl, *dest, *grp, *off, *rbb, *rsb, *cnt, *rbe, *rse;
+    char *perm_lds;
+    __device__ __forceinline__ PlanAll(const KArgs &a, char *smem) {
+        hist = (int *)smem;
+        segb = hist + (a.nPB * a.E + 3) / 4 * 4;
+        nfl = segb + a.E * a.R;
+        dest = nfl + a.E * a.R;
+        grp = dest + a.R + 1;
+        perm_lds = smem + ((((a.nPB * a.E + 3) / 4 * 4 + 2 * a.E * a.R + 2 * (a.R + 1)) * 4 + 7) & ~7);
+        off = (int *)(smem + a.tab_lds_off);  // (decode_tables() reads this layout)
+        rbb = off + a.E + 1;
+        rsb = rbb + a.E + 1;
+        cnt = rsb + a.E + 1;
+        rbe = cnt + a.E + 1;
+    }
+};
+// Part 1, every workgroup: counts, offsets, row blocks.  Returns false if an expert is over its capacity.
+__device__ __forceinline__ bool plan_all_tables(const KArgs &a, PlanAll &p, int *n_rb, int *n_rbs) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int E = a.E, R = a.R, nh = a.nPB * E;
+    if ((nh & 3) == 0) {
+        const u32x4_t *src = (const u32x4_t *)a.blk_hist;
+#pragma unroll 8
+        for (int q = tid; q < nh / 4; q += kThreads) ((u32x4_t *)p.hist)[q] = src[q];
+    } else {
+#pragma unroll 8
+        for (int q = tid; q < nh; q += kThreads) p.hist[q] = a.blk_hist[q];
+    }
+    if (!a.seg_from_blocks)
+        for (int q = tid; q < E * R; q += kThreads) {
+            const int r = q / E, e = q - r * E;
+            p.segb[q] = a.seg_cnt[(size_t)e * R + r];
+        }
+    __syncthreads();
+    if (a.seg_from_blocks) {  // a destination is a whole number of blocks: add up its blocks' histograms
+        const int bpd = a.per_dest / kPermBlock;
+        for (int q = tid; q < E * R; q += kThreads) {
+            const int r = q / E, e = q - r * E;
+            const int *h = p.hist + r * bpd * E + e;
+            int n = 0;
+#pragma unroll 4
+            for (int b = 0; b < bpd; ++b) n += h[b * E];
+            p.segb[q] = n;
+        }
+        __syncthreads();
+    }
+    // per expert: rows per destination -> expert-local first row of the destination; rows and row blocks of the expert.
+    // One height: ceil(rows / BM).  Mixed heights: see plan_task.
+    const int lbm = 31 - __clz(a.tl.BM);
+    int over = 0;
+    for (int e = tid; e < E; e += kThreads) {
+        int n = 0;
+#pragma unroll 4
+        for (int r = 0; r < R; ++r) {
+            const int c = p.segb[r * E + e];
+            p.segb[r * E + e] = n;
+            n += c;
+        }
+        p.cnt[e] = n;
+        p.off[e] = n;
+        const int rem = n & (a.tl.BM - 1);
+        const bool small = a.tl.BMS != 0 && rem > 0 && rem <= a.tl.BMS && (!a.tl.tail_with_big || (n >> lbm) == 0);
+        p.rbb[e] = (n >> lbm) + ((rem > 0 && !small) ? 1 : 0);
+        p.rsb[e] = small ? 1 : 0;
+        over |= (a.capacity > 0 && n > a.capacity) ? 1 : 0;
+    }
+    if (__syncthreads_or(over)) return false;
+    if (wave == 0) {
+        const int rows = wave_scan_lds(p.off, E, 0);
+        if (lane == 0) p.off[E] = rows;
+    } else if (wave == 1) {
+        const int rb = wave_scan_lds(p.rbb, E, 0);
+        if (lane == 0) p.rbb[E] = rb;
+    } else if (wave == 2) {
+        const int rb = wave_scan_lds(p.rsb, E, 0);
+        if (lane == 0) p.rsb[E] = rb;
+    }
+    __syncthreads();
+    *n_rb = uniform(p.rbb[E]);
+    *n_rbs = uniform(p.rsb[E]);
+    p.rse = p.rbe + *n_rb;
+    for (int e = tid; e < E; e += kThreads) {
+        for (int i = p.rbb[e]; i < p.rbb[e + 1]; ++i) p.rbe[i] = e;
+        if (p.rsb[e + 1] > p.rsb[e]) p.rse[p.rsb[e]] = e;
+    }
+    if (a.capacity > 0)  // padded layout: expert e owns the `capacity` rows from e * capacity
+        for (int e = tid; e <= E; e += kThreads) p.off[e] = e * a.capacity;
+    __syncthreads();
+    return true;
+}
+// Part 2, the workgroups with a plan or permutation task: flags per (destination, expert) and their ranges.  Flags are
+// destination-major, then expert; a segment with expert-local rows [b0, b0+c) touches row blocks b0/tile_m .. (b0+c-1)/tile_m.
+__device__ __forceinline__ void plan_all_flags(const KArgs &a, const PlanAll &p) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int E = a.E, R = a.R, lm = 31 - __clz(a.tile_m);
+    for (int q = tid; q < E * R; q += kThreads) {
+        const int r = q / E, e = q - r * E;
+        const int b0 = p.segb[q], b1 = r + 1 < R ? p.segb[q + E] : p.cnt[e];
+        p.nfl[q] = b1 > b0 ? (((b1 - 1) >> lm) - (b0 >> lm) + 1) * a.ncb : 0;
+    }
+    __syncthreads();
+    for (int r = wave; r < R; r += 4) {
+        const int total = wave_scan_lds(p.nfl + r * E, E, 0);
+        if (lane == 0) {
+            p.dest[r] = total;
+            // fence groups of the per-destination mode: all flags of a destination, or group_size at a time
+            p.grp[r] = a.group_size > 0 ? (total + a.group_size - 1) / a.group_size : 1;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int total = wave_scan_lds(p.dest, R, 0);
+        if (lane == 0) p.dest[R] = total;
+    } else if (wave == 1) {
+        const int groups = wave_scan_lds(p.grp, R, 0);
+        if (lane == 0) p.grp[R] = groups;
+    }
+    __syncthreads();
+}
+__device__ __forceinline__ void plan_all_publish(const KArgs &a, const PlanAll &p, int n_rb, int n_rbs) {
+    for (int e = threadIdx.x; e <= a.E; e += kThreads) {
+        a.offsets[e] = p.off[e];
+        if (e < a.E) a.counts[e] = p.cnt[e];
+    }
+    for (int r = threadIdx.x; r <= a.R; r += kThreads) {
+        a.dest_flag_begin[r] = p.dest[r];
+        a.dest_group_begin[r] = p.grp[r];
+    }
+    if (threadIdx.x == 0) {
+        a.ctrl->n_rb = (u32)n_rb;
+        a.ctrl->n_rbs = (u32)n_rbs;
+        a.ctrl->n_flags = (u32)p.dest[a.R];
+    }
+}
+
 // Single-workgroup task.  Reads blk_hist[nPB][E] and, unless it can be derived from it, seg_cnt[E][R]
 // (complete),
 // writes counts, offsets, blk_base, seg_begin, flag_base, dest_flag_begin, dest_group_begin,
@@ -285,6 +458,42 @@ __device__ __forceinline__ void perm_task(const KArgs &a, int b, char *smem, con
             const int b0 = a.seg_begin[(size_t)e * a.R + r];
             a.slot_flag[s] = a.flag_base[(size_t)r * E + e] + (ql / a.tile_m - b0 / a.tile_m) * a.ncb;
         }
+    }
+    __syncthreads();
+}
+
+// Permutation block b of the megakernel with the plan in LDS.
+__device__ __forceinline__ void perm_block_lds(const KArgs &a, const PlanAll &p, int b) {
+    const int tid = threadIdx.x;
+    const int E = a.E, k = a.k, lm = 31 - __clz(a.tile_m);
+    u64 *mask = (u64 *)p.perm_lds;  // [E]
+    int *base = (int *)(mask + E);  // [E] sorted position of the block's first slot of e
+    const int t0 = b * kPermBlock;
+    const int nt = min(kPermBlock, a.T - t0);
+    for (int e = tid; e < E; e += kThreads) {
+        mask[e] = 0ull;
+        int n = p.off[e];
+#pragma unroll 4
+        for (int bb = 0; bb < b; ++bb) n += p.hist[bb * E + e];
+        base[e] = n;
+    }
+    __syncthreads();
+    for (int q = tid; q < nt * k; q += kThreads) atomicOr(&mask[a.idx[(size_t)t0 * k + q]], 1ull << (q / k));
+    if (a.capacity > 0) {
+        // padded layout: the unused entries of perm, experts dealt round-robin to the blocks
+        for (int e = b; e < E; e += a.nPB)
+            for (int j = p.cnt[e] + tid; j < a.capacity; j += kThreads) a.perm[(size_t)e * a.capacity + j] = -1;
+    }
+    __syncthreads();
+    for (int q = tid; q < nt * k; q += kThreads) {
+        const int s = t0 * k + q, tl = q / k;
+        const int e = a.idx[s];
+        const int pos = base[e] + __popcll(mask[e] & ((1ull << tl) - 1ull));
+        a.perm[pos] = s;
+        a.inv_perm[s] = pos;
+        const int r = (t0 + tl) / a.per_dest;
+        const int f = r * E + e;
+        a.slot_flag[s] = p.dest[r] + p.nfl[f] + (((pos - p.off[e]) >> lm) - (p.segb[f] >> lm)) * a.ncb;
     }
     __syncthreads();
 }

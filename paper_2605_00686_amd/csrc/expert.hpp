@@ -514,6 +514,7 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, const TileInfo &ti, char
 struct StageLds {  // broadcast slots of a stage's task loop, in dynamic LDS at KArgs::sched_lds_off
     int next, ok;
     int pick;  // tile stage: the list to draw from next, -1 = all lists are empty
+    int n_rb, n_rbs;  // row blocks in use, big / small (from the front stage)
     int q, hops, ticket, g1_left;  // ready-queue scheduler: the workgroup's state (see ready_queue_stage)
 };
 

@@ -182,9 +182,9 @@ __global__ __launch_bounds__(kThreads) void k_combine(KArgs a) {
 }
 
 // Front tasks of the megakernel from their counter, in this order: [gate-weight transposition tiles | gate tasks | plan |
-// permutation blocks].  Returns
-// nonzero if a wait failed or the routing was found invalid.  A real call, like the GEMM stages (see there), so that the
-// gate's registers are its own.
+// permutation blocks]; then the wait for all of them, and the decode tables in LDS.  Returns nonzero if a wait failed or the
+// routing was found invalid; the numbers of row blocks are left in StageLds.  A real call, like the GEMM stages (see
+// there), so that the gate's registers are its own.
 template <typename ET, int V>
 static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 smem_off, volatile int *caller_local) {
     KArgs a = load_kernel_args(args);
@@ -193,80 +193,128 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     const int tid = threadIdx.x;
     Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
-    const u64 t0 = kernel_start_ticks(c);
     *caller_local = 5;  // (see the call sites of tile_stage)
-    __syncthreads();
     if (tid == 0) sl->next = (int)atomicAdd(&c->next_task, 1u);
     if constexpr (V > 0) {
         gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
+    const u64 t0 = kernel_start_ticks(c);
     __syncthreads();
     int task = uniform(sl->next);
-    bool seen_plan = false, seen_wgt = false, bad = false;
-    // (the next task is only drawn when this one is done: there are about as many gate tasks
-    // as workgroups, and drawing ahead would give the first workgroups two each)
-    while (task < a.t_g1) {
-        int phase;
-        if (task < a.t_gate) {
-            phase = 0;
-            if constexpr (V > 0) wgt_task(a, task, smem);
-            sync_stores();
-            if (tid == 0) {
-                fence_release(0);
-                atomicAdd(&c->wgt_done, 1u);
-            }
-        } else if (task < a.t_plan) {
-            phase = 0;
-            route_task<ET, V, true>(a, args, task - a.t_gate, smem, true, &sl->pick, [&]() __attribute__((always_inline)) {
-                if (!seen_wgt) {  // the transposed gate weights are complete
-                    if (tid == 0) sl->ok = wait_ge(c, &c->wgt_done, (u32)a.t_gate, a.wait_ticks) ? 1 : 0;
-                    __syncthreads();
-                    seen_wgt = sl->ok != 0;
-                }
-                return seen_wgt;
-            });
-            sync_stores();
-            if (tid == 0) {
-                fence_release(0);
-                atomicAdd(&c->route_done, 1u);
-            }
-        } else if (task < a.t_perm) {
-            phase = 1;
-            if (tid == 0) sl->ok = wait_ge(c, &c->route_done, (u32)a.nRT, a.wait_ticks) ? 1 : 0;
-            __syncthreads();
-#ifdef MOE_TILE_TIMING
-            if (tid == 0) c->dbg[39] = now_ticks() - c->t0;
-#endif
-            if (sl->ok) plan_task(a, smem);
-            sync_stores();
-            if (tid == 0) {
-                fence_release(0);
-                __hip_atomic_store(&c->plan_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        } else {
-            phase = 2;
-            if (!seen_plan) {
-                if (tid == 0) sl->ok = (wait_ge(c, &c->plan_done, 1u, a.wait_ticks) && ld_relaxed_agent(&c->error) == 0) ? 1 : 0;
-                __syncthreads();
-                seen_plan = true;
-                bad = bad || !sl->ok;
-            }
-            if (!bad) perm_task<ET>(a, task - a.t_perm, smem, a.blk_base + (size_t)(task - a.t_perm) * a.E, a.counts);
-            sync_stores();
-            if (tid == 0) {
-                fence_release(0);
-                atomicAdd(&c->perm_done, 1u);
-            }
-        }
+    auto draw_next = [&](int phase) __attribute__((always_inline)) {
         __syncthreads();
         if (tid == 0) {
-            mark_phase_end(c, phase, t0);
+            if (phase >= 0) mark_phase_end(c, phase, t0);
             sl->next = (int)atomicAdd(&c->next_task, 1u);
         }
         __syncthreads();
         task = uniform(sl->next);
+    };
+    auto wait_for = [&](const u32 *p, u32 target) __attribute__((always_inline)) {
+        __syncthreads();
+        if (tid == 0) sl->ok = !wait_ge(c, p, target, a.wait_ticks) ? 0 : ld_relaxed_agent(&c->error) == 0 ? 1 : 2;
+        __syncthreads();
+        return uniform(sl->ok);  // 0: not reached, 1: reached, 2: reached, but an error is recorded
+    };
+    auto release_and_count = [&](u32 *counter) __attribute__((always_inline)) {
+        sync_stores();
+        if (tid == 0) {
+            fence_release(0);
+            atomicAdd(counter, 1u);
+        }
+    };
+    // (the next task is only drawn when this one is done: there are about as many gate tasks
+    // as workgroups, and drawing ahead would give the first workgroups two each)
+    if constexpr (V > 0) {
+        while (task < a.t_gate) {
+            wgt_task(a, task, smem);
+            release_and_count(&c->wgt_done);
+            draw_next(-1);
+        }
     }
+    bool seen_wgt = false;
+    while (task < a.t_plan) {
+        route_task<ET, V, true>(a, args, task - a.t_gate, smem, true, &sl->pick, [&]() __attribute__((always_inline)) {
+            if (!seen_wgt) seen_wgt = wait_for(&c->wgt_done, (u32)a.t_gate) != 0;  // the transposed gate weights are complete
+            return seen_wgt;
+        });
+        release_and_count(&c->route_done);
+        draw_next(0);
+    }
+    int n_rb = 0, n_rbs = 0;
+    const int routed = wait_for(&c->route_done, (u32)a.nRT);
+    bool bad = routed != 1;
+    if (a.plan_all) {
+        PlanAll p(a, smem);
+        // (counts and offsets are reported also when an id was invalid or an expert is over its capacity)
+        const bool over = routed != 0 && !plan_all_tables(a, p, &n_rb, &n_rbs);
+        if (task == a.t_plan && over) {
+            for (int e = tid; e <= a.E; e += kThreads) {
+                a.offsets[e] = e * a.capacity;
+                if (e < a.E) a.counts[e] = p.cnt[e];
+            }
+            if (tid == 0) set_error(c, MOE_ERR_CAPACITY);
+        } else if (task == a.t_plan && routed == 2) {
+            for (int e = tid; e <= a.E; e += kThreads) {
+                a.offsets[e] = p.off[e];
+                if (e < a.E) a.counts[e] = p.cnt[e];
+            }
+        }
+        bad = bad || over;
+        if (!bad && task < a.t_g1) plan_all_flags(a, p);
+        while (task < a.t_g1) {
+            const bool plan = task < a.t_perm;
+            if (!bad) {
+                if (plan)
+                    plan_all_publish(a, p, n_rb, n_rbs);
+                else
+                    perm_block_lds(a, p, task - a.t_perm);
+            }
+            release_and_count(plan ? &c->plan_done : &c->perm_done);
+            draw_next(plan ? 1 : 2);
+        }
+        bad = wait_for(&c->plan_done, 1u) != 1 || bad;
+    } else {
+        if (task == a.t_plan) {
+            if (routed != 0) plan_task(a, smem);
+            release_and_count(&c->plan_done);
+            draw_next(1);
+        }
+        bad = wait_for(&c->plan_done, 1u) != 1 || bad;
+        while (task < a.t_g1) {
+            const int b = task - a.t_perm;
+            if (!bad) perm_task<ET>(a, b, smem, a.blk_base + (size_t)b * a.E, a.counts);
+            release_and_count(&c->perm_done);
+            draw_next(2);
+        }
+        if (!bad) {
+            n_rb = (int)c->n_rb;
+            n_rbs = (int)c->n_rbs;
+            if (a.tab_lds_off > 0) {  // [offsets | rb_base | rbs_base | counts | rb_expert | rbs_expert]
+                int32_t *t_off = (int32_t *)(smem + a.tab_lds_off);
+                int32_t *t_rbb = t_off + a.E + 1;
+                int32_t *t_rsb = t_rbb + a.E + 1;
+                int32_t *t_cnt = t_rsb + a.E + 1;
+                int32_t *t_rbe = t_cnt + a.E + 1;
+                int32_t *t_rse = t_rbe + n_rb;
+                for (int i = tid; i <= a.E; i += kThreads) {
+                    t_off[i] = a.offsets[i];
+                    t_rbb[i] = a.rb_base[i];
+                    t_rsb[i] = a.rbs_base[i];
+                    t_cnt[i] = i < a.E ? a.counts[i] : 0;
+                }
+                for (int i = tid; i < n_rb; i += kThreads) t_rbe[i] = a.rb_expert[i];
+                for (int i = tid; i < n_rbs; i += kThreads) t_rse[i] = a.rbs_expert[i];
+            }
+        }
+    }
+    bad = wait_for(&c->perm_done, (u32)a.nPB) != 1 || bad;
+    if (tid == 0) {
+        sl->n_rb = n_rb;
+        sl->n_rbs = n_rbs;
+    }
+    __syncthreads();
     return bad ? 1 : 0;
 }
 
@@ -293,7 +341,7 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
     constexpr bool MIXED = !std::is_same<P, PS>::value;
     static_assert(P::MIN_WAVES == PS::MIN_WAVES, "one occupancy for both tile codes");
     extern __shared__ __align__(16) char smem[];
-    __shared__ int s_task, s_ok, s_last;
+    __shared__ int s_last;
     Ctrl *c = a.ctrl;
     const int tid = threadIdx.x;
     const KArgsAddr kargs = kernel_args_address();
@@ -324,38 +372,9 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
     } else {
         front = front_stage<ET, 0>(kargs, lds, &stage_mark);
     }
-    bool bad = uniform(front) != 0;
-
-    // ---- wait for the plan and the permutation (and with them for every gate task); copy
-    // the decode tables to LDS
-    if (tid == 0) s_ok = (wait_ge(c, &c->plan_done, 1u, a.wait_ticks) && ld_relaxed_agent(&c->error) == 0) ? 1 : 0;
-    __syncthreads();
-    bad = bad || !s_ok;
-    int n_rb = 0, n_rbs = 0;
-    if (!bad) {
-        n_rb = (int)c->n_rb;
-        n_rbs = (int)c->n_rbs;
-        if (a.tab_lds_off > 0) {  // [offsets | rb_base | rbs_base | counts | rb_expert | rbs_expert]
-            int32_t *t_off = (int32_t *)(smem + a.tab_lds_off);
-            int32_t *t_rbb = t_off + a.E + 1;
-            int32_t *t_rsb = t_rbb + a.E + 1;
-            int32_t *t_cnt = t_rsb + a.E + 1;
-            int32_t *t_rbe = t_cnt + a.E + 1;
-            int32_t *t_rse = t_rbe + n_rb;
-            for (int i = tid; i <= a.E; i += kThreads) {
-                t_off[i] = a.offsets[i];
-                t_rbb[i] = a.rb_base[i];
-                t_rsb[i] = a.rbs_base[i];
-                t_cnt[i] = i < a.E ? a.counts[i] : 0;
-            }
-            for (int i = tid; i < n_rb; i += kThreads) t_rbe[i] = a.rb_expert[i];
-            for (int i = tid; i < n_rbs; i += kThreads) t_rse[i] = a.rbs_expert[i];
-        }
-    }
-    __syncthreads();
-    if (tid == 0) s_ok = wait_ge(c, &c->perm_done, (u32)a.nPB, a.wait_ticks) ? 1 : 0;
-    __syncthreads();
-    bad = bad || !s_ok;
+    const bool bad = uniform(front) != 0;
+    const StageLds *sl0 = (const StageLds *)(smem + a.sched_lds_off);
+    const int n_rb = uniform(sl0->n_rb), n_rbs = uniform(sl0->n_rbs);
 
     if (!bad) {
         // ---- stage 2: GEMM tiles, one call per kind, this XCD's lists first
@@ -667,12 +686,15 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
     const size_t rsm = gate_task_smem_bytes(pl.p.E, pl.p.d, elem_size(pl.p.dtype));
     if (a_in.Wg && rsm > smem) smem = rsm;
     if (plan_smem(pl) > smem) smem = plan_smem(pl);
+    if (plan_all_fits(pl.p.E, pl.p.R, pl.nPB) && plan_all_smem_bytes(pl.p.E, pl.p.R, pl.nPB) > smem)
+        smem = plan_all_smem_bytes(pl.p.E, pl.p.R, pl.nPB);
     // decode tables live behind everything else, for the life of the workgroup
     const size_t tab_bytes = (size_t)(4 * (pl.p.E + 1) + pl.tl.maxRB + pl.p.E) * 4;
     a.tab_lds_off = 0;
     if (tab_bytes <= 6 * 1024 && smem + tab_bytes + sizeof(StageLds) + 16 <= kLdsBudget) {  // small enough that two workgroups of the 128-row tile still share a CU
         a.tab_lds_off = (int)align_up(smem, 16);
         smem = a.tab_lds_off + tab_bytes;
+        a.plan_all = plan_all_fits(pl.p.E, pl.p.R, pl.nPB) ? 1 : 0;
     }
     a.sched_lds_off = (int)align_up(smem, 16);
     smem = a.sched_lds_off + sizeof(StageLds);
