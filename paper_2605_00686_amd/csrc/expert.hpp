@@ -765,16 +765,16 @@ struct Vec16<float> {
     }
 };
 
-// One token by one wavefront: out_row = sum_j wt[j] * rows[j], fp32 accumulation in
-// slot order, one rounding.  Each lane handles U 16-byte pieces of the row at a
-// time and loads 8/U slots of each before it accumulates them.  STREAM: the rows are read with
+// Pieces [c_begin, c_end) (16 bytes each) of one token's row by one wavefront: out_row = sum_j wt[j] * rows[j], fp32
+// accumulation in slot order, one rounding.  Each lane handles U pieces at a time and loads IF/U slots of each before it
+// accumulates them: IF loads in flight per lane.  STREAM: the rows are read with
 // non-temporal loads (for inputs larger than the last-level cache, which would only churn it).
-template <typename ET, int U, bool STREAM>
-__device__ __forceinline__ void combine_token(const char *rows, const float *wt, char *out_row, int k, int pieces,
+template <typename ET, int IF, int U, bool STREAM>
+__device__ __forceinline__ void combine_token(const char *rows, const float *wt, char *out_row, int k, int c_begin, int c_end,
                                               size_t rstride, int lane) {
     using V = Vec16<ET>;
-    constexpr int KB = 8 / U;
-    for (int c0 = lane; c0 < pieces; c0 += 64 * U) {
+    constexpr int KB = IF / U;
+    for (int c0 = c_begin + lane; c0 < c_end; c0 += 64 * U) {
         float acc[U][V::N];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -787,7 +787,7 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int c = c0 + 64 * u;
-                    if (j0 + jj < k && c < pieces) {
+                    if (j0 + jj < k && c < c_end) {
                         const char *src = rows + (size_t)(j0 + jj) * rstride + (size_t)c * 16;
                         if (STREAM) {
                             const u32x4_t t4 = __builtin_nontemporal_load((const u32x4_t *)src);
@@ -803,7 +803,7 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
                     const float wj = wt[j0 + jj];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        if (c0 + 64 * u < pieces) {
+                        if (c0 + 64 * u < c_end) {
                             float f[V::N];
                             V::unpack(v[u][jj], f);
 #pragma unroll
@@ -816,7 +816,7 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = c0 + 64 * u;
-            if (c < pieces) V::store(out_row + (size_t)c * 16, acc[u]);
+            if (c < c_end) V::store(out_row + (size_t)c * 16, acc[u]);
         }
     }
 }
@@ -826,7 +826,10 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
 // epoch; otherwise check once and report.  Flags are read with relaxed atomic
 // loads (a first pass that keeps many loads in flight, then a spin on whatever
 // was not ready) followed by one acquire fence at the requested scope.  Then
-// one wavefront per token, 16-byte pieces, up to eight rows in flight per lane.
+// one wavefront per token, or several that share a token's row when the task has fewer than four tokens: a task is a chain
+// of trips to memory (flag numbers, flags, rows), so what counts is that all four wavefronts load, and that a workgroup
+// has few tasks.  Inside the megakernel (WAIT), where a CU holds one workgroup, a lane keeps 16 loads in flight; alone, where
+// it holds several, 8.
 template <typename ET, bool WAIT, bool STREAM = false>
 __device__ __forceinline__ void combine_task(const KArgs &a, int task) {
     using V = Vec16<ET>;
@@ -872,20 +875,23 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task) {
         if (WAIT && waited && tid == 0) atomicAdd(&a.ctrl->stats[14], now_ticks() - tw0);
     }
     const size_t rstride = (size_t)a.d * sizeof(ET);
-    for (int tt = wave; tt < nt; tt += 4) {
+    const int share = nt == 1 ? 4 : nt == 2 ? 2 : 1;  // wavefronts per token
+    const int per_wave = (pieces + share - 1) / share, c_begin = (wave % share) * per_wave, c_end = min(c_begin + per_wave, pieces);
+    for (int tt = wave / share; tt < nt; tt += 4 / share) {
         const int t = t_first + tt;
         const char *rows = staging + (size_t)t * k * rstride;
         char *orow = (char *)a.out + (size_t)t * rstride;
         const float *wt = a.w + (size_t)t * k;
-        // eight 16-byte loads in flight per lane whatever k is
+        // IF 16-byte loads in flight per lane whatever k is
+        constexpr int IF = WAIT ? 16 : 8;
         if (k == 1)
-            combine_token<ET, 8, STREAM>(rows, wt, orow, k, pieces, rstride, lane);
+            combine_token<ET, IF, IF, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
         else if (k <= 2)
-            combine_token<ET, 4, STREAM>(rows, wt, orow, k, pieces, rstride, lane);
+            combine_token<ET, IF, IF / 2, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
         else if (k <= 4)
-            combine_token<ET, 2, STREAM>(rows, wt, orow, k, pieces, rstride, lane);
+            combine_token<ET, IF, IF / 4, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
         else
-            combine_token<ET, 1, STREAM>(rows, wt, orow, k, pieces, rstride, lane);
+            combine_token<ET, IF, IF / 8, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
     }
 }
 

@@ -501,9 +501,11 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->nPB = (p->T + kPermBlock - 1) / kPermBlock;
     pl->gate_tok = p->dtype == MOE_DT_BF16 ? gate_tokens(p->T) : kRouteTokens;
     pl->nRT = (p->T + pl->gate_tok - 1) / pl->gate_tok;
-    pl->comb_tokens = p->T >= 16384 ? 16 : p->T >= 8192 ? 8 : p->T >= 2048 ? 4 : 1;
+    // few tokens: no more tasks than a chip full of workgroups has to do in one go, down to one token for all four wavefronts
+    pl->comb_tokens = p->T >= 16384 ? 16 : p->T >= 8192 ? 8 : p->T > 512 ? 4 : p->T > 256 ? 2 : 1;
     // the ready-queue scheduler enqueues combine tasks per destination: none may span two
-    if (p->scheduler == MOE_SCHED_READY_QUEUE && pl->per_dest % pl->comb_tokens != 0) pl->comb_tokens = 1;
+    if (p->scheduler == MOE_SCHED_READY_QUEUE)
+        while (pl->per_dest % pl->comb_tokens != 0) pl->comb_tokens >>= 1;
     pl->nCT = (p->T + pl->comb_tokens - 1) / pl->comb_tokens;
     // tile shape: the smallest row block that holds an average expert, never
     // smaller than the publish tile (a publish tile must not span two compute tiles)
