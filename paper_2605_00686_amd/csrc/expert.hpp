@@ -13,29 +13,29 @@ template <class C>
 struct Bf16Policy {
     using ET = bf16_t;
     using Cfg = C;
-    static constexpr bool FUSED = false;
+    static constexpr bool FUSED = false, BN1_VARIES = false;
     static constexpr int BM = C::BM, BN1 = C::BN / 2, BN2 = C::BN;
     static constexpr int C_STRIDE = C::C_STRIDE;
     static constexpr int SMEM_MAIN = C::SMEM_MAIN;
     // wavefronts per SIMD the kernel is built for: two workgroups per CU where their LDS fits
     static constexpr int MIN_WAVES = (2 * (C::SMEM_MAIN + 8 * 1024) <= 160 * 1024) ? 2 : 1;
     template <bool GATED, class RowPtr, class Hook>
-    static __device__ __forceinline__ void gemm(RowPtr rp, const ET *B0, const ET *B1, int ldb, int ncols, int K,
-                                                char *smem, Hook while_loading) {
+    static __device__ __forceinline__ void gemm(RowPtr rp, const ET *B0, const ET *B1, int ldb, int ncols, int /*nrows*/,
+                                                int K, char *smem, Hook while_loading) {
         gemm_tile_bf16<C, GATED>(rp, B0, B1, ldb, ncols, K, smem, while_loading);
     }
 };
 struct F32Policy {
     using ET = float;
-    static constexpr bool FUSED = false;
+    static constexpr bool FUSED = false, BN1_VARIES = true;
     static constexpr int BM = TileF32::BM, BN1 = TileF32::BN, BN2 = TileF32::BN;
     static constexpr int C_STRIDE = TileF32::C_STRIDE;
     static constexpr int SMEM_MAIN = TileF32::SMEM_MAIN;
     static constexpr int MIN_WAVES = 1;
     template <bool GATED, class RowPtr, class Hook>
-    static __device__ __forceinline__ void gemm(RowPtr rp, const ET *B0, const ET *B1, int ldb, int ncols, int K,
-                                                char *smem, Hook while_loading) {
-        gemm_tile_f32<GATED>(rp, B0, B1, ldb, ncols, K, smem, while_loading);
+    static __device__ __forceinline__ void gemm(RowPtr rp, const ET *B0, const ET *B1, int ldb, int ncols, int nrows,
+                                                int K, char *smem, Hook while_loading) {
+        gemm_tile_f32<GATED>(rp, B0, B1, ldb, ncols, nrows, K, smem, while_loading);
     }
 };
 // The fused FFN (moe_problem_t::fuse_ffn): same main loops, other tile loop (see fused_stage)
@@ -295,7 +295,7 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char 
     };
     const size_t wofs = (size_t)ti.e * a.d * a.f + ti.n0;
     MOE_TT_BEGIN();
-    P::template gemm<true>(rowptr, (const ET *)a.W1 + wofs, (const ET *)a.W3 + wofs, a.f, ti.ncols, a.d, smem, [] {});
+    P::template gemm<true>(rowptr, (const ET *)a.W1 + wofs, (const ET *)a.W3 + wofs, a.f, ti.ncols, ti.nrows, a.d, smem, [] {});
     after_gemm();
     MOE_TT(a.ctrl, 1);
     const int ppr = ti.ncols * (int)sizeof(ET) / 16;
@@ -492,7 +492,7 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, const TileInfo &ti, char
     auto rowptr = [&](int r) { return h + (size_t)(ti.row0 + min(r, ti.nrows - 1)) * a.f; };
     const ET *B0 = (const ET *)a.W2 + (size_t)ti.e * a.f * a.d + ti.n0;
     MOE_TT_BEGIN();
-    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, a.f, smem, [&] { publish_prepare<P>(a, ti, smem); });
+    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, ti.nrows, a.f, smem, [&] { publish_prepare<P>(a, ti, smem); });
     after_gemm();
     MOE_TT(a.ctrl, 7);
     publish_tile<P>(a, ti, smem);
@@ -586,7 +586,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
             };
             MOE_TT_BEGIN();
             if (GATED) {
-                const TileInfo ti = decode_tile<SMALL>(a, tb, tq, i, a.tl.NT1, P::BN1, a.f);
+                const TileInfo ti = decode_tile<SMALL>(a, tb, tq, i, a.tl.NT1, P::BN1_VARIES ? a.tl.BN1 : P::BN1, a.f);
                 MOE_TT(c, 0);
                 const u32 before = g1_tile<P>(a, ti, smem, draw);
                 // ready-queue scheduler: the last GEMM1 tile of a row block enqueues the block's GEMM2

@@ -514,7 +514,9 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     if (p->dtype == MOE_DT_F32) {
         pl->kind = TK_F32;
         bm = TileF32::BM;
-        pl->tl.BN1 = TileF32::BN;
+        // GEMM1 takes 32-column tiles when 64-column ones would not give every CU of the chip a tile
+        const long long blocks = (long long)(pl->N < p->E ? pl->N : p->E) * (avg / bm + 1);
+        pl->tl.BN1 = blocks * ((p->f + TileF32::BN - 1) / TileF32::BN) < 256 ? TileF32::BN_NARROW : TileF32::BN;
         pl->tl.BN2 = TileF32::BN;
     } else if (p->fuse_ffn) {
         // the fused FFN: row blocks of 32 rows for decode-sized experts, else 64; the block's h must fit the LDS
