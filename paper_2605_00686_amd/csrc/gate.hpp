@@ -199,11 +199,18 @@ __device__ __forceinline__ void load_lds16(const void *base, u32 voff, u32 lds_a
                  : "m0", "memory");
 }
 
+// Direct global->LDS loads of 16 bytes are only issued from 16-byte aligned tensors.  A view that starts in between (legal:
+// elements are 2 bytes) takes exact logits of all experts, whose ordinary loads accept any address; the results are the same.
+__device__ __forceinline__ bool gate_loads_direct(const KArgs &a) {
+    return ((((uintptr_t)a.x) | ((uintptr_t)a.Wg)) & 15) == 0;
+}
+
 // The gate weights into this XCD's L2, by all workgroups of the XCD together, each its share of the cache lines (16 bytes
 // of each land in a KB of LDS nobody reads): every workgroup streams all of them, in step with the others, and would
 // otherwise meet memory's latency at every chunk instead of once.  (Where workgroups run is only assumed: round-robin over
 // the XCDs.)  The caller waits for the loads before it uses that KB.
 __device__ __forceinline__ void gate_warm_l2(const KArgs &a, u32 lds_scratch, int wg, int n_wg) {
+    if (!gate_loads_direct(a)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long lines = (long long)a.d * a.E * 2 / 128;
     const int part = wg / kTileQueues, parts = (n_wg + kTileQueues - 1) / kTileQueues;

@@ -37,3 +37,36 @@ def test_gate_variants(T, d, E, k):
         assert np.array_equal(i2.cpu().numpy(), ridx), f"min margin {margin.min()}"
         np.testing.assert_allclose(w2.cpu().numpy(), rw, rtol=1.5e-7, atol=0)
     assert np.array_equal(buf.counts.cpu().numpy(), np.bincount(ridx.reshape(-1), minlength=E))
+
+
+@pytest.mark.parametrize("which", ["x", "Wg"])
+@pytest.mark.parametrize("T,d,E,k", [(21, 128, 16, 2), (70, 64, 128, 8), (33, 192, 129, 8)],
+                         ids=lambda v: str(v))
+def test_gate_of_views_off_16_bytes(T, d, E, k, which):
+    """Contiguous views that start between 16-byte boundaries: the same choices as with the aligned tensors."""
+    from paper_2605_00686_amd import binding as B
+    print(f"case gate view T={T} d={d} E={E} k={k} {which}", flush=True)
+    inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=64, R=1, dtype="bf16", seed=T + E, bias_std=0.3))
+    p = B.problem(T, d, E, k, 64, 1, "bf16")
+    dev = {n: inp[n].cuda() for n in ("x", "Wg", "gate_bias", "W1", "W3", "W2")}
+    room = torch.zeros(dev[which].numel() + 16, dtype=torch.bfloat16, device="cuda")
+    view = room[1:1 + dev[which].numel()].reshape(dev[which].shape)
+    view.copy_(dev[which])
+    assert view.data_ptr() % 16 != 0
+    off = {**dev, which: view}
+    out = []
+    for t in (dev, off):
+        idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+        w = torch.full((T, k), float("nan"), dtype=torch.float32, device="cuda")
+        B.moe_route(p, t["x"], t["Wg"], t["gate_bias"], idx, w)
+        out.append((idx.cpu(), w.cpu()))
+    if which == "Wg":  # (the experts' products ask for aligned rows of x)
+        buf = B.Buffers(p)
+        B.forward(p, buf, dev["x"], view, dev["gate_bias"], dev["W1"], dev["W3"], dev["W2"])
+        torch.cuda.synchronize()
+        assert int(buf.stats[7].item()) == 0
+        out.append((buf.topk_idx.cpu(), buf.topk_w.cpu()))
+    for idx, w in out[1:]:
+        assert torch.equal(idx, out[0][0])
+        # fp64 sums in another order, rounded once: one unit in the last place of fp32 and a little
+        np.testing.assert_allclose(w.numpy(), out[0][1].numpy(), rtol=1.5e-7, atol=0)
