@@ -829,8 +829,10 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
 // one wavefront per token, or several that share a token's row when the task has fewer than four tokens: a task is a chain
 // of trips to memory (flag numbers, flags, rows), so what counts is that all four wavefronts load, and that a workgroup
 // has few tasks.  Inside the megakernel (WAIT), where a CU holds one workgroup, a lane keeps 16 loads in flight; alone, where
-// it holds several, 8.
-template <typename ET, bool WAIT, bool STREAM = false>
+// it holds several, 8.  SHARE = false: a wavefront per token whatever the task has (the standalone launch of four tokens or more
+// per task: with shared rows as a run-time choice it took 28.2 instead of 25.6 us on 4096 x 8 rows of 2048, 93 instead of 82 us
+// on 16384 x 2 rows of 4096).
+template <typename ET, bool WAIT, bool STREAM = false, bool SHARE = true>
 __device__ __forceinline__ void combine_task(const KArgs &a, int task) {
     using V = Vec16<ET>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -875,7 +877,7 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task) {
         if (WAIT && waited && tid == 0) atomicAdd(&a.ctrl->stats[14], now_ticks() - tw0);
     }
     const size_t rstride = (size_t)a.d * sizeof(ET);
-    const int share = nt == 1 ? 4 : nt == 2 ? 2 : 1;  // wavefronts per token
+    const int share = !SHARE ? 1 : nt == 1 ? 4 : nt == 2 ? 2 : 1;  // wavefronts per token
     const int per_wave = (pieces + share - 1) / share, c_begin = (wave % share) * per_wave, c_end = min(c_begin + per_wave, pieces);
     for (int tt = wave / share; tt < nt; tt += 4 / share) {
         const int t = t_first + tt;

@@ -176,9 +176,9 @@ __global__ __launch_bounds__(kThreads) void k_dispatch_finish(KArgs a) {
         z[i] = 0u;
 }
 
-template <typename ET, bool STREAM>
+template <typename ET, bool STREAM, bool SHARE>
 __global__ __launch_bounds__(kThreads) void k_combine(KArgs a) {
-    combine_task<ET, false, STREAM>(a, blockIdx.x);
+    combine_task<ET, false, STREAM, SHARE>(a, blockIdx.x);
 }
 
 // Front tasks of the megakernel from their counter, in this order: [gate-weight transposition tiles | gate tasks | plan |
@@ -1030,17 +1030,18 @@ int moe_combine(const moe_problem_t *p, const void *staging, const uint32_t *fla
     hipStream_t st = (hipStream_t)stream;
     // rows that do not fit the 256 MB last-level cache are streamed past it
     const bool past_cache = (size_t)pl.N * p->d * elem_size(p->dtype) > ((size_t)192 << 20);
-    if (p->dtype == MOE_DT_F32) {
-        if (past_cache)
-            hipLaunchKernelGGL((k_combine<float, true>), dim3(pl.nCT), dim3(kThreads), 0, st, a);
+    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(pl.nCT), dim3(kThreads), 0, st, a); };
+    auto pick = [&](auto et) {
+        using ET = decltype(et);
+        if (pl.comb_tokens < 4)
+            past_cache ? launch(k_combine<ET, true, true>) : launch(k_combine<ET, false, true>);
         else
-            hipLaunchKernelGGL((k_combine<float, false>), dim3(pl.nCT), dim3(kThreads), 0, st, a);
-    } else {
-        if (past_cache)
-            hipLaunchKernelGGL((k_combine<bf16_t, true>), dim3(pl.nCT), dim3(kThreads), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_combine<bf16_t, false>), dim3(pl.nCT), dim3(kThreads), 0, st, a);
-    }
+            past_cache ? launch(k_combine<ET, true, false>) : launch(k_combine<ET, false, false>);
+    };
+    if (p->dtype == MOE_DT_F32)
+        pick(float{});
+    else
+        pick(bf16_t{});
     return hip_ok(hipGetLastError());
 }
 
