@@ -47,6 +47,11 @@ constexpr int kGateSlots = 16;  // standalone second pass: candidates per group 
 __host__ __device__ inline int gate_variant(int E, int d) {
     return E <= 32 ? (d % 128 == 0 ? 1 : 6) : E <= 64 ? 2 : E <= 128 ? 3 : E <= 192 ? 4 : 5;
 }
+// Standalone gate: exact logits of all experts at once where the experts are few and the tokens many or the reduction short.
+// The candidates are a large share of the experts there and the second pass streams the weights again, in chunks it has to
+// transpose.  moe_route, E = 8, exact / screened, us: 16384 tokens of d 4096 140 / 156, of d 1024 52 / 72; 4096 of d 4096
+// 37 / 42; 1024 of d 1024 15 / 16; but 1024 of d 4096 37 / 32.  E = 24: 59 / 46 on 4096 of d 4096.
+__host__ __device__ inline bool route_exact(int T, int E, int d) { return E <= 16 && (T > 2048 || d <= 1024); }
 // Blocks of 16 experts (at most), reduction indices per chunk (divides d; about 8 KB of weights, so that the chunk's
 // latency is spread over enough work), chunk slots per wavefront
 template <int V>

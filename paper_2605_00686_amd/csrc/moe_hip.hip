@@ -820,6 +820,7 @@ int moe_route(const moe_problem_t *p, const void *x, const void *Wg, const float
         return hip_ok(hipGetLastError());
     };
     if (p->dtype == MOE_DT_F32) return launch(k_route<float, 0>);
+    if (route_exact(p->T, p->E, p->d)) return launch(k_route<bf16_t, 0>);
     switch (gate_variant(p->E, p->d)) {
         case 1: return launch(k_route<bf16_t, 1>);
         case 2: return launch(k_route<bf16_t, 2>);

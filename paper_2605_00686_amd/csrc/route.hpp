@@ -370,8 +370,8 @@ template <typename ET, int V, bool WGT, class WgtReady>
 __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int task, char *smem, bool do_hist, int *s_slot,
                                            WgtReady wgt_ready) {
     const int E = a.E, k = a.k;
-    // (bf16 problems with a gate have V > 0)
-    const bool compute = (V > 0 || sizeof(ET) == 4) && a.Wg != nullptr;
+    // (the megakernel's bf16 problems with a gate have V > 0)
+    const bool compute = (V > 0 || !WGT || sizeof(ET) == 4) && a.Wg != nullptr;
     const int S = (compute && a.gate_split > 1) ? a.gate_split : 1;
     const int block = task / S, slice = task % S;
     const int TOK = compute ? a.gate_tok : kPermBlock;

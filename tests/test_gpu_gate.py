@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 # (T, d, E, k)
 CASES = [(5, 64, 1, 1), (37, 128, 7, 3), (1030, 192, 16, 2), (16, 256, 17, 2), (2050, 128, 32, 4), (65, 320, 33, 6),
          (1025, 128, 64, 8), (40, 2880, 65, 4), (4100, 64, 128, 8), (33, 192, 129, 8), (130, 128, 192, 8), (70, 256, 200, 8),
-         (2049, 64, 255, 5), (64, 1024, 256, 8)]
+         (2049, 64, 255, 5), (64, 1024, 256, 8),
+         (2050, 1088, 16, 2), (2049, 64, 17, 3), (40, 1088, 16, 2), (40, 1024, 15, 2), (9, 1088, 3, 1)]
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])
@@ -40,7 +41,7 @@ def test_gate_variants(T, d, E, k):
 
 
 @pytest.mark.parametrize("which", ["x", "Wg"])
-@pytest.mark.parametrize("T,d,E,k", [(21, 128, 16, 2), (70, 64, 128, 8), (33, 192, 129, 8)],
+@pytest.mark.parametrize("T,d,E,k", [(21, 1152, 16, 2), (70, 64, 128, 8), (33, 192, 129, 8)],
                          ids=lambda v: str(v))
 def test_gate_of_views_off_16_bytes(T, d, E, k, which):
     """Contiguous views that start between 16-byte boundaries: the same choices as with the aligned tensors."""
