@@ -241,6 +241,7 @@ __device__ __forceinline__ void route_logits_dispatch(const KArgs &a, int t0, ch
 // Exact logits of all experts in lg[16][E] (LDS) -> top-k by k rounds of a 64-lane butterfly
 // argmax on (value, index), softmax over the chosen k; each wavefront selects for its four
 // tokens (wave, wave + 4, ...) at once, so that the four shuffle chains overlap.  Choices counted in cnt if do_hist.
+// Logits that are no numbers: a position no expert can be given is -1, which count_choice and the dispatch report.
 __device__ __forceinline__ void select_full(const KArgs &a, int t0, int TOK, const double *lg, int *cnt, bool do_hist) {
     constexpr int TPW = kRouteTokens / 4;
     const int E = a.E, k = a.k;
@@ -255,6 +256,22 @@ __device__ __forceinline__ void select_full(const KArgs &a, int t0, int TOK, con
         my_e[i] = -1;
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[i][q] = (lane + 64 * q < E) ? lg[tl * E + lane + 64 * q] : NEG;
+    }
+    // The argmax rounds below need k logits that are numbers above -inf, which is also what marks the experts already
+    // taken; a gate bias of -inf and logits that are no numbers can leave fewer.
+    bool scarce = false;
+    if (E > 64) {
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            int n = 0;
+            u64 nan = 0ull;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                n += __popcll(__ballot(v[i][q] > NEG));
+                nan |= __ballot(v[i][q] != v[i][q]);
+            }
+            scarce = scarce || n < k || nan != 0ull;
+        }
     }
     if (E <= 64) {
         // one logit per lane: its output position is the number of logits that beat it (larger value, or
@@ -278,6 +295,36 @@ __device__ __forceinline__ void select_full(const KArgs &a, int t0, int TOK, con
                 if (lane == j) {
                     my_v[i] = bv;
                     my_e[i] = src;
+                }
+            }
+        }
+    } else if (scarce) {  // by rank, as for up to 64 experts: position j is the lowest expert that exactly j logits beat, or -1
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            int rank[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rank[q] = lane + 64 * q < E ? 0 : (1 << 20);
+            for (int c = 0; c < E; ++c) {
+                const double ov = lg[(wave + 4 * i) * E + c];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    rank[q] += (ov > v[i][q] || (ov == v[i][q] && c < lane + 64 * q)) ? 1 : 0;
+            }
+            for (int j = 0; j < k; ++j) {
+                int be = -1;
+                double bv = NEG;
+#pragma unroll
+                for (int q = 3; q >= 0; --q) {
+                    const u64 m = __ballot(rank[q] == j);
+                    if (m != 0ull) {
+                        const int src = __ffsll((long long)m) - 1;
+                        bv = __shfl(v[i][q], src, 64);
+                        be = src + 64 * q;
+                    }
+                }
+                if (lane == j) {
+                    my_v[i] = bv;
+                    my_e[i] = be;
                 }
             }
         }
