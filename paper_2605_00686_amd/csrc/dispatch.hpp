@@ -93,8 +93,10 @@ struct PlanAll {  // pointers into LDS
         rbe = cnt + a.E + 1;
     }
 };
-// Part 1, every workgroup: counts, offsets, row blocks.  Returns false if an expert is over its capacity.
-__device__ __forceinline__ bool plan_all_tables(const KArgs &a, PlanAll &p, int *n_rb, int *n_rbs) {
+// Part 1, every workgroup: counts, offsets, row blocks.  Returns MOE_OK, MOE_ERR_CAPACITY if an expert is over its capacity, or
+// MOE_ERR_BAD_ROUTING if the counts do not account for every slot; then the counts are valid, and in the second case the
+// offsets before any padding, and nothing else is written.
+__device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *n_rb, int *n_rbs) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, R = a.R, nh = a.nPB * E;
     if ((nh & 3) == 0) {
@@ -143,7 +145,7 @@ __device__ __forceinline__ bool plan_all_tables(const KArgs &a, PlanAll &p, int 
         p.rsb[e] = small ? 1 : 0;
         over |= (a.capacity > 0 && n > a.capacity) ? 1 : 0;
     }
-    if (__syncthreads_or(over)) return false;
+    if (__syncthreads_or(over)) return MOE_ERR_CAPACITY;
     if (wave == 0) {
         const int rows = wave_scan_lds(p.off, E, 0);
         if (lane == 0) p.off[E] = rows;
@@ -155,6 +157,8 @@ __device__ __forceinline__ bool plan_all_tables(const KArgs &a, PlanAll &p, int 
         if (lane == 0) p.rsb[E] = rb;
     }
     __syncthreads();
+    // (rows past N would have no place in the sorted order and their row blocks none in the tables)
+    if (uniform(p.off[E]) != a.N) return MOE_ERR_BAD_ROUTING;
     *n_rb = uniform(p.rbb[E]);
     *n_rbs = uniform(p.rsb[E]);
     p.rse = p.rbe + *n_rb;
@@ -165,7 +169,7 @@ __device__ __forceinline__ bool plan_all_tables(const KArgs &a, PlanAll &p, int 
     if (a.capacity > 0)  // padded layout: expert e owns the `capacity` rows from e * capacity
         for (int e = tid; e <= E; e += kThreads) p.off[e] = e * a.capacity;
     __syncthreads();
-    return true;
+    return MOE_OK;
 }
 // Part 2, the workgroups with a plan or permutation task: flags per (destination, expert) and their ranges.  Flags are
 // destination-major, then expert; a segment with expert-local rows [b0, b0+c) touches row blocks b0/tile_m .. (b0+c-1)/tile_m.
@@ -304,8 +308,10 @@ __device__ __forceinline__ void plan_task(const KArgs &a, char *smem) {
         }
     }
     __syncthreads();
+    int bad = 0;
     if (wave == 0) {
         int rows = wave_exclusive_scan(s_cnt, s_off, E, 1, 0);
+        bad = rows != a.N ? 1 : 0;
         if (a.capacity > 0) {  // padded layout: expert e owns the `capacity` rows from e * capacity
             for (int e = lane; e < E; e += 64) {
                 s_off[e] = e * a.capacity;
@@ -323,7 +329,14 @@ __device__ __forceinline__ void plan_task(const KArgs &a, char *smem) {
             a.ctrl->n_rbs = (u32)rbs;
         }
     }
-    __syncthreads();
+    if (__syncthreads_or(bad)) {  // the counts do not account for every slot: they and the status say so, nothing else is written
+        for (int e = tid; e <= E; e += kThreads) {
+            a.offsets[e] = s_off[e];
+            if (e < E) a.counts[e] = s_cnt[e];
+        }
+        if (tid == 0) set_error(a.ctrl, MOE_ERR_BAD_ROUTING);
+        return;
+    }
     for (int e = tid; e <= E; e += kThreads) {
         a.offsets[e] = s_off[e];
         a.rb_base[e] = s_rb[e];
@@ -478,7 +491,10 @@ __device__ __forceinline__ void perm_block_lds(const KArgs &a, const PlanAll &p,
         base[e] = n;
     }
     __syncthreads();
-    for (int q = tid; q < nt * k; q += kThreads) atomicOr(&mask[a.idx[(size_t)t0 * k + q]], 1ull << (q / k));
+    for (int q = tid; q < nt * k; q += kThreads) {
+        const int e = a.idx[(size_t)t0 * k + q];
+        if (e >= 0 && e < E) atomicOr(&mask[e], 1ull << (q / k));
+    }
     if (a.capacity > 0) {
         // padded layout: the unused entries of perm, experts dealt round-robin to the blocks
         for (int e = b; e < E; e += a.nPB)
@@ -488,6 +504,7 @@ __device__ __forceinline__ void perm_block_lds(const KArgs &a, const PlanAll &p,
     for (int q = tid; q < nt * k; q += kThreads) {
         const int s = t0 * k + q, tl = q / k;
         const int e = a.idx[s];
+        if (e < 0 || e >= E) continue;
         const int pos = base[e] + __popcll(mask[e] & ((1ull << tl) - 1ull));
         a.perm[pos] = s;
         a.inv_perm[s] = pos;

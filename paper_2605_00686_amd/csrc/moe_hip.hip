@@ -247,21 +247,17 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     bool bad = routed != 1;
     if (a.plan_all) {
         PlanAll p(a, smem);
-        // (counts and offsets are reported also when an id was invalid or an expert is over its capacity)
-        const bool over = routed != 0 && !plan_all_tables(a, p, &n_rb, &n_rbs);
-        if (task == a.t_plan && over) {
+        // (counts and offsets are reported also when an id was invalid or an expert is over its capacity, unless the error
+        // cut the wait short)
+        const int planned = routed != 0 ? plan_all_tables(a, p, &n_rb, &n_rbs) : MOE_OK;
+        if (task == a.t_plan && routed != 0 && (routed == 2 || planned != MOE_OK)) {
             for (int e = tid; e <= a.E; e += kThreads) {
-                a.offsets[e] = e * a.capacity;
+                a.offsets[e] = a.capacity > 0 ? e * a.capacity : p.off[e];
                 if (e < a.E) a.counts[e] = p.cnt[e];
             }
-            if (tid == 0) set_error(c, MOE_ERR_CAPACITY);
-        } else if (task == a.t_plan && routed == 2) {
-            for (int e = tid; e <= a.E; e += kThreads) {
-                a.offsets[e] = p.off[e];
-                if (e < a.E) a.counts[e] = p.cnt[e];
-            }
+            if (tid == 0 && planned != MOE_OK) set_error(c, planned);
         }
-        bad = bad || over;
+        bad = bad || planned != MOE_OK;
         if (!bad && task < a.t_g1) plan_all_flags(a, p);
         while (task < a.t_g1) {
             const bool plan = task < a.t_perm;

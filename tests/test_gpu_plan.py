@@ -36,3 +36,35 @@ def test_plan_forms(T, E, R, k, tile_m, capacity):
     assert np.array_equal(buf.slot_flag.cpu().numpy(), plan["slot_flag"])
     assert np.all(buf.flags.cpu().numpy()[:plan["n_flags"]] == 1)
     assert int(buf.stats[0].item()) == plan["fences_per_dest"]
+
+
+@pytest.mark.parametrize("T,E,R", [(192, 64, 64), (195, 64, 65)], ids=["every_workgroup", "one_workgroup"])
+@pytest.mark.parametrize("capacity", [0, 192])
+def test_plan_reports_slots_that_no_expert_counts(T, E, R, capacity):
+    """An id outside [0, E) among routing that is an input, either form of the plan and either layout: reported, nothing else
+    written (perm keeps its poison), and the workspace is good for the next call."""
+    from paper_2605_00686_amd import binding as B
+    print(f"case plan bad id T={T} E={E} R={R} capacity={capacity}", flush=True)
+    inp = W.make_inputs(dict(T=T, d=64, E=E, k=2, f=64, R=R, dtype="bf16", seed=5, tile_m=32))
+    p = B.problem(T, 64, E, 2, 64, R, "bf16", tile_m=32, capacity=capacity)
+    buf = B.Buffers(p)
+    good = (torch.arange(T)[:, None] + torch.arange(2)[None, :] * 3) % E
+    dev = {n: inp[n].cuda() for n in ("x", "W1", "W3", "W2")}
+    buf.topk_w.fill_(0.5)
+    buf.perm.fill_(-7)
+    for bad_id in (E, -1, 1 << 20):
+        ids = good.clone()
+        ids[T // 2, 1] = bad_id
+        buf.topk_idx.copy_(ids)
+        B.forward(p, buf, dev["x"], None, None, dev["W1"], dev["W3"], dev["W2"])
+        torch.cuda.synchronize()
+        assert int(buf.stats[7].item()) == B.MOE_ERR_BAD_ROUTING
+        assert bool((buf.perm == -7).all().item())
+    buf.topk_idx.copy_(good)
+    p.epoch = 2
+    B.forward(p, buf, dev["x"], None, None, dev["W1"], dev["W3"], dev["W2"])
+    torch.cuda.synchronize()
+    assert int(buf.stats[7].item()) == 0
+    counts, offsets, perm, inv = oracle.dispatch(good.to(torch.int32).numpy(), E, capacity)
+    assert np.array_equal(buf.counts.cpu().numpy(), counts) and np.array_equal(buf.perm.cpu().numpy(), perm)
+    assert np.array_equal(buf.offsets.cpu().numpy(), offsets) and np.array_equal(buf.inv_perm.cpu().numpy(), inv)
