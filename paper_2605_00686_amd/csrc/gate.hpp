@@ -16,7 +16,9 @@
 //   candidates   {e : L~ + eps >= tau}: every expert whose exact logit reaches the k-th
 //                largest exact logit is among them, ties included
 // If a token ever has more than 64 candidates (logits closer together than their error
-// bound, e.g. all equal) the task falls back to exact logits for all experts.
+// bound, e.g. all equal), or a logit or its bound is not finite (a NaN or an infinity in x or
+// Wg: such bounds order nothing), the task falls back to exact logits for all experts.  An
+// expert masked by a bias of -inf is no such case: its logit is -inf, exactly.
 //
 // First pass.  The reduction is split over the four wavefronts, which then work without
 // barriers: each streams its slice of the gate weights, as they lie in memory ([d][E]),
@@ -331,7 +333,8 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
                 load_lds16(x + (size_t)c_begin * KC * 2, (u32)((min(t0 + row, a.T - 1) - t0) * d * 2 + min(l, lpr - 1) * 128),
                            lds_offset(smem + G::O_EXACT));
     }
-    for (int e = tid; e < E; e += kThreads) s_bias[e] = a.bias ? a.bias[e] : 0.f;
+    static_assert(kThreads == kMaxExperts, "one bias per thread");
+    s_bias[tid] = a.bias && tid < E ? a.bias[tid] : 0.f;
     // MFMA operands of a chunk: lane l feeds token (or expert) l % 16 and reduction indices 8 * (l / 16) .. + 7 of a step of
     // 32 (expert columns past the padded row read a valid piece and are masked in the end)
     int b_off[NB];
@@ -455,7 +458,10 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
         const int tl = (tid >> 4) & (TOK - 1);  // (with fewer tokens than 16 the other lane rows repeat them)
         const float scale = (float)(d + 64) * (1.0f / 4194304.0f);  // (d + 64) * 2^-22
         const float *L0 = (const float *)(smem + G::O_SLOTS) + tl * (16 * NB) + li;
+        // (the bias addition: |logit| is at most the sum of magnitudes plus |bias|, hence twice the latter)
+        const float s_mag = 1.01f * (scale + 1.0f / 4194304.0f), s_add = 1.01f * 2.0f / 4194304.0f;
         u32 klo[NB], khi[NB], kmax = 0u;
+        u32 huge = 0u;  // largest bit pattern of a magnitude: from 0x7f800000 on it is no finite number
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             float l = 0.f, mag = 0.f;
@@ -466,7 +472,8 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
             }
             const float bias = s_bias[(li + 16 * q) & (kMaxExperts - 1)];
             l += bias;
-            const float eps = 1.01f * (mag * scale + (fabsf(l) + fabsf(bias)) * (1.0f / 4194304.0f)) + 1e-30f;
+            huge = max(max(huge, __float_as_uint(mag)), bias == -__builtin_huge_valf() ? 0u : __float_as_uint(l) & 0x7fffffffu);
+            const float eps = fmaf(mag, s_mag, fmaf(fminf(fabsf(bias), 3.4e38f), s_add, 1e-30f));
             klo[q] = li + 16 * q < E ? float_key(l - eps) : 0u;
             khi[q] = li + 16 * q < E ? float_key(l + eps) : 0u;
             kmax = max(kmax, klo[q]);
@@ -499,8 +506,8 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
             if (in && pos < kMaxCand && (tid >> 4) < TOK) cand[tl * kMaxCand + pos] = li + 16 * q;
             before += __popc(m);
         }
-        // (fewer than k: logits that are no numbers)
-        if (li == 0 && (tid >> 4) < TOK) s_ncand[tl] = before < k ? kMaxCand + 1 : before;
+        const bool odd = row_max16(huge) >= 0x7f800000u;
+        if (li == 0 && (tid >> 4) < TOK) s_ncand[tl] = odd ? kMaxCand + 1 : before;
     }
     __syncthreads();
     const int n_max = uniform((int)row_max16(li < TOK ? (u32)s_ncand[li] : 0u));

@@ -35,6 +35,12 @@ def spoil(inp, kind, E, k):
         inp["Wg"][11, E - 1] = NAN
     elif kind == "inf_row":
         inp["x"][T - 1, 3] = INF
+    elif kind == "inf_bias":
+        inp["gate_bias"][E // 2] = INF
+    elif kind == "nan_bias":
+        inp["gate_bias"][0] = NAN
+    elif kind == "masked_finite":  # every second expert, with the lowest finite number
+        inp["gate_bias"][1::2] = torch.finfo(torch.float32).min
     elif kind == "masked":  # every second expert
         inp["gate_bias"][1::2] = -INF
     elif kind == "all_but_few":  # fewer than k are left
@@ -43,6 +49,7 @@ def spoil(inp, kind, E, k):
 
 def check(B, cfg, kind):
     print(f"case not finite {kind} {cfg}", flush=True)
+    cfg = dict(cfg, f=64, R=1, bias_std=0.3)
     T, d, E, k = (cfg[n] for n in ("T", "d", "E", "k"))
     inp = W.make_inputs(cfg)
     spoil(inp, kind, E, k)
@@ -82,7 +89,7 @@ def check(B, cfg, kind):
     assert int(buf.stats[7].item()) == 0 and int(buf.counts.sum().item()) == T * k
 
 
-KINDS = ["nan_row", "nan_column", "inf_row", "masked", "all_but_few"]
+KINDS = ["nan_row", "nan_column", "inf_row", "inf_bias", "nan_bias", "masked", "masked_finite", "all_but_few"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
@@ -90,4 +97,16 @@ KINDS = ["nan_row", "nan_column", "inf_row", "masked", "all_but_few"]
 def test_exact_gate_of_more_than_64_experts(E, k, kind):
     """fp32 problems: the selection on exact logits of all experts."""
     from paper_2605_00686_amd import binding as B
-    check(B, dict(T=37, d=64, E=E, k=k, f=64, R=1, dtype="f32", seed=E + k, bias_std=0.3), kind)
+    check(B, dict(T=37, d=64, E=E, k=k, dtype="f32", seed=E + k), kind)
+
+
+# (T, d, E, k): every code variant of the screen, tasks of 4, 8 and 16 tokens, rows of Wg off 16 bytes; experts few enough
+# that all of a token's could pass as candidates, and more
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("T,d,E,k", [(37, 1152, 8, 2), (9, 1088, 16, 4), (37, 192, 48, 8), (2050, 64, 48, 6), (70, 64, 64, 8),
+                                     (1030, 64, 64, 3), (37, 128, 65, 8), (37, 128, 128, 8), (33, 64, 192, 8), (40, 64, 256, 5)],
+                         ids=lambda v: str(v))
+def test_screened_gate(T, d, E, k, kind):
+    """bf16 problems: bounds that are not finite select no candidates."""
+    from paper_2605_00686_amd import binding as B
+    check(B, dict(T=T, d=d, E=E, k=k, dtype="bf16", seed=E + k), kind)
