@@ -236,7 +236,7 @@ __device__ __forceinline__ void mark_phase_end(Ctrl *c, int phase, u64 t0) {
 #define MOE_TT(ctrl, slot)                                     \
     do {                                                       \
         const u64 tt_now_ = now_ticks();                       \
-        if (threadIdx.x == 0) atomicAdd(&(ctrl)->dbg[slot], tt_now_ - tt_prev_); \
+        if (threadIdx.x == 0 && (ctrl)) atomicAdd(&(ctrl)->dbg[slot], tt_now_ - tt_prev_); \
         tt_prev_ = tt_now_;                                    \
     } while (0)
 #else
