@@ -15,10 +15,13 @@
 //                logit >= tau
 //   candidates   {e : L~ + eps >= tau}: every expert whose exact logit reaches the k-th
 //                largest exact logit is among them, ties included
-// If a token ever has more than 64 candidates (logits closer together than their error
-// bound, e.g. all equal), or a logit or its bound is not finite (a NaN or an infinity in x or
-// Wg: such bounds order nothing), the task falls back to exact logits for all experts.  An
-// expert masked by a bias of -inf is no such case: its logit is -inf, exactly.
+// A row of zeros (a padded slot of a decode step) has the biases as its logits, exactly: no
+// error bound, and of the experts that tie for the last places only the first are candidates.
+// Other logits closer together than their error bounds make many candidates.  A task of 4 tokens
+// has room for all E of each; if a token of a larger task has more than there is room for
+// (kCandidates), or a logit or its bound is not finite (a NaN or an infinity in x or Wg: such
+// bounds order nothing), the task falls back to exact logits for all experts.  An expert masked
+// by a bias of -inf is no such case: its logit is -inf, exactly.
 //
 // First pass.  The reduction is split over the four wavefronts, which then work without
 // barriers: each streams its slice of the gate weights, as they lie in memory ([d][E]),
@@ -41,7 +44,7 @@
 
 namespace moe {
 
-constexpr int kMaxCand = 64;
+constexpr int kCandidates = 1024;  // of a task: 64 per token of 16, 128 of 8, 256 of 4
 constexpr int kGateSlots = 16;  // standalone second pass: candidates per group of lanes and sweep over the reduction
 
 // The gate's code for a problem: 1 .. 6 = route_screened for bf16, by E and d; 0 = exact logits of all experts (fp32; also
@@ -67,13 +70,13 @@ struct GateCfg {
     // LDS: the task's expert counts, the bias, candidates, their exact logits, numbers of candidates, the wavefronts' slots
     static constexpr int O_BIAS = kMaxExperts * 4;
     static constexpr int O_CAND = O_BIAS + kMaxExperts * 4;
-    static constexpr int O_EXACT = O_CAND + kRouteTokens * kMaxCand * 4;
-    static constexpr int O_NCAND = O_EXACT + kRouteTokens * kMaxCand * 8;
+    static constexpr int O_EXACT = O_CAND + kCandidates * 4;
+    static constexpr int O_NCAND = O_EXACT + kCandidates * 8;
     static constexpr int O_SLOTS = O_NCAND + 128;
     static constexpr int TOTAL = O_SLOTS + 4 * WAVE;
     static_assert(WAVE >= kRouteTokens * 16 * NB * 8, "a wavefront's approximate logits and magnitudes take its slots' place");
     static_assert(WAVE >= kGateSlots * 64 * 8, "so do its partial exact logits ...");
-    static_assert(4 * WAVE >= kRouteTokens * kMaxCand * 4 * 8, "... in either form of the second pass");
+    static_assert(4 * WAVE >= kCandidates * 4 * 8, "... in either form of the second pass");
 };
 __host__ __device__ inline int gate_screened_lds(int variant) {
     switch (variant) {
@@ -246,9 +249,10 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
     const int ppr = (E + 7) / 8;                     // pieces per (padded) weight row
     int *cnt = (int *)smem;
     float *s_bias = (float *)(smem + G::O_BIAS);
-    int *cand = (int *)(smem + G::O_CAND);           // [16][64] candidate experts
-    double *exact = (double *)(smem + G::O_EXACT);   // [16][64] their exact logits
-    int *s_ncand = (int *)(smem + G::O_NCAND);       // [16]
+    const int llpt = 8 - (31 - __clz(TOK)), lmc = llpt + 2;  // log2 of: threads, and candidates at most, per token
+    int *cand = (int *)(smem + G::O_CAND);           // [TOK][1 << lmc] candidate experts
+    double *exact = (double *)(smem + G::O_EXACT);   // [TOK][1 << lmc] their exact logits
+    int *s_ncand = (int *)(smem + G::O_NCAND);       // [TOK]
     // the wavefront's chunk slots; after the first pass its partial logits [16][16 * NB] and sums of magnitudes
     char *wslots = smem + G::O_SLOTS + wave * G::WAVE;
     const u32 wslots_lds = lds_offset(wslots);
@@ -461,7 +465,7 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
         // (the bias addition: |logit| is at most the sum of magnitudes plus |bias|, hence twice the latter)
         const float s_mag = 1.01f * (scale + 1.0f / 4194304.0f), s_add = 1.01f * 2.0f / 4194304.0f;
         u32 klo[NB], khi[NB], kmax = 0u;
-        u32 huge = 0u;  // largest bit pattern of a magnitude: from 0x7f800000 on it is no finite number
+        u32 mmax = 0u, lmax = 0u;  // largest bit pattern of a magnitude and of a logit: from 0x7f800000 on no finite number
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             float l = 0.f, mag = 0.f;
@@ -472,11 +476,33 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
             }
             const float bias = s_bias[(li + 16 * q) & (kMaxExperts - 1)];
             l += bias;
-            huge = max(max(huge, __float_as_uint(mag)), bias == -__builtin_huge_valf() ? 0u : __float_as_uint(l) & 0x7fffffffu);
+            mmax = max(mmax, __float_as_uint(mag));
+            lmax = max(lmax, bias == -__builtin_huge_valf() ? 0u : __float_as_uint(l) & 0x7fffffffu);
             const float eps = fmaf(mag, s_mag, fmaf(fminf(fabsf(bias), 3.4e38f), s_add, 1e-30f));
             klo[q] = li + 16 * q < E ? float_key(l - eps) : 0u;
             khi[q] = li + 16 * q < E ? float_key(l + eps) : 0u;
             kmax = max(kmax, klo[q]);
+        }
+        bool zero = false;  // a row of zeros
+        if (__builtin_expect(__any(mmax == 0u) != 0, 0)) {
+            zero = row_max16(mmax) == 0u;  // (so far: no product large enough for fp32)
+            const char *xr = x + (size_t)(min(t0 + tl, a.T - 1) - t0) * d * 2;
+            u32 bits = 0u;
+            for (int o = li * 16; o < 2 * d; o += 8 * 256) {
+                u32x4_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = *(const u32x4_t *)(xr + min(o + 256 * u, 2 * d - 16));
+#pragma unroll
+                for (int u = 0; u < 8; ++u) bits |= v[u][0] | v[u][1] | v[u][2] | v[u][3];
+            }
+            const u32 row_bits = row_max16(bits & 0x7fff7fffu);
+            zero = zero && row_bits == 0u;
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+                if (zero && li + 16 * q < E) {
+                    klo[q] = khi[q] = float_key(0.f + s_bias[(li + 16 * q) & (kMaxExperts - 1)]);
+                    kmax = max(kmax, klo[q]);
+                }
         }
         // K: the k-th largest lower bound, or a smaller one that still parts the keys at k (what is needed is that at least
         // k lower bounds reach K): bisection between the largest key and none, over as soon as exactly k keys reach K
@@ -498,42 +524,64 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
             if (__all(found)) break;
         }
         int before = 0;
+        auto collect = [&](auto in) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const bool in = khi[q] >= K && khi[q] != 0u;
-            const u32 m = (u32)(__ballot(in) >> (lane & 48)) & 0xffffu;  // this token's 16 lanes
-            const int pos = before + __popc(m & ((1u << li) - 1u));
-            if (in && pos < kMaxCand && (tid >> 4) < TOK) cand[tl * kMaxCand + pos] = li + 16 * q;
-            before += __popc(m);
+            for (int q = 0; q < NB; ++q) {
+                const bool mine = in(q);
+                const u32 m = (u32)(__ballot(mine) >> (lane & 48)) & 0xffffu;  // this token's 16 lanes
+                const int pos = before + (int)__popc(m & ((1u << li) - 1u));
+                if (mine && pos < (1 << lmc) && (tid >> 4) < TOK) cand[(tl << lmc) + pos] = li + 16 * q;
+                before += (int)__popc(m);
+            }
+        };
+        if (__builtin_expect(__any(zero) != 0, 0)) {
+            int left = 0;  // places of a row of zeros left for the experts at K, in their order
+#pragma unroll
+            for (int q = 0; q < NB; ++q) left += klo[q] > K ? 1 : 0;
+            left = k - row_sum16(left);
+            collect([&](int q) __attribute__((always_inline)) {
+                const bool in = khi[q] >= K && khi[q] != 0u, tie = zero && in && khi[q] == K;
+                const u32 m = (u32)(__ballot(tie) >> (lane & 48)) & 0xffffu;
+                const bool late = tie && (int)__popc(m & ((1u << li) - 1u)) >= left;
+                left -= (int)__popc(m);
+                return in && !late;
+            });
+        } else {
+            collect([&](int q) __attribute__((always_inline)) { return khi[q] >= K && khi[q] != 0u; });
         }
-        const bool odd = row_max16(huge) >= 0x7f800000u;
-        if (li == 0 && (tid >> 4) < TOK) s_ncand[tl] = odd ? kMaxCand + 1 : before;
+        const bool odd = row_max16(max(mmax, lmax)) >= 0x7f800000u;
+        if (li == 0 && (tid >> 4) < TOK) s_ncand[tl] = odd ? kCandidates + 1 : before;
     }
     __syncthreads();
     const int n_max = uniform((int)row_max16(li < TOK ? (u32)s_ncand[li] : 0u));
     MOE_TT(a.ctrl, 41);
-    if (n_max > kMaxCand) {
+    if (n_max > (1 << lmc)) {
         __syncthreads();
         return false;
     }
 
     if constexpr (WGT) {
-        // ---- second pass, exact fp64 logits of the candidates: a wavefront takes every fourth token, four of its candidates
-        // at a time, 512 reduction indices per step (16 bytes per lane and row), UM steps' loads in flight
+        // ---- second pass, exact fp64 logits of the candidates: a wavefront takes every fourth group of four candidates of a
+        // token (groups counted over all tokens, so that a token of many keeps all wavefronts busy), 512 reduction indices
+        // per step (16 bytes per lane and row), UM steps' loads in flight
         if (!wgt_ready()) return true;
         constexpr int CG = 4, UM = 4;
-        double *part = (double *)(smem + G::O_SLOTS);  // [16][64][4]: sums over the 16 lanes of each DPP row
+        double *part = (double *)(smem + G::O_SLOTS);  // [TOK][1 << lmc][4]: sums over the 16 lanes of each DPP row
         const char *WgT = (const char *)a.WgT;
         const int nm = (d + 511) / 512;
-        for (int tl = wave; tl < TOK; tl += 4) {
-            const int n = uniform(s_ncand[tl]);
+        const int my_n = s_ncand[li & (TOK - 1)];
+        int groups = 0;
+        for (int tl = 0; tl < TOK; ++tl) {
+            const int n = __builtin_amdgcn_readlane(my_n, tl);
             const char *xr = x + (size_t)(min(t0 + tl, a.T - 1) - t0) * d * 2;
-            for (int c0 = 0; c0 < n; c0 += CG) {
+            const int first = CG * ((wave - groups) & 3);
+            groups += (n + CG - 1) / CG;
+            for (int c0 = first; c0 < n; c0 += 4 * CG) {
                 const char *wr[CG];
                 double acc[CG];
 #pragma unroll
                 for (int i = 0; i < CG; ++i) {
-                    wr[i] = WgT + (size_t)uniform(cand[tl * kMaxCand + min(c0 + i, n - 1)]) * d * 2;
+                    wr[i] = WgT + (size_t)uniform(cand[(tl << lmc) + min(c0 + i, n - 1)]) * d * 2;
                     acc[i] = 0.0;
                 }
                 for (int m0 = 0; m0 < nm; m0 += UM) {
@@ -566,15 +614,17 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
 #pragma unroll
                 for (int i = 0; i < CG; ++i) {
                     const double s = row_sum16(acc[i]);
-                    if (li == 0 && c0 + i < n) part[(tl * kMaxCand + c0 + i) * 4 + kq] = s;
+                    if (li == 0 && c0 + i < n) part[((tl << lmc) + c0 + i) * 4 + kq] = s;
                 }
             }
         }
         __syncthreads();
-        for (int i = tid; i < TOK * kMaxCand; i += kThreads) {
-            const int c = i % kMaxCand, t = i / kMaxCand;
-            if (c < s_ncand[t])
+        {
+            const int t = tid >> llpt, n = s_ncand[t];
+            for (int c = tid & ((1 << llpt) - 1); c < n; c += 1 << llpt) {
+                const int i = (t << lmc) + c;
                 exact[i] = (double)s_bias[cand[i]] + ((part[4 * i] + part[4 * i + 1]) + (part[4 * i + 2] + part[4 * i + 3]));
+            }
         }
         __syncthreads();
     } else {
@@ -588,7 +638,7 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
             int eoff[kGateSlots];  // the candidate's row of T, with the swizzle in the lowest bits
 #pragma unroll
             for (int s = 0; s < kGateSlots; ++s) {
-                const int e = cand[tl * kMaxCand + min(base + sub + s * gpt, n - 1)];
+                const int e = cand[(tl << lmc) + min(base + sub + s * gpt, n - 1)];
                 eoff[s] = e * (KC * 2) + ((j ^ swz(e)) * 16);
                 acc[s] = 0.0;
             }
@@ -633,17 +683,16 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
 #pragma unroll
             for (int s = 0; s < kGateSlots; ++s) part[s * 64 + lane] = acc[s];
             __syncthreads();
-            for (int i = tid; i < TOK * kMaxCand; i += kThreads) {
-                const int c = i % kMaxCand, t = i / kMaxCand, cs = c - base;
-                if (cs >= 0 && c < s_ncand[t] && cs < kGateSlots * gpt) {
-                    const int at = (cs / gpt) * 64 + (t + TOK * (cs % gpt)) * 4;
-                    double v = (double)s_bias[cand[i]];
-                    for (int w = 0; w < 4; ++w) {
-                        const double *pw = (const double *)(smem + G::O_SLOTS + w * G::WAVE) + at;
-                        v += (pw[0] + pw[1]) + (pw[2] + pw[3]);
-                    }
-                    exact[i] = v;
+            const int t = tid >> llpt, c_end = min(s_ncand[t], base + kGateSlots * gpt);
+            for (int c = base + (tid & ((1 << llpt) - 1)); c < c_end; c += 1 << llpt) {
+                const int i = (t << lmc) + c, cs = c - base;
+                const int at = (cs / gpt) * 64 + (t + TOK * (cs % gpt)) * 4;
+                double v = (double)s_bias[cand[i]];
+                for (int w = 0; w < 4; ++w) {
+                    const double *pw = (const double *)(smem + G::O_SLOTS + w * G::WAVE) + at;
+                    v += (pw[0] + pw[1]) + (pw[2] + pw[3]);
                 }
+                exact[i] = v;
             }
             __syncthreads();
         }
@@ -651,34 +700,43 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
     MOE_TT(a.ctrl, 42);
 
     // ---- select: the output position of a candidate is the number of candidates that beat it (larger logit, or equal
-    // and lower expert id); softmax over the k selected.  16 lanes per token, lane j holds candidates j, j + 16, ...
+    // and lower expert id); softmax over the k selected.  16 lanes per token (more where the candidates ask for it), lane j
+    // holds candidates j, j + lanes, ...
     {
-        const int tl = tid >> 4;
+        constexpr int CPL = kCandidates / kThreads;  // candidates per lane, at most
+        const int ll = n_max <= 16 * CPL ? 4 : llpt, lpt = 1 << ll;
+        const int tl = tid >> ll, lj = tid & (lpt - 1);
         const bool live = tl < TOK && t0 + tl < a.T;
         const int n = live ? s_ncand[tl] : 0;
-        const double *ev = exact + (live ? tl : 0) * kMaxCand;
-        const int *ce = cand + (live ? tl : 0) * kMaxCand;
+        const double *ev = exact + ((live ? tl : 0) << lmc);
+        const int *ce = cand + ((live ? tl : 0) << lmc);
         double top = -__builtin_huge_val(), sum = 0.0;
-        for (int c = 0; c < n_max; ++c)
-            if (c < n) top = fmax(top, ev[c]);
-        // two rounds over the lane's candidates: ranks (kept in cand's upper bits) and the softmax's sum, then the results
-        int rk[kMaxCand / 16];
-        double ex[kMaxCand / 16];
+        // (four at a time: their reads of LDS are then in flight together)
+        for (int c = 0; c < n_max; c += 4)
 #pragma unroll
-        for (int q = 0; q < kMaxCand / 16; ++q) {
+            for (int u = 0; u < 4; ++u)
+                if (c + u < n) top = fmax(top, ev[c + u]);
+        // two rounds over the lane's candidates: ranks (kept in cand's upper bits) and the softmax's sum, then the results
+        int rk[CPL];
+        double ex[CPL];
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
             rk[q] = 1 << 20;
             ex[q] = 0.0;
-            if (16 * q < n_max) {
-                const int ci = min(li + 16 * q, max(n - 1, 0));
+            if (lpt * q < n_max) {
+                const int ci = min(lj + lpt * q, max(n - 1, 0));
                 const double v = ev[ci];
                 const int e = ce[ci];
                 int rank = 0;
-                for (int c = 0; c < n_max; ++c) {
-                    const double ov = ev[c];
-                    const int oe = ce[c];
-                    rank += (c < n && (ov > v || (ov == v && oe < e))) ? 1 : 0;
+                for (int c = 0; c < n_max; c += 4) {
+                    double ov[4];
+                    int oe[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) ov[u] = ev[c + u], oe[u] = ce[c + u];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) rank += (c + u < n && (ov[u] > v || (ov[u] == v && oe[u] < e))) ? 1 : 0;
                 }
-                if (li + 16 * q < n && rank < k) {
+                if (lj + lpt * q < n && rank < k) {
                     rk[q] = rank;
                     ex[q] = exp(v - top);
                 }
@@ -686,10 +744,11 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
             }
         }
         sum = row_sum16(sum);
+        for (int off = 16; off < lpt; off <<= 1) sum += __shfl_xor(sum, off, 64);
 #pragma unroll
-        for (int q = 0; q < kMaxCand / 16; ++q)
-            if (16 * q < n_max && rk[q] < k) {
-                const int e = ce[li + 16 * q];
+        for (int q = 0; q < CPL; ++q)
+            if (lpt * q < n_max && rk[q] < k) {
+                const int e = ce[lj + lpt * q];
                 a.idx[(size_t)(t0 + tl) * k + rk[q]] = e;
                 a.w[(size_t)(t0 + tl) * k + rk[q]] = (float)(ex[q] / sum);
                 if (do_hist) count_choice(a, cnt, t0 + tl, e);
