@@ -26,10 +26,10 @@
 // First pass.  The reduction is split over the four wavefronts, which then work without
 // barriers: each streams its slice of the gate weights, as they lie in memory ([d][E]),
 // in chunks of KC reduction indices into LDS slots of its own, by direct global->LDS loads
-// two or three chunks ahead (through registers, one chunk ahead, when E is no multiple of 8
-// and the rows are unaligned), and takes its MFMA operands from there with the transposing
-// LDS read, those of the next chunk while this one multiplies.  The wavefronts' partial
-// sums meet in LDS.
+// two or three chunks ahead (through registers, one chunk ahead, where the rows of Wg are
+// unaligned: E is no multiple of 8, or Wg is a view that starts between 16-byte boundaries), and
+// takes its MFMA operands from there with the transposing LDS read, those of the next chunk while
+// this one multiplies.  The wavefronts' partial sums meet in LDS.
 // Second pass, in the megakernel: rows of the transposed gate weights WgT[E][d], which the
 // first front tasks of the kernel wrote to the workspace while the first passes ran, times
 // the tokens' rows, straight from L2.  Standalone (no workspace): the weights are streamed
@@ -209,23 +209,24 @@ __device__ __forceinline__ void load_lds16(const void *base, u32 voff, u32 lds_a
                  : "m0", "memory");
 }
 
-// Direct global->LDS loads of 16 bytes are only issued from 16-byte aligned tensors.  A view that starts in between (legal:
-// elements are 2 bytes) takes exact logits of all experts, whose ordinary loads accept any address; the results are the same.
-__device__ __forceinline__ bool gate_loads_direct(const KArgs &a) {
-    return ((((uintptr_t)a.x) | ((uintptr_t)a.Wg)) & 15) == 0;
-}
+// Direct global->LDS loads of 16 bytes are only issued from 16-byte aligned addresses.  A view of Wg that starts in between
+// (legal: elements are 2 bytes) goes through registers, like the rows of an E that is no multiple of 8; one of x (standalone
+// only: the experts' products ask for aligned rows) takes exact logits of all experts, whose ordinary loads accept any address.
+__device__ __forceinline__ bool gate_screens(const KArgs &a) { return (((uintptr_t)a.x) & 15) == 0; }
 
 // The gate weights into this XCD's L2, by all workgroups of the XCD together, each its share of the cache lines (16 bytes
 // of each land in a KB of LDS nobody reads): every workgroup streams all of them, in step with the others, and would
 // otherwise meet memory's latency at every chunk instead of once.  (Where workgroups run is only assumed: round-robin over
 // the XCDs.)  The caller waits for the loads before it uses that KB.
 __device__ __forceinline__ void gate_warm_l2(const KArgs &a, u32 lds_scratch, int wg, int n_wg) {
-    if (!gate_loads_direct(a)) return;
+    if (!gate_screens(a)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long lines = (long long)a.d * a.E * 2 / 128;
+    const u32 skip = (0u - (u32)(uintptr_t)a.Wg) & 15u;  // to the first aligned address
+    const char *Wg = (const char *)a.Wg + skip;
+    const long long lines = ((long long)a.d * a.E * 2 - skip) / 128;
     const int part = wg / kTileQueues, parts = (n_wg + kTileQueues - 1) / kTileQueues;
     const int l0 = (int)(lines * part / parts), l1 = (int)(lines * (part + 1) / parts);
-    for (int l = l0 + wave * 64; l < l1; l += kThreads) load_lds16(a.Wg, (u32)min(l + lane, l1 - 1) * 128u, lds_scratch);
+    for (int l = l0 + wave * 64; l < l1; l += kThreads) load_lds16(Wg, (u32)min(l + lane, l1 - 1) * 128u, lds_scratch);
 }
 
 // Tokens [t0, t0 + TOK): idx and w written, choices counted in cnt if do_hist (LDS, zeroed).  Returns false, with nothing
@@ -260,7 +261,7 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
     const char *x = (const char *)a.x + (size_t)t0 * d * 2;
     const int nC = d / KC;
     const int c_begin = nC * wave / 4, c_end = nC * (wave + 1) / 4;
-    const bool aligned = (E & 7) == 0;
+    const bool aligned = (E & 7) == 0 && (((uintptr_t)a.Wg) & 15) == 0;  // every row of Wg
     MOE_TT_BEGIN();
     // piece p of row r of x (and of T) sits at p ^ swz(r); piece p of weight row r at (p + rot(r)) mod ppr: the 16
     // rows of an MFMA operand, and the 4 rows of a transposing read, then come from different banks (narrow rows: as is)

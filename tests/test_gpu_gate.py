@@ -71,3 +71,55 @@ def test_gate_of_views_off_16_bytes(T, d, E, k, which):
         assert torch.equal(idx, out[0][0])
         # fp64 sums in another order, rounded once: one unit in the last place of fp32 and a little
         np.testing.assert_allclose(w.numpy(), out[0][1].numpy(), rtol=1.5e-7, atol=0)
+
+
+@pytest.mark.parametrize("offset", [1, 4, 7])
+@pytest.mark.parametrize("T,d,E,k", [(9, 1152, 8, 2), (1030, 64, 64, 8), (2050, 192, 48, 6), (40, 1024, 256, 8), (130, 64, 72, 4)],
+                         ids=lambda v: str(v))
+def test_unaligned_view_of_the_gate_weights(T, d, E, k, offset):
+    """Wg as a view that starts `offset` elements past a 16-byte boundary, inside a tensor whose neighbours are no numbers:
+    the oracle's choices, standalone and in the layer, in every code variant that takes whole pieces otherwise."""
+    from paper_2605_00686_amd import binding as B
+    print(f"case gate weights off T={T} d={d} E={E} k={k} offset={offset}", flush=True)
+    inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=64, R=1, dtype="bf16", seed=T + E + offset, bias_std=0.3))
+    p = B.problem(T, d, E, k, 64, 1, "bf16")
+    dev = {n: inp[n].cuda() for n in ("x", "gate_bias", "W1", "W3", "W2")}
+    room = torch.full((d * E + 16,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    view = room[offset:offset + d * E].reshape(d, E)
+    view.copy_(inp["Wg"])
+    ridx, rw, _ = parity.oracle_routing(inp)
+    idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.full((T, k), float("nan"), dtype=torch.float32, device="cuda")
+    B.moe_route(p, dev["x"], view, dev["gate_bias"], idx, w)
+    buf = B.Buffers(p)
+    B.forward(p, buf, dev["x"], view, dev["gate_bias"], dev["W1"], dev["W3"], dev["W2"])
+    torch.cuda.synchronize()
+    assert int(buf.stats[7].item()) == 0
+    for i2, w2 in ((idx, w), (buf.topk_idx, buf.topk_w)):
+        assert np.array_equal(i2.cpu().numpy(), ridx)
+        np.testing.assert_allclose(w2.cpu().numpy(), rw, rtol=1.5e-7, atol=0)  # (as above)
+
+
+def test_unaligned_view_of_the_gate_weights_keeps_the_screen():
+    """The gate phase of a decode batch takes at most twice as long on such a view as on aligned weights (exact logits of
+    all experts take more than three times as long)."""
+    from paper_2605_00686_amd import binding as B
+    print("case gate weights off, time", flush=True)
+    inp = W.make_inputs(dict(T=8, d=2048, E=128, k=8, f=64, R=1, dtype="bf16", seed=3, bias_std=0.3, tile_m=32))
+    p = B.problem(8, 2048, 128, 8, 64, 1, "bf16", tile_m=32)
+    buf = B.Buffers(p)
+    dev = {n: inp[n].cuda() for n in ("x", "Wg", "gate_bias", "W1", "W3", "W2")}
+    room = torch.zeros(dev["Wg"].numel() + 16, dtype=torch.bfloat16, device="cuda")
+    view = room[1:1 + dev["Wg"].numel()].reshape(dev["Wg"].shape)
+    view.copy_(dev["Wg"])
+    gate_us = []
+    for wg in (dev["Wg"], view):
+        seen = []
+        for _ in range(12):
+            p.epoch += 1
+            B.forward(p, buf, dev["x"], wg, dev["gate_bias"], dev["W1"], dev["W3"], dev["W2"])
+            torch.cuda.synchronize()
+            seen.append(int(buf.stats[8].item()) / 1000)
+        gate_us.append(sorted(seen)[len(seen) // 2])
+    print(f"gate phase {gate_us[0]:.1f} us, on a view off 16 bytes {gate_us[1]:.1f} us", flush=True)
+    assert gate_us[1] <= 2 * gate_us[0]
