@@ -497,7 +497,9 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->nPB = (p->T + kPermBlock - 1) / kPermBlock;
     pl->gate_tok = p->dtype == MOE_DT_BF16 ? gate_tokens(p->T) : kRouteTokens;
     pl->nRT = (p->T + pl->gate_tok - 1) / pl->gate_tok;
-    // few tokens: no more tasks than a chip full of workgroups has to do in one go, down to one token for all four wavefronts
+    // combine tasks of the megakernel: a workgroup has few of them, down to one token for all four wavefronts.  Whole layer, 1 / 2
+    // / 4 tokens per task, us: 513 tokens on 16 experts of 1024 x 256 99 / 94 / 91, 900 on 64 of 2048 x 256 224 / 212 / 214.
+    // (The standalone combine has a rule of its own: standalone_combine_tokens.)
     pl->comb_tokens = p->T >= 16384 ? 16 : p->T >= 8192 ? 8 : p->T > 512 ? 4 : p->T > 256 ? 2 : 1;
     // the ready-queue scheduler enqueues combine tasks per destination: none may span two
     if (p->scheduler == MOE_SCHED_READY_QUEUE)
@@ -628,6 +630,16 @@ static void fill_args(const Plan &pl, void *workspace, KArgs *a) {
         a->h = ws + pl.o_h;
         a->zero_bytes = pl.zero_bytes;
     }
+}
+
+// Tokens per task of the standalone combine.  A CU holds three of its workgroups: up to 768 tasks run at once, and as long as
+// that many are enough, fewer tokens per task, whose rows more wavefronts share, are faster; from there on a wavefront per
+// token.  A row must have enough 16-byte pieces for the lanes that share it.  Rows not in the L2, 1 / 2 / 4 tokens per task, us:
+// 513 tokens x 8 rows of 2048 5.4 / 5.9 / 8.2; 768 6.6 / 7.2 / 8.6; 900 8.5 / 7.7 / 9.2; 1536 11.7 / 10.6 / 12.8; 1800 14.2 / 13.8 /
+// 14.0; 2048 15.2 / 14.6 / 13.8; 1024 x 2 of 4096 7.0 / 6.2 / 6.7; 1024 x 6 of 1024 6.3 / 4.8 / 5.3; 513 x 4 of 512 3.2 / 3.0 / 2.9.
+static int standalone_combine_tokens(int T, size_t row_bytes) {
+    const size_t pieces = row_bytes / 16;
+    return T >= 16384 ? 16 : T >= 8192 ? 8 : T > 1536 || pieces < 128 ? 4 : T > 768 || pieces < 256 ? 2 : 1;
 }
 
 static size_t plan_smem(const Plan &pl) { return plan_smem_bytes(pl.p.E, pl.p.R, pl.nPB); }
@@ -1026,11 +1038,14 @@ int moe_combine(const moe_problem_t *p, const void *staging, const uint32_t *fla
     a.status_dev = status_dev;
     hipStream_t st = (hipStream_t)stream;
     // rows that do not fit the 256 MB last-level cache are streamed past it
-    const bool past_cache = (size_t)pl.N * p->d * elem_size(p->dtype) > ((size_t)192 << 20);
-    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(pl.nCT), dim3(kThreads), 0, st, a); };
+    const size_t row_bytes = (size_t)p->d * elem_size(p->dtype);
+    const bool past_cache = (size_t)pl.N * row_bytes > ((size_t)192 << 20);
+    a.comb_tokens = standalone_combine_tokens(p->T, row_bytes);
+    a.nCT = (p->T + a.comb_tokens - 1) / a.comb_tokens;
+    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(a.nCT), dim3(kThreads), 0, st, a); };
     auto pick = [&](auto et) {
         using ET = decltype(et);
-        if (pl.comb_tokens < 4)
+        if (a.comb_tokens < 4)
             past_cache ? launch(k_combine<ET, true, true>) : launch(k_combine<ET, false, true>);
         else
             past_cache ? launch(k_combine<ET, true, false>) : launch(k_combine<ET, false, false>);

@@ -10,7 +10,9 @@ pytestmark = pytest.mark.gpu
 
 # (T, d, k, dtype)
 CASES = [(1, 64, 1, "bf16"), (256, 192, 8, "bf16"), (257, 1088, 2, "bf16"), (512, 64, 4, "bf16"), (513, 320, 9, "bf16"),
-         (515, 576, 17, "bf16"), (130, 7168, 8, "bf16"), (300, 16, 3, "f32"), (514, 1040, 1, "f32"), (3, 4112, 12, "f32")]
+         (515, 576, 17, "bf16"), (130, 7168, 8, "bf16"), (300, 16, 3, "f32"), (514, 1040, 1, "f32"), (3, 4112, 12, "f32"),
+         (768, 2048, 2, "bf16"), (769, 2048, 3, "bf16"), (767, 1984, 5, "bf16"), (1536, 1024, 1, "bf16"), (1537, 2048, 2, "bf16"),
+         (1535, 960, 4, "bf16"), (770, 512, 6, "f32"), (9, 1024, 2, "f32")]
 
 
 @pytest.mark.parametrize("T,d,k,dtype", CASES, ids=["T%d_d%d_k%d_%s" % c for c in CASES])
