@@ -14,7 +14,11 @@ pytestmark = pytest.mark.gpu
 CASES = [(5, 64, 1, 1), (37, 128, 7, 3), (1030, 192, 16, 2), (16, 256, 17, 2), (2050, 128, 32, 4), (65, 320, 33, 6),
          (1025, 128, 64, 8), (40, 2880, 65, 4), (4100, 64, 128, 8), (33, 192, 129, 8), (130, 128, 192, 8), (70, 256, 200, 8),
          (2049, 64, 255, 5), (64, 1024, 256, 8),
-         (2050, 1088, 16, 2), (2049, 64, 17, 3), (40, 1088, 16, 2), (40, 1024, 15, 2), (9, 1088, 3, 1)]
+         (2050, 1088, 16, 2), (2049, 64, 17, 3), (40, 1088, 16, 2), (40, 1024, 15, 2), (9, 1088, 3, 1),
+         # both sides of the standalone gate's rule for short reductions, at 4, 8 and 16 tokens per task
+         (130, 384, 24, 4), (65, 448, 33, 6), (70, 256, 48, 4), (130, 192, 64, 8), (9, 64, 96, 8), (1030, 576, 20, 2), (1025, 640, 32, 4),
+         (1025, 256, 64, 8), (1030, 128, 200, 4), (2049, 768, 17, 3), (2050, 832, 32, 4), (2049, 448, 47, 4), (2050, 512, 48, 6),
+         (2049, 256, 64, 8), (4100, 256, 128, 8), (2049, 256, 255, 5)]
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])
@@ -74,7 +78,7 @@ def test_gate_of_views_off_16_bytes(T, d, E, k, which):
 
 
 @pytest.mark.parametrize("offset", [1, 4, 7])
-@pytest.mark.parametrize("T,d,E,k", [(9, 1152, 8, 2), (1030, 64, 64, 8), (2050, 192, 48, 6), (40, 1024, 256, 8), (130, 64, 72, 4)],
+@pytest.mark.parametrize("T,d,E,k", [(9, 1152, 8, 2), (1030, 256, 64, 8), (2050, 576, 48, 6), (40, 1024, 256, 8), (130, 128, 72, 4)],
                          ids=lambda v: str(v))
 def test_unaligned_view_of_the_gate_weights(T, d, E, k, offset):
     """Wg as a view that starts `offset` elements past a 16-byte boundary, inside a tensor whose neighbours are no numbers:

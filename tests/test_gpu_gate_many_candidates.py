@@ -34,14 +34,14 @@ def make(T, d, E, k, kind):
     return inp
 
 
-# (T, d, E, k, kind)
+# (T, d, E, k, kind); d past what the standalone gate takes on exact logits of all experts
 CASES = [(9, 128, 128, 8, "zero_rows"), (9, 192, 256, 8, "all_zero"), (130, 1024, 80, 6, "zero_rows"),
-         (130, 64, 200, 8, "all_zero"), (8, 2048, 128, 8, "near"), (37, 64, 255, 5, "near"), (12, 128, 33, 6, "zero_rows"),
-         (1030, 64, 128, 8, "all_zero"), (1030, 128, 129, 4, "zero_rows"), (1030, 256, 256, 32, "near"), (1030, 64, 200, 32, ""),
-         (2050, 64, 40, 32, ""), (2050, 64, 65, 32, ""), (2050, 128, 256, 32, ""), (2050, 64, 64, 8, "zero_rows"),
-         (2050, 64, 80, 8, "zero_rows"), (2050, 128, 17, 3, "all_zero"), (2050, 64, 48, 4, "near"),
-         (9, 64, 64, 8, "tied_bias"), (130, 192, 129, 8, "tied_bias"), (1030, 7168, 24, 4, "tied_bias"), (2050, 64, 200, 8, "tied_bias"),
-         (9, 1088, 48, 4, "tiny"), (2050, 64, 48, 4, "tiny"), (2050, 64, 256, 8, "tiny")]
+         (130, 128, 200, 8, "all_zero"), (8, 2048, 128, 8, "near"), (37, 128, 255, 5, "near"), (12, 320, 33, 6, "zero_rows"),
+         (1030, 192, 128, 8, "all_zero"), (1030, 192, 129, 4, "zero_rows"), (1030, 256, 256, 32, "near"), (1030, 192, 200, 32, ""),
+         (2050, 576, 40, 32, ""), (2050, 256, 65, 32, ""), (2050, 256, 256, 32, ""), (2050, 320, 64, 8, "zero_rows"),
+         (2050, 256, 80, 8, "zero_rows"), (2050, 832, 17, 3, "all_zero"), (2050, 576, 48, 4, "near"),
+         (9, 192, 64, 8, "tied_bias"), (130, 192, 129, 8, "tied_bias"), (1030, 7168, 24, 4, "tied_bias"), (2050, 256, 200, 8, "tied_bias"),
+         (9, 1088, 48, 4, "tiny"), (2050, 576, 48, 4, "tiny"), (2050, 256, 256, 8, "tiny")]
 
 
 @pytest.mark.parametrize("T,d,E,k,kind", CASES, ids=["T%d_d%d_E%d_k%d_%s" % c for c in CASES])

@@ -103,8 +103,8 @@ def test_exact_gate_of_more_than_64_experts(E, k, kind):
 # (T, d, E, k): every code variant of the screen, tasks of 4, 8 and 16 tokens, rows of Wg off 16 bytes; experts few enough
 # that all of a token's could pass as candidates, and more
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("T,d,E,k", [(37, 1152, 8, 2), (9, 1088, 16, 4), (37, 192, 48, 8), (2050, 64, 48, 6), (70, 64, 64, 8),
-                                     (1030, 64, 64, 3), (37, 128, 65, 8), (37, 128, 128, 8), (33, 64, 192, 8), (40, 64, 256, 5)],
+@pytest.mark.parametrize("T,d,E,k", [(37, 1152, 8, 2), (9, 1088, 16, 4), (37, 320, 48, 8), (2050, 576, 48, 6), (70, 192, 64, 8),
+                                     (1030, 256, 64, 3), (37, 128, 65, 8), (37, 128, 128, 8), (33, 128, 192, 8), (40, 128, 256, 5)],
                          ids=lambda v: str(v))
 def test_screened_gate(T, d, E, k, kind):
     """bf16 problems: bounds that are not finite select no candidates."""
