@@ -220,7 +220,10 @@ __device__ __forceinline__ void load_lds16(const void *base, u32 voff, u32 lds_a
 // Direct global->LDS loads of 16 bytes are only issued from 16-byte aligned addresses.  A view of Wg that starts in between
 // (legal: elements are 2 bytes) goes through registers, like the rows of an E that is no multiple of 8; one of x (standalone
 // only: the experts' products ask for aligned rows) takes exact logits of all experts, whose ordinary loads accept any address.
-__device__ __forceinline__ bool gate_screens(const KArgs &a) { return (((uintptr_t)a.x) & 15) == 0; }
+// So do gate weights of 4 GB and more: the screen addresses them with 32 bits (and a piece past their end).
+__device__ __forceinline__ bool gate_screens(const KArgs &a) {
+    return (((uintptr_t)a.x) & 15) == 0 && (long long)a.d * a.E * 2 <= 0xffffff00ll;
+}
 
 // The gate weights into this XCD's L2, by all workgroups of the XCD together, each its share of the cache lines (16 bytes
 // of each land in a KB of LDS nobody reads): every workgroup streams all of them, in step with the others, and would

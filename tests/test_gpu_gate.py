@@ -127,3 +127,34 @@ def test_unaligned_view_of_the_gate_weights_keeps_the_screen():
         gate_us.append(sorted(seen)[len(seen) // 2])
     print(f"gate phase {gate_us[0]:.1f} us, on a view off 16 bytes {gate_us[1]:.1f} us", flush=True)
     assert gate_us[1] <= 2 * gate_us[0]
+
+
+def test_gate_weights_past_32_bits():
+    """Gate weights of more than 4 GB whose rows are unaligned: x has a few entries per token, at both ends and on either side
+    of the 2^32nd byte, so the logits are known from those rows of Wg alone."""
+    from paper_2605_00686_amd import binding as B
+    E, k, T = 255, 4, 3
+    d = 8421568  # 64 * 131587; d * E * 2 bytes is just past 2^32
+    assert d % 64 == 0 and d * E * 2 > 2 ** 32
+    print(f"case gate weights past 32 bits d={d} E={E}", flush=True)
+    gen = torch.Generator().manual_seed(1)
+    at = [0, 77, d // 2 + 1, 2 ** 32 // (2 * E) - 3, 2 ** 32 // (2 * E) + 5, d - 1]
+    rows = torch.randn(len(at), E, generator=gen).bfloat16()
+    vals = torch.randn(T, len(at), generator=gen).bfloat16()
+    x = torch.zeros(T, d, dtype=torch.bfloat16, device="cuda")
+    Wg = torch.zeros(d, E, dtype=torch.bfloat16, device="cuda")
+    for i, r in enumerate(at):
+        x[:, r] = vals[:, i].cuda()
+        Wg[r] = rows[i].cuda()
+    logits = (vals.double() @ rows.double()).numpy()
+    order = np.argsort(-logits, axis=1, kind="stable")[:, :k]
+    chosen = np.take_along_axis(logits, order, axis=1)
+    soft = np.exp(chosen - chosen[:, :1])
+    soft /= soft.sum(axis=1, keepdims=True)
+    p = B.problem(T, d, E, k, 64, 1, "bf16")
+    idx = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.full((T, k), float("nan"), dtype=torch.float32, device="cuda")
+    B.moe_route(p, x, Wg, None, idx, w)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), order)
+    np.testing.assert_allclose(w.cpu().numpy(), soft, rtol=1.5e-7, atol=0)
