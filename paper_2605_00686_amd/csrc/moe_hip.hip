@@ -316,12 +316,12 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
 
 // The whole layer in one persistent kernel.  Every workgroup walks through three
 // stages, drawing work from counters in the control block:
-//   1. front tasks, one counter, in this order: [gate tasks | plan | permutation blocks];
+//   1. front tasks, one counter, in this order: [gate-weight transposition | gate tasks | plan | permutation blocks];
 //   2. GEMM tiles, four kinds in turn (GEMM1 then GEMM2, big then small row blocks), each kind
 //      from one list per XCD (see TileQueue): its own XCD's list first, then the others;
 //   3. combine tasks, one counter.
 // No wait can deadlock, whatever the grid size: a task only waits for tasks of an
-// earlier kind (permutation <- plan <- gate, GEMM1 <- permutation, GEMM2 <- GEMM1,
+// earlier kind (permutation <- plan <- gate <- transposition, GEMM1 <- permutation, GEMM2 <- GEMM1,
 // combine <- GEMM2), a workgroup only moves on to a later kind when every entry of the
 // kinds before has been drawn, and whoever drew an entry is running it.  So the not yet finished entry of the earliest kind is always either
 // running with everything it needs, or about to be drawn by a workgroup that is not
@@ -578,8 +578,8 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->o_rbs_base = take((size_t)(p->E + 1) * 4);
     pl->o_rbs_expert = take((size_t)p->E * 4);
     pl->o_h = take((size_t)pl->NP * p->f * elem_size(p->dtype));
-    // partial logits of a gate split over its reduction (few tokens only): at most kGateSplitTasks tasks
-    pl->o_gate_partial = take((size_t)kGateSplitTasks * kRouteTokens * p->E * 8);
+    // partial logits of a gate split over its reduction (fp32 problems of few tokens): at most kGateSplitTasks tasks
+    pl->o_gate_partial = take(p->dtype == MOE_DT_F32 ? (size_t)kGateSplitTasks * kRouteTokens * p->E * 8 : 0);
     // transposed gate weights (bf16 problems; unused when the routing is an input)
     pl->o_wgt = take(p->dtype == MOE_DT_BF16 ? (size_t)p->E * p->d * 2 : 0);
     pl->total = o;
@@ -698,15 +698,18 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
     const size_t rsm = gate_task_smem_bytes(pl.p.E, pl.p.d, elem_size(pl.p.dtype));
     if (a_in.Wg && rsm > smem) smem = rsm;
     if (plan_smem(pl) > smem) smem = plan_smem(pl);
-    if (plan_all_fits(pl.p.E, pl.p.R, pl.nPB) && plan_all_smem_bytes(pl.p.E, pl.p.R, pl.nPB) > smem)
-        smem = plan_all_smem_bytes(pl.p.E, pl.p.R, pl.nPB);
-    // decode tables live behind everything else, for the life of the workgroup
+    // The decode tables live behind everything else, for the life of the workgroup, where they are small (6 KB: up to 255
+    // experts and not very many row blocks); only with them there every workgroup can derive the plan by itself.
     const size_t tab_bytes = (size_t)(4 * (pl.p.E + 1) + pl.tl.maxRB + pl.p.E) * 4;
+    auto tables_fit = [&](size_t before) { return tab_bytes <= 6 * 1024 && before + tab_bytes + sizeof(StageLds) + 16 <= kLdsBudget; };
+    size_t with_plan = plan_all_smem_bytes(pl.p.E, pl.p.R, pl.nPB);
+    if (with_plan < smem) with_plan = smem;
+    a.plan_all = plan_all_fits(pl.p.E, pl.p.R, pl.nPB) && tables_fit(with_plan) ? 1 : 0;
+    if (a.plan_all) smem = with_plan;
     a.tab_lds_off = 0;
-    if (tab_bytes <= 6 * 1024 && smem + tab_bytes + sizeof(StageLds) + 16 <= kLdsBudget) {  // small enough that two workgroups of the 128-row tile still share a CU
+    if (tables_fit(smem)) {
         a.tab_lds_off = (int)align_up(smem, 16);
         smem = a.tab_lds_off + tab_bytes;
-        a.plan_all = plan_all_fits(pl.p.E, pl.p.R, pl.nPB) ? 1 : 0;
     }
     a.sched_lds_off = (int)align_up(smem, 16);
     smem = a.sched_lds_off + sizeof(StageLds);

@@ -1,6 +1,6 @@
 """GPU test of the plan inside the megakernel on both sides of the rule that chooses between its two forms (every workgroup
-derives it in LDS; one workgroup writes it to memory): destinations x experts and token blocks x experts at and just past
-the limits, destinations that are and are not whole token blocks, against the oracle."""
+derives it in LDS; one workgroup writes it to memory): destinations x experts, token blocks x experts and the decode tables at
+and just past the limits, destinations that are and are not whole token blocks, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -11,9 +11,24 @@ from tests import parity
 
 pytestmark = pytest.mark.gpu
 
-# (T, E, R, k, tile_m, capacity): the tables' limits are 8 * E * R <= 32 KB and 4 * E * ceil(T / 64) <= 64 KB
+# (T, E, R, k, tile_m, capacity)
 CASES = [(192, 64, 64, 2, 32, 0), (195, 64, 65, 2, 32, 0), (4096, 256, 4, 2, 128, 0), (4100, 256, 4, 2, 128, 0),
-         (640, 3, 10, 2, 64, 0), (640, 3, 10, 2, 64, 512), (77, 5, 7, 3, 128, 77)]
+         (640, 3, 10, 2, 64, 0), (640, 3, 10, 2, 64, 512), (77, 5, 7, 3, 128, 77),
+         (8192, 128, 4, 2, 128, 0), (8196, 128, 4, 2, 128, 0), (47, 255, 1, 2, 32, 0), (48, 255, 1, 2, 32, 0)]
+# which of them derive the plan in every workgroup
+IN_EVERY_WORKGROUP = [True, False, False, False, True, True, True, True, False, True, False]
+
+
+def in_every_workgroup(T, E, R, k, tile_m):
+    """The rule of the launch: at most 32 KB of segment tables (8 * E * R), 64 KB of histograms (4 * E * ceil(T / 64)) and 6 KB of
+    decode tables (4 * (6 * E + 4 + row blocks); row blocks of 32 rows with fewer than 96 rows per expert and a 32-row publish
+    tile, else of 256)."""
+    bm = 32 if T * k // E < 96 and tile_m == 32 else 256
+    return 8 * E * R <= 32768 and 4 * E * -(-T // 64) <= 65536 and 4 * (6 * E + 4 + T * k // bm) <= 6144
+
+
+def test_cases_lie_on_both_sides():
+    assert [in_every_workgroup(*c[:5]) for c in CASES] == IN_EVERY_WORKGROUP
 
 
 @pytest.mark.parametrize("T,E,R,k,tile_m,capacity", CASES, ids=["T%d_E%d_R%d_k%d_m%d_c%d" % c for c in CASES])
