@@ -830,7 +830,7 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
 // of trips to memory (flag numbers, flags, rows), so what counts is that all four wavefronts load, and that a workgroup
 // has few tasks.  Inside the megakernel (WAIT), where a CU holds one workgroup, a lane keeps 16 loads in flight; alone, where
 // it holds several, 8.  SHARE = false: a wavefront per token whatever the task has (the standalone launch of four tokens or more
-// per task: with shared rows as a run-time choice it took 28.2 instead of 25.6 us on 4096 x 8 rows of 2048, 93 instead of 82 us
+// per task: with shared rows as a run-time choice it took 28.7 instead of 25.9 us on 4096 x 8 rows of 2048, 91 instead of 80 us
 // on 16384 x 2 rows of 4096).
 template <typename ET, bool WAIT, bool STREAM = false, bool SHARE = true>
 __device__ __forceinline__ void combine_task(const KArgs &a, int task) {

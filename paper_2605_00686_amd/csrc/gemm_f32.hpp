@@ -70,7 +70,9 @@ template <bool GATED, int ROWS, int CB, class RowPtr, class Hook>
 __device__ __forceinline__ void gemm_rows_f32(RowPtr rowptr, const float *B0, const float *B1, int ldb, int ncols, int K,
                                               char *smem, Hook while_loading) {
     using C = TileF32;
-    constexpr int DEPTH = ROWS <= 2 ? 8 : 4;  // pieces in flight per wavefront: what the registers beside the sums hold
+    // pieces in flight per wavefront: what the registers beside the sums hold (in the forms of 3 and 4 row blocks not all of it:
+    // the compiler reports 36 spilled vector registers for the fp32 megakernel, and around the exchange sums go to scratch)
+    constexpr int DEPTH = ROWS <= 2 ? 8 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int col = min(l32 * CB, ncols - CB);  // (columns past the tile's repeat its last ones and are not stored)

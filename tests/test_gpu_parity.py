@@ -170,15 +170,15 @@ def test_megakernel_gate_many_experts_and_ties(E):
     dict(T=512, d=256, E=2, k=2, f=128, R=1, dtype="bf16", seed=33, tile_m=32),
     # more destinations than a wavefront has lanes, tiny segments
     dict(T=256, d=128, E=16, k=2, f=64, R=128, dtype="bf16", seed=34, tile_m=32),
-    # three blocks of 16 tokens and a long reduction: the gate is split ten ways over the reduction
+    # few tokens and a long reduction: gate tasks of 4 tokens
     dict(T=48, d=4096, E=24, k=3, f=128, R=3, dtype="bf16", seed=35, tile_m=32, bias_std=0.5),
-    # the same in fp32 (two slices)
+    # few tokens in fp32: the gate is split over the reduction, eight slices
     dict(T=40, d=1024, E=12, k=2, f=64, R=2, dtype="f32", seed=36),
     # one expert, every token its own destination
     dict(T=16, d=64, E=1, k=1, f=64, R=16, dtype="bf16", seed=37, tile_m=32),
-    # a decode-sized batch with many experts: the split gate takes precedence over the bf16 screen
+    # a decode-sized batch with many experts: gate tasks of 4 tokens
     dict(T=128, d=2048, E=128, k=8, f=64, R=8, dtype="bf16", seed=40, tile_m=32, bias_std=0.5),
-    # 128 blocks of 16 tokens, 64 experts: half of the workgroups get a gate task (the bf16 screen)
+    # 256 gate tasks of 8 tokens, one per workgroup
     dict(T=2048, d=1024, E=64, k=2, f=64, R=8, dtype="bf16", seed=41),
     # fp32 rows of h of 64 bytes: two row blocks share a cache line wherever an expert starts at an odd row
     dict(T=40, d=1024, E=200, k=2, f=16, R=1, dtype="f32", seed=43055, bias_std=0.5, tile_m=64),
@@ -191,8 +191,12 @@ def test_megakernel_gate_many_experts_and_ties(E):
     dict(T=1, d=128, E=4, k=2, f=64, R=1, dtype="bf16", seed=38, tile_m=32),
     # a single token, fp32
     dict(T=1, d=64, E=2, k=2, f=64, R=1, dtype="f32", seed=39),
+    # the most slices a split gate can have (16), few experts and many
+    dict(T=48, d=4096, E=24, k=3, f=64, R=3, dtype="f32", seed=45, bias_std=0.5),
+    dict(T=128, d=2048, E=128, k=8, f=32, R=8, dtype="f32", seed=46, bias_std=0.5),
 ], ids=["k_eq_E", "odd_f32", "one_dest", "many_dest", "split_gate", "split_gate_f32", "one_expert",
-        "split_gate_many_experts", "gate_128_blocks", "h_rows_share_lines", "k_32_of_40", "k_32_of_256", "max_dest", "one_token", "one_token_f32"])
+        "split_gate_many_experts", "gate_128_blocks", "h_rows_share_lines", "k_32_of_40", "k_32_of_256", "max_dest", "one_token", "one_token_f32",
+        "split_gate_16_f32", "split_gate_16_many_experts_f32"])
 @pytest.mark.parametrize("signal_mode", [0, 1])
 def test_megakernel_odd_shapes(cfg, signal_mode):
     B = _binding()
