@@ -219,20 +219,12 @@ __device__ __forceinline__ void load_lds16(const void *base, u32 voff, u32 lds_a
                  : "m0", "memory");
 }
 
-// Direct global->LDS loads of 16 bytes are only issued from 16-byte aligned addresses.  A view of Wg that starts in between
-// (legal: elements are 2 bytes) goes through registers, like the rows of an E that is no multiple of 8; one of x (standalone
-// only: the experts' products ask for aligned rows) takes exact logits of all experts, whose ordinary loads accept any address.
-// So do gate weights of 4 GB and more: the screen addresses them with 32 bits (and a piece past their end).
-__device__ __forceinline__ bool gate_screens(const KArgs &a) {
-    return (((uintptr_t)a.x) & 15) == 0 && (long long)a.d * a.E * 2 <= 0xffffff00ll;
-}
-
 // The gate weights into this XCD's L2, by all workgroups of the XCD together, each its share of the cache lines (16 bytes
 // of each land in a KB of LDS nobody reads): every workgroup streams all of them, in step with the others, and would
 // otherwise meet memory's latency at every chunk instead of once.  (Where workgroups run is only assumed: round-robin over
 // the XCDs.)  The caller waits for the loads before it uses that KB.
 __device__ __forceinline__ void gate_warm_l2(const KArgs &a, u32 lds_scratch, int wg, int n_wg) {
-    if (!gate_screens(a)) return;
+    if (!a.gate_screens) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const u32 skip = (0u - (u32)(uintptr_t)a.Wg) & 15u;  // to the first aligned address
     const char *Wg = (const char *)a.Wg + skip;
@@ -274,7 +266,7 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
     const char *x = (const char *)a.x + (size_t)t0 * d * 2;
     const int nC = d / KC;
     const int c_begin = nC * wave / 4, c_end = nC * (wave + 1) / 4;
-    const bool aligned = (E & 7) == 0 && (((uintptr_t)a.Wg) & 15) == 0;  // every row of Wg
+    const bool aligned = a.gate_rows_aligned != 0;
     MOE_TT_BEGIN();
     // piece p of row r of x (and of T) sits at p ^ swz(r); piece p of weight row r at (p + rot(r)) mod ppr: the 16
     // rows of an MFMA operand, and the 4 rows of a transposing read, then come from different banks (narrow rows: as is)

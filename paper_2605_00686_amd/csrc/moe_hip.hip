@@ -642,6 +642,18 @@ static int standalone_combine_tokens(int T, size_t row_bytes) {
     return T >= 16384 ? 16 : T >= 8192 ? 8 : T > 1536 || pieces < 128 ? 4 : T > 768 || pieces < 256 ? 2 : 1;
 }
 
+// What the gate's screen may assume of x and Wg, decided here because a task would wait for it.  Direct global->LDS loads of
+// 16 bytes are only issued from 16-byte aligned addresses.  Unaligned rows of Wg (E is no multiple of 8, or a view that starts
+// between 16-byte boundaries, which is legal: elements are 2 bytes) go through registers; an unaligned x (standalone only: the
+// experts' products ask for aligned rows) takes exact logits of all experts, whose ordinary loads accept any address.  So do
+// gate weights of 4 GB and more and rows of x longer than 2^26: the screen addresses the weights (and a piece past their end)
+// with 32 bits, the 16 rows of a task with 31.
+static void set_gate(KArgs *a, const void *x, const void *Wg, const float *bias) {
+    a->x = x; a->Wg = Wg; a->bias = bias;
+    a->gate_screens = ((uintptr_t)x & 15) == 0 && a->d <= 1 << 26 && (long long)a->d * a->E * 2 <= 0xffffff00ll;
+    a->gate_rows_aligned = (a->E & 7) == 0 && ((uintptr_t)Wg & 15) == 0;
+}
+
 static size_t plan_smem(const Plan &pl) { return plan_smem_bytes(pl.p.E, pl.p.R, pl.nPB); }
 
 static int check_ws(const void *ws) {
@@ -821,7 +833,8 @@ int moe_route(const moe_problem_t *p, const void *x, const void *Wg, const float
     if (!x || !Wg || !topk_idx || !topk_w) return MOE_ERR_INVALID_ARG;
     KArgs a;
     fill_args(pl, nullptr, &a);
-    a.x = x; a.Wg = Wg; a.bias = gate_bias; a.idx = topk_idx; a.w = topk_w;
+    set_gate(&a, x, Wg, gate_bias);
+    a.idx = topk_idx; a.w = topk_w;
     const size_t smem = gate_task_smem_bytes(p->E, p->d, elem_size(p->dtype));
     hipStream_t st = (hipStream_t)stream;
     auto launch = [&](auto kern) {
@@ -958,7 +971,8 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     if ((rc = check_ws(workspace))) return rc;
     KArgs a;
     fill_args(pl, workspace, &a);
-    a.x = x; a.Wg = Wg; a.bias = gate_bias; a.W1 = W1; a.W3 = W3; a.W2 = W2;
+    set_gate(&a, x, Wg, gate_bias);
+    a.W1 = W1; a.W3 = W3; a.W2 = W2;
     a.idx = topk_idx; a.w = topk_w; a.counts = counts; a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
     a.slot_flag = slot_flag; a.staging = staging; a.flags = flags; a.out = out;
     a.stats = (u64 *)stats;

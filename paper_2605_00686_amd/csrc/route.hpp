@@ -430,7 +430,7 @@ __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int t
     MOE_TT_BEGIN();
     if (compute) {
         if constexpr (V > 0) {
-            if (!gate_screens(a) || !route_screened<V, WGT>(a, t0, TOK, smem, do_hist, wgt_ready)) {
+            if (!a.gate_screens || !route_screened<V, WGT>(a, t0, TOK, smem, do_hist, wgt_ready)) {
                 route_fallback(args, lds_offset(smem), t0, TOK, do_hist ? 1 : 0);
                 __syncthreads();
             }
