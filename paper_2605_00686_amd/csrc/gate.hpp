@@ -52,17 +52,19 @@ constexpr int kGateSlots = 16;  // standalone second pass: candidates per group 
 __host__ __device__ inline int gate_variant(int E, int d) {
     return E <= 32 ? (d % 128 == 0 ? 1 : 6) : E <= 64 ? 2 : E <= 128 ? 3 : E <= 192 ? 4 : 5;
 }
-// Standalone gate: exact logits of all experts at once where the experts are few or the reduction short.  The screen pays a
-// fixed 10 to 15 us for its two sweeps, threshold and selection, the more the more tokens a task has (see gate_tokens); the exact
-// logits' cost grows with d and with the blocks of 16 experts.  moe_route, exact / screened, us:
-//   E = 8    4096 tokens of d 4096 37 / 43, of d 1024 15 / 20; 1024 of d 1024 14.6 / 16.7, but of d 4096 36 / 32
-//   E = 24   4096 of d 768 17.8 / 20.1, of d 1024 21.0 / 20.5; 2048 of d 512 15.1 / 15.7; 128 of d 384 12.8 / 14.1, of d 512 15.2 / 14.1
-//   E = 48   4096 of d 256 15.1 / 17.6, of d 512 19.8 / 20.0; 2048 of d 256 15.0 / 16.3; 128 of d 256 15.1 / 14.4
-//   E = 64   4096 of d 256 17.4 / 17.9, of d 384 19.9 / 19.6; 2048 of d 192 15.4 / 16.0; 128 of d 128 14.0 / 14.6, of d 192 15.5 / 14.7
-//   E = 128  4096 of d 192 18.6 / 19.7, of d 256 21.2 / 20.4; 2048 of d 128 16.7 / 16.7; 128 of d 64 14.1 / 15.2, of d 128 16.9 / 15.5
+// Standalone gate: exact logits of all experts at once where the experts are few and the reduction short.  The screen pays a
+// fixed 10 us for its two sweeps, threshold and selection, the more the more tokens a task has (see gate_tokens); the exact
+// logits' cost grows with d and with the blocks of 16 experts, and is higher for rows of Wg that are no multiple of 16 bytes.
+// moe_route, exact / screened, us:
+//   E = 8    4096 tokens of d 2048 21.8 / 22.6, of d 4096 36.2 / 35.8; 1024 of d 1024 14.4 / 15.5, of d 2048 21.4 / 19.3
+//   E = 12   4096 of d 1024 18.1 / 18.7, of d 2048 31.2 / 25.8
+//   E = 24   4096 of d 640 16.3 / 17.0, of d 768 17.6 / 17.4; 2048 of d 384 12.3 / 13.6, of d 512 14.9 / 14.3; 128 of d 256 11.4 / 13.5
+//   E = 48   4096 of d 256 15.2 / 15.5, of d 512 19.6 / 17.5; 2048 of d 256 14.9 / 15.0; 128 of d 256 14.9 / 13.3
+//   E = 64   4096 of d 192 15.4 / 15.5, of d 256 17.4 / 16.0; 2048 of d 128 13.7 / 15.2; 128 of d 64 12.2 / 13.3, of d 128 13.7 / 13.6
+//   E = 128  4096 of d 128 16.7 / 16.5, of d 192 18.6 / 17.7; 2048 of d 64 13.8 / 15.2; 128 of d 64 13.8 / 14.1, of d 128 16.6 / 14.5
 __host__ __device__ inline bool route_exact(int T, int E, int d) {
-    if (E <= 16) return T > 2048 || d <= 1024;
-    const int most = E <= 32 ? 768 : E <= 48 ? 448 : E <= 64 ? 256 : 192;
+    if (E <= 16) return d <= (T > 2048 && E % 8 == 0 ? 2048 : 1024);
+    const int most = E <= 32 ? 640 : E <= 48 ? 384 : E <= 64 ? 192 : 128;
     return d <= (T > 2048 ? most : T > 1024 ? most * 3 / 4 : most / 2);
 }
 // Blocks of 16 experts (at most), reduction indices per chunk (divides d; about 8 KB of weights, so that the chunk's

@@ -16,9 +16,10 @@ CASES = [(5, 64, 1, 1), (37, 128, 7, 3), (1030, 192, 16, 2), (16, 256, 17, 2), (
          (2049, 64, 255, 5), (64, 1024, 256, 8),
          (2050, 1088, 16, 2), (2049, 64, 17, 3), (40, 1088, 16, 2), (40, 1024, 15, 2), (9, 1088, 3, 1),
          # both sides of the standalone gate's rule for short reductions, at 4, 8 and 16 tokens per task
-         (130, 384, 24, 4), (65, 448, 33, 6), (70, 256, 48, 4), (130, 192, 64, 8), (9, 64, 96, 8), (1030, 576, 20, 2), (1025, 640, 32, 4),
-         (1025, 256, 64, 8), (1030, 128, 200, 4), (2049, 768, 17, 3), (2050, 832, 32, 4), (2049, 448, 47, 4), (2050, 512, 48, 6),
-         (2049, 256, 64, 8), (4100, 256, 128, 8), (2049, 256, 255, 5)]
+         (130, 320, 24, 4), (65, 384, 32, 6), (70, 192, 48, 4), (130, 256, 33, 8), (9, 64, 96, 8), (70, 128, 64, 8), (1030, 448, 20, 2),
+         (1025, 512, 32, 4), (1025, 256, 47, 4), (1025, 192, 64, 8), (1030, 128, 200, 4), (2049, 640, 17, 3), (2050, 704, 32, 4),
+         (2049, 384, 47, 4), (2050, 448, 48, 6), (2049, 192, 64, 8), (2050, 256, 64, 8), (4100, 128, 128, 8), (4100, 192, 128, 8),
+         (2049, 192, 255, 5), (2050, 2048, 8, 2), (2049, 2112, 16, 2), (2049, 1024, 12, 2), (2049, 1088, 15, 2)]
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])
