@@ -174,7 +174,10 @@ int moe_workspace_init(const moe_problem_t *p, void *workspace, void *stream);
  * Gate (section 2.1 step 1).  logits[t,e] = sum_i x[t,i] Wg[i,e] + gate_bias[e]
  * accumulated in fp64; topk_idx[t,:] = the k largest in descending order
  * (equal scores: lower expert id first); topk_w[t,j] = softmax over the k
- * chosen logits (sums to 1).
+ * chosen logits (sums to 1).  A logit that is no number beats none and is beaten
+ * by none: position j then is the lowest expert that exactly j logits beat, or -1
+ * where there is none (which the dispatch and the whole layer report as
+ * MOE_ERR_BAD_ROUTING).
  *   x [T,d], Wg [d,E] in, dtype; gate_bias [E] fp32 in, may be NULL.
  *   topk_idx [T,k] int32 out; topk_w [T,k] fp32 out.   E <= 256.
  */
