@@ -166,7 +166,10 @@ __device__ __forceinline__ void fence_acquire(int system_scope) {
 // workgroups' half-written tiles included; with write-through stores the fence finds little to do
 // (measured: 1.5 % of the whole layer on the two large workloads).  The instruction is written out
 // because no builtin sets these cache-policy bits on a 16-byte store; every caller follows its
-// stores with sync_stores(), which waits for them.
+// stores with sync_stores(), which waits for them.  A store with both bits set is performed at system scope and is
+// acknowledged when it is: after that wait the tile is visible to every XCD, and there is nothing left in this L2 that a release
+// fence (a write-back of all the L2's dirty lines, about a microsecond) would have to find, so a tile's completion is counted
+// right behind sync_stores().
 // The s_nop belongs to the store: a vector store of more than 8 bytes reads its data registers for a few cycles
 // after it issues, and a vector ALU instruction that overwrites one of them in the very next slots changes what
 // the later lanes store.  For its own stores the compiler keeps that distance; it cannot see into this statement
@@ -175,6 +178,12 @@ __device__ __forceinline__ void fence_acquire(int system_scope) {
 __device__ __forceinline__ void store_tile16(char *p, const uint4 &v) {
     const u32x4_t w = {v.x, v.y, v.z, v.w};
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(w));
+}
+
+// The same for 4 bytes (a relaxed store at system scope is written through): results of front tasks that other workgroups read.
+template <typename T>
+__device__ __forceinline__ void store_through(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Workgroup barrier that also waits for this wavefront's outstanding global

@@ -202,17 +202,17 @@ __device__ __forceinline__ void plan_all_flags(const KArgs &a, const PlanAll &p)
 }
 __device__ __forceinline__ void plan_all_publish(const KArgs &a, const PlanAll &p, int n_rb, int n_rbs) {
     for (int e = threadIdx.x; e <= a.E; e += kThreads) {
-        a.offsets[e] = p.off[e];
-        if (e < a.E) a.counts[e] = p.cnt[e];
+        store_through(&a.offsets[e], p.off[e]);
+        if (e < a.E) store_through(&a.counts[e], p.cnt[e]);
     }
     for (int r = threadIdx.x; r <= a.R; r += kThreads) {
-        a.dest_flag_begin[r] = p.dest[r];
-        a.dest_group_begin[r] = p.grp[r];
+        store_through(&a.dest_flag_begin[r], p.dest[r]);
+        store_through(&a.dest_group_begin[r], p.grp[r]);
     }
     if (threadIdx.x == 0) {
-        a.ctrl->n_rb = (u32)n_rb;
-        a.ctrl->n_rbs = (u32)n_rbs;
-        a.ctrl->n_flags = (u32)p.dest[a.R];
+        store_through(&a.ctrl->n_rb, (u32)n_rb);
+        store_through(&a.ctrl->n_rbs, (u32)n_rbs);
+        store_through(&a.ctrl->n_flags, (u32)p.dest[a.R]);
     }
 }
 
@@ -498,7 +498,7 @@ __device__ __forceinline__ void perm_block_lds(const KArgs &a, const PlanAll &p,
     if (a.capacity > 0) {
         // padded layout: the unused entries of perm, experts dealt round-robin to the blocks
         for (int e = b; e < E; e += a.nPB)
-            for (int j = p.cnt[e] + tid; j < a.capacity; j += kThreads) a.perm[(size_t)e * a.capacity + j] = -1;
+            for (int j = p.cnt[e] + tid; j < a.capacity; j += kThreads) store_through(&a.perm[(size_t)e * a.capacity + j], -1);
     }
     __syncthreads();
     for (int q = tid; q < nt * k; q += kThreads) {
@@ -506,11 +506,11 @@ __device__ __forceinline__ void perm_block_lds(const KArgs &a, const PlanAll &p,
         const int e = a.idx[s];
         if (e < 0 || e >= E) continue;
         const int pos = base[e] + __popcll(mask[e] & ((1ull << tl) - 1ull));
-        a.perm[pos] = s;
-        a.inv_perm[s] = pos;
+        store_through(&a.perm[pos], s);
+        store_through(&a.inv_perm[s], pos);
         const int r = (t0 + tl) / a.per_dest;
         const int f = r * E + e;
-        a.slot_flag[s] = p.dest[r] + p.nfl[f] + (((pos - p.off[e]) >> lm) - (p.segb[f] >> lm)) * a.ncb;
+        store_through(&a.slot_flag[s], p.dest[r] + p.nfl[f] + (((pos - p.off[e]) >> lm) - (p.segb[f] >> lm)) * a.ncb);
     }
     __syncthreads();
 }

@@ -302,12 +302,40 @@ __device__ __forceinline__ void store_c_tile(const char *c_tile, int c_stride, i
     }
 }
 
+struct StageLds {  // broadcast slots of a stage's task loop, in dynamic LDS at KArgs::sched_lds_off
+    int next, ok;
+    int pick;  // tile stage: the list to draw from next, -1 = all lists are empty
+    int n_rb, n_rbs;  // row blocks in use, big / small (from the front stage)
+    int q, hops, ticket, g1_left;  // ready-queue scheduler: the workgroup's state (see ready_queue_stage)
+    // statistics of the stage that runs, kept by thread 0: tiles of GEMM1 and GEMM2, publish tiles, releases, end of the last tile.  They
+    // go to the control block once per stage: an atomic per tile and counter, all workgroups on one line, is what the
+    // next tile's first wait would wait for.
+    int n_g1, n_g2, n_pub, n_rel;
+    u64 t_end;
+};
+__device__ __forceinline__ void stage_stats_begin(StageLds *sl) {
+    sl->n_g1 = sl->n_g2 = sl->n_pub = sl->n_rel = 0;
+}
+__device__ __forceinline__ void stage_stats_end(const KArgs &a, const StageLds *sl, u64 t0) {
+    Ctrl *c = a.ctrl;
+    if (sl->n_rel) atomicAdd(&c->stats[3], (u64)sl->n_rel);
+    if (sl->n_pub) atomicAdd(&c->stats[2], (u64)sl->n_pub);
+    if (sl->n_g1) {
+        atomicAdd(&c->stats[4], (u64)sl->n_g1);
+        atomicMax(&c->stats[8 + 3], sl->t_end - t0);
+    }
+    if (sl->n_g2) {
+        atomicAdd(&c->stats[5], (u64)sl->n_g2);
+        atomicMax(&c->stats[8 + 4], sl->t_end - t0);
+    }
+}
+
 // GEMM1 + SwiGLU: h[rows of the block, n0 .. n0+ncols) = silu(x W1[e]) * (x W3[e]).
 // Rows are gathered straight from x through perm: the permuted activations are
 // never materialised.
 // `after_gemm()` runs between the main loop and the write-out (the megakernel draws
 // its next tile there, so that the counter's latency hides behind the write-out).
-// Returns, in thread 0, how many GEMM1 tiles of the row block had finished before this one.
+// Returns, in thread 0 and under the ready-queue scheduler, how many GEMM1 tiles of the row block had finished before this one.
 template <class P, class Hook>
 __device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char *smem, Hook after_gemm) {
     using ET = typename P::ET;
@@ -326,13 +354,14 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char 
     char *h = (char *)a.h + ((size_t)ti.row0 * a.f + ti.n0) * sizeof(ET);
     store_c_tile(smem, P::C_STRIDE, ti.nrows, ti.ncols * (int)sizeof(ET) / 16,
                  [&](int r) { return h + (size_t)r * a.f * sizeof(ET); });
-    sync_stores();
+    sync_stores();  // (the rows are in memory: see store_tile16)
     MOE_TT(a.ctrl, 2);
     u32 before = 0;
     if (threadIdx.x == 0) {
-        fence_release(0);
-        before = atomicAdd(&a.h_ready[ti.rb], 1u);
-        atomicAdd(&a.ctrl->stats[4], 1ull);
+        if (a.rq_slots)
+            before = atomicAdd(&a.h_ready[ti.rb], 1u);
+        else
+            atomicAdd(&a.h_ready[ti.rb], 1u);  // (nobody waits for its answer)
     }
     MOE_TT(a.ctrl, 3);
     return before;
@@ -395,6 +424,7 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
     const int *s_dest = s_slot + P::BM;
     const int *s_seg = s_dest + P::BM;
     const int *s_nseg = s_seg + P::BM + 1;
+    StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     MOE_TT_BEGIN();
     const int nseg = *s_nseg;
     const int cbn = (ti.ncols + a.tile_n - 1) / a.tile_n;  // column blocks in this compute tile
@@ -430,7 +460,7 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
             const u64 n = (u64)nseg * cbn;
             atomicAdd(&a.ctrl->stats[0], n);
             atomicAdd(&a.ctrl->stats[1], n);
-            atomicAdd(&a.ctrl->stats[2], n);
+            sl->n_pub += nseg * cbn;
         }
         // (the flags were stored by lane 0 of this wavefront)
         if (a.dest_done && wave == 0)
@@ -441,7 +471,8 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
         sync_stores();
         MOE_TT(a.ctrl, 12);
         if (wave == 0) {
-            fence_release(0);  // the rows of this tile may now be counted
+            // the rows of this tile may now be counted: they were written through, and sync_stores() waited until they were
+            // in memory (see store_tile16)
             u64 n_fence = 0, n_flag = 0;
             for (int base = 0; base < nseg; base += 64) {
                 // lane i: the cbn flags [f0, f0 + cbn) of publish row-tile i; they lie in one
@@ -495,8 +526,8 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
                     atomicAdd(&a.ctrl->stats[0], n_fence);
                     atomicAdd(&a.ctrl->stats[1], n_flag);
                 }
-                atomicAdd(&a.ctrl->stats[2], (u64)nseg * cbn);
-                atomicAdd(&a.ctrl->stats[3], 1ull);
+                sl->n_pub += nseg * cbn;
+                sl->n_rel += 1;
             }
         }
     }
@@ -519,7 +550,6 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, const TileInfo &ti, char
     MOE_TT(a.ctrl, 7);
     publish_tile<P>(a, ti, smem);
     MOE_TT(a.ctrl, 8);
-    if (threadIdx.x == 0) atomicAdd(&a.ctrl->stats[5], 1ull);
 }
 
 // ---- the stages of the megakernel
@@ -533,12 +563,6 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, const TileInfo &ti, char
 // reference to the kernel's own copy would force that copy into per-lane
 // scratch memory, for every stage), and LDS as an offset.  Everything else is
 // inlined into the kernel, so that the kernel's launch bounds govern it.
-struct StageLds {  // broadcast slots of a stage's task loop, in dynamic LDS at KArgs::sched_lds_off
-    int next, ok;
-    int pick;  // tile stage: the list to draw from next, -1 = all lists are empty
-    int n_rb, n_rbs;  // row blocks in use, big / small (from the front stage)
-    int q, hops, ticket, g1_left;  // ready-queue scheduler: the workgroup's state (see ready_queue_stage)
-};
 
 // One kind of tile (GEMM1 if GATED, else GEMM2; big or SMALL row blocks) from the eight tile
 // queues, the one of XCD `home` first, until none is left; or, when one_a >= 0, exactly one
@@ -561,6 +585,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const Tables tb = decode_tables(a, smem, n_rb, n_rbs);
     const u64 t0 = kernel_start_ticks(c);
+    if (tid == 0) stage_stats_begin(sl);
     constexpr int LIST = (GATED ? 0 : 2) + (SMALL ? 1 : 0);
     *caller_local = LIST;  // (see the call sites)
     bool more = true;
@@ -629,15 +654,18 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                 if (single) fence_acquire(0);
                 __syncthreads();
                 MOE_TT(c, 5);
-                if (sl->ok)
+                if (sl->ok) {
                     g2_tile<P>(a, ti, smem, draw);
-                else
+                    if (tid == 0) sl->n_g2 += 1;
+                } else {
                     draw();
+                }
                 MOE_TT(c, 9);
             }
             __syncthreads();
             if (tid == 0) {
-                mark_phase_end(c, GATED ? 3 : 4, t0);
+                if (GATED) sl->n_g1 += 1;
+                sl->t_end = now_ticks();
                 sl->next = (int)next;
             }
             __syncthreads();
@@ -648,6 +676,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
 #endif
         }
     }
+    if (tid == 0) stage_stats_end(a, sl, t0);
 }
 
 // ---- the fused FFN (moe_problem_t::fuse_ffn; paper section 2.3: a tile traverses dispatch -> GEMM -> activation ->
@@ -675,7 +704,6 @@ __device__ __forceinline__ void fused_block(const KArgs &a, const TileInfo &rb, 
         const size_t wofs = (size_t)rb.e * a.d * a.f + n0;
         gemm_tile_bf16<C, true, true, false>(xrow, (const ET *)a.W1 + wofs, (const ET *)a.W3 + wofs, a.f, ncols, a.d, smem,
                                              [] {}, hres, n0, a.f);
-        if (threadIdx.x == 0) atomicAdd(&a.ctrl->stats[4], 1ull);
     }
     // (the last tile's epilogue ended with a barrier: h is complete for every wavefront)
     TileInfo ti = rb;
@@ -687,7 +715,6 @@ __device__ __forceinline__ void fused_block(const KArgs &a, const TileInfo &rb, 
         gemm_tile_bf16<C, false, false, true>([](int) { return (const ET *)nullptr; }, B0, B0, a.d, ti.ncols, a.f, smem, [] {},
                                               hres, 0, 0);
         publish_tile<P>(a, ti, smem);
-        if (threadIdx.x == 0) atomicAdd(&a.ctrl->stats[5], 1ull);
     }
 }
 
@@ -703,6 +730,7 @@ static __device__ __attribute__((noinline)) void fused_stage(KArgsAddr args, u32
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const Tables tb = decode_tables(a, smem, n_rb, 0);
     const u64 t0 = kernel_start_ticks(c);
+    if (tid == 0) stage_stats_begin(sl);
     *caller_local = 4;  // (see the call sites of tile_stage)
     while (true) {
         // the first list, from this XCD's on, that still has row blocks
@@ -738,14 +766,16 @@ static __device__ __attribute__((noinline)) void fused_stage(KArgsAddr args, u32
             fused_block<P>(a, rb, smem);
             __syncthreads();
             if (tid == 0) {
-                mark_phase_end(c, 3, t0);
-                mark_phase_end(c, 4, t0);
+                sl->n_g1 += a.tl.NT1;
+                sl->n_g2 += a.tl.NT2;
+                sl->t_end = now_ticks();
                 sl->next = (int)next;
             }
             __syncthreads();
             i = uniform(sl->next);
         }
     }
+    if (tid == 0) stage_stats_end(a, sl, t0);
 }
 
 // ---- combine

@@ -149,7 +149,7 @@ __device__ __forceinline__ void wgt_task(const KArgs &a, int task, char *smem) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             o[i] = (u32)tile[(kp + 2 * i) * LD + ee] | ((u32)tile[(kp + 2 * i + 1) * LD + ee] << 16);
-        if (e0 + ee < E) *(u32x4_t *)(WgT + (size_t)(e0 + ee) * d + k0 + kp) = o;
+        if (e0 + ee < E) store_tile16((char *)(WgT + (size_t)(e0 + ee) * d + k0 + kp), make_uint4(o[0], o[1], o[2], o[3]));
     }
     __syncthreads();
 }
@@ -757,8 +757,8 @@ __device__ __forceinline__ bool route_screened(const KArgs &a, int t0, int TOK, 
         for (int q = 0; q < CPL; ++q)
             if (lpt * q < n_max && rk[q] < k) {
                 const int e = ce[lj + lpt * q];
-                a.idx[(size_t)(t0 + tl) * k + rk[q]] = e;
-                a.w[(size_t)(t0 + tl) * k + rk[q]] = (float)(ex[q] / sum);
+                store_through(&a.idx[(size_t)(t0 + tl) * k + rk[q]], e);
+                store_through(&a.w[(size_t)(t0 + tl) * k + rk[q]], (float)(ex[q] / sum));
                 if (do_hist) count_choice(a, cnt, t0 + tl, e);
             }
     }

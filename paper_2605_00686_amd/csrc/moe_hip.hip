@@ -217,10 +217,13 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
         __syncthreads();
         return uniform(sl->ok);  // 0: not reached, 1: reached, 2: reached, but an error is recorded
     };
-    auto release_and_count = [&](u32 *counter) __attribute__((always_inline)) {
+    // (the tasks' results are atomics and written-through stores, which sync_stores() sees into memory: a release fence would write
+    // back everything dirty in the XCD's L2, and that stalls the other workgroups' loads.  Only the single-workgroup plan and
+    // its permutation blocks store their many tables in the ordinary way.)
+    auto release_and_count = [&](u32 *counter, bool fence) __attribute__((always_inline)) {
         sync_stores();
         if (tid == 0) {
-            fence_release(0);
+            if (fence) fence_release(0);
             atomicAdd(counter, 1u);
         }
     };
@@ -229,7 +232,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     if constexpr (V > 0) {
         while (task < a.t_gate) {
             wgt_task(a, task, smem);
-            release_and_count(&c->wgt_done);
+            release_and_count(&c->wgt_done, false);
             draw_next(-1);
         }
     }
@@ -239,7 +242,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
             if (!seen_wgt) seen_wgt = wait_for(&c->wgt_done, (u32)a.t_gate) != 0;  // the transposed gate weights are complete
             return seen_wgt;
         });
-        release_and_count(&c->route_done);
+        release_and_count(&c->route_done, false);
         draw_next(0);
     }
     int n_rb = 0, n_rbs = 0;
@@ -267,21 +270,21 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
                 else
                     perm_block_lds(a, p, task - a.t_perm);
             }
-            release_and_count(plan ? &c->plan_done : &c->perm_done);
+            release_and_count(plan ? &c->plan_done : &c->perm_done, false);
             draw_next(plan ? 1 : 2);
         }
         bad = wait_for(&c->plan_done, 1u) != 1 || bad;
     } else {
         if (task == a.t_plan) {
             if (routed != 0) plan_task(a, smem);
-            release_and_count(&c->plan_done);
+            release_and_count(&c->plan_done, true);
             draw_next(1);
         }
         bad = wait_for(&c->plan_done, 1u) != 1 || bad;
         while (task < a.t_g1) {
             const int b = task - a.t_perm;
             if (!bad) perm_task<ET>(a, b, smem, a.blk_base + (size_t)b * a.E, a.counts);
-            release_and_count(&c->perm_done);
+            release_and_count(&c->perm_done, true);
             draw_next(2);
         }
         if (!bad) {
@@ -404,9 +407,8 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
         }
     }
     // last workgroup out copies the statistics and clears the control block
-    sync_stores();
+    sync_stores();  // (what the last workgroup reads of the others' work are atomics)
     if (tid == 0) {
-        fence_release(0);
         const u32 old = atomicAdd(&c->exit_count, 1u);
         s_last = (old == gridDim.x - 1) ? 1 : 0;
         if (s_last) fence_acquire(0);

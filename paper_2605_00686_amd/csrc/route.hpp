@@ -376,8 +376,8 @@ __device__ __forceinline__ void select_full(const KArgs &a, int t0, int TOK, con
     for (int i = 0; i < TPW; ++i) {
         const int tl = wave + 4 * i, t = t0 + tl;
         if (tl < TOK && t < a.T && lane < k) {
-            a.idx[(size_t)t * k + lane] = my_e[i];
-            a.w[(size_t)t * k + lane] = (float)(ex[i] / sum[i]);
+            store_through(&a.idx[(size_t)t * k + lane], my_e[i]);
+            store_through(&a.w[(size_t)t * k + lane], (float)(ex[i] / sum[i]));
             if (do_hist) count_choice(a, cnt, t, my_e[i]);
         }
     }
@@ -442,10 +442,9 @@ __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int t
                 double *lg = (double *)lds;
                 const size_t per = (size_t)kRouteTokens * E;
                 double *mine = a.gate_partial + ((size_t)block * S + slice) * per;
-                for (int i = threadIdx.x; i < (int)per; i += kThreads) mine[i] = lg[i];
+                for (int i = threadIdx.x; i < (int)per; i += kThreads) store_through(&mine[i], lg[i]);
                 sync_stores();
                 if (threadIdx.x == 0) {
-                    fence_release(0);
                     const u32 before = atomicAdd(&a.gate_parts[block], 1u);
                     *s_slot = (before == (u32)(S - 1)) ? 1 : 0;
                     if (*s_slot) fence_acquire(0);
