@@ -25,26 +25,31 @@ constexpr u64 kWaitTicks = 400000000ull;  // 4 s of the 100 MHz wall clock: defa
 // (the bound a call uses is KArgs::wait_ticks, from moe_problem_t::wait_ticks: tests of the time-out path set it to
 // almost nothing, so that the waits give up, the error spreads and every workgroup leaves in the ordinary way)
 
+// A counter that many workgroups add to, alone on its cache line.  Atomics on one line are served one after the other wherever they
+// come from, 11 ns each on this chip (256 workgroups with one atomic each: 2.8 us on one line, 0.8 us on one line per XCD), and
+// the queue in front of a line holds up the loads of the tiles' operands behind it.
+struct alignas(128) Counter {
+    u32 v;
+};
+constexpr int kExitGroups = 8;
+
 // Control block at the start of the workspace.  All zero between calls: the
 // last workgroup to leave a kernel clears what the kernel dirtied.
 struct Ctrl {
-    u32 next_task;   // persistent scheduler: next task to hand out
-    u32 route_done;  // gate tasks finished
-    u32 plan_done;   // 1 once offsets / tables are valid
-    u32 perm_done;   // permutation blocks finished
-    u32 exit_count;  // workgroups that left the kernel
-    u32 error;       // first device status (moe_status_t as positive number), 0 = ok
+    Counter next_task;   // persistent scheduler: next front task to hand out
+    Counter wgt_done;    // gate-weight transposition tasks finished
+    Counter route_done;  // gate tasks finished
+    Counter plan_done;   // 1 once offsets / tables are valid
+    Counter perm_done;   // permutation blocks finished
+    Counter error;       // first device status (moe_status_t as positive number), 0 = ok
+    Counter exit_group[kExitGroups];  // workgroups that left the kernel, by workgroup number modulo kExitGroups ...
+    Counter exit_count;  // ... and groups whose last one did
+    Counter tile_next[4][8];  // tile queues, [GEMM1 big, GEMM1 small, GEMM2 big, GEMM2 small] x XCD: next entry to hand out
+    Counter rq_head[8];    // ready queues, one per XCD: next entry to take ...
+    Counter rq_tail[8];    // ... and next free entry
     u32 n_rb;        // (big) row blocks in use, all experts
+    u32 n_rbs;       // small row blocks in use (mixed tile heights), all experts
     u32 n_flags;     // publish tiles / flags in use
-    u32 tile_next[4][8];  // tile queues, [GEMM1 big, GEMM1 small, GEMM2 big, GEMM2 small] x XCD: next entry to hand out
-    u32 comb_next;     // next combine task
-    u32 wgt_done;      // gate-weight transposition tasks finished
-    u32 n_rbs;         // small row blocks in use (mixed tile heights), all experts
-    u32 pad[5];
-    u32 rq_head[8];    // ready queues, one per XCD: next entry to take ...
-    u32 rq_tail[8];    // ... and next free entry
-    u64 t0;          // wall-clock tick of the first task drawn
-    u64 stats[MOE_NUM_STATS];
 #ifdef MOE_TILE_TIMING
     u64 dbg[48];  // development build only: time spent in the parts of a tile, summed over tiles
 #endif
@@ -109,7 +114,8 @@ struct KArgs {
     int32_t *flag_base;        // [R][E]
     int32_t *dest_flag_begin;  // [R+1]
     int32_t *dest_group_begin; // [R+1] first fence group of destination r
-    u32 *group_counter;        // [fence groups] publish tiles written so far (PER_DEST)
+    u32 *group_counter;        // [fence groups * group_stride] publish tiles written so far (PER_DEST)
+    int group_stride;          // words from one group's counter to the next: a cache line when a group is a whole destination
     int32_t *rb_base;          // [E+1] first row block of expert e
     int32_t *rb_expert;        // [maxRB]
     int32_t *rbs_base;         // [E+1] first small row block of expert e (each expert has at most one)
@@ -122,6 +128,7 @@ struct KArgs {
     u32 *dest_done;            // [R] flags stored so far per destination (ready-queue scheduler), else NULL
     u32 *rq_slots;             // [8][rq_cap] ready-queue entries, 0 = empty (ready-queue scheduler), else NULL
     int rq_cap;                // entries per ready queue: all GEMM2 tiles plus all combine tasks
+    u64 *wg_stats;             // [workgroups][kWgStats] what each workgroup of the megakernel has to report (see StageLds)
     size_t zero_bytes;         // bytes from ctrl that must be zero between calls
     int tab_lds_off;           // megakernel: LDS offset of the cached decode tables, 0 = none
     int plan_all;              // megakernel: every workgroup derives the plan by itself (see PlanAll); needs the cached tables
@@ -131,7 +138,7 @@ struct KArgs {
 __device__ __forceinline__ u64 now_ticks() { return wall_clock64(); }
 
 __device__ __forceinline__ void set_error(Ctrl *c, int status) {
-    atomicCAS(&c->error, 0u, (u32)(-status));
+    atomicCAS(&c->error.v, 0u, (u32)(-status));
 }
 
 __device__ __forceinline__ u32 ld_relaxed_agent(const u32 *p) {
@@ -195,6 +202,26 @@ __device__ __forceinline__ void sync_stores() {
     __syncthreads();
 }
 
+constexpr int kLeadGroups = 16;
+constexpr int kMaxWorkgroups = 512;  // of the megakernel
+constexpr int kWgStats = 32;         // words of a workgroup's report: MOE_NUM_STATS, then the tick of its start
+// What a workgroup keeps for its life, in dynamic LDS at KArgs::sched_lds_off: broadcast slots of the stages' task loops, and its
+// share of the statistics.  The latter leave the workgroup once, at its end, as a report of its own that the last workgroup
+// out sums up: an atomic per task and counter, all workgroups on the same lines, held up the operand loads of everybody (the
+// last GEMM2 tiles of 128 tokens x 128 experts took 36 us instead of 16 while the other workgroups added up their numbers).
+struct StageLds {
+    int next, ok;
+    int pick;  // tile stage: the list to draw from next, -1 = all lists are empty
+    int n_rb, n_rbs;  // row blocks in use, big / small (from the front stage)
+    int q, hops, ticket, g1_left;  // ready-queue scheduler: the workgroup's state (see ready_queue_stage)
+    int n_lead, lead[kLeadGroups][2];  // fence groups the tile being published has completed: first flag, end (see publish_tile)
+    // numbered like moe_megakernel_forward's stats; [8..13] are the tick of the workgroup's last end of that phase, 0 = none.  Thread
+    // 0's, except [6]
+    u64 stat[MOE_NUM_STATS];
+    u64 t_start;
+};
+__device__ __forceinline__ void mark_phase_end(StageLds *sl, int phase) { sl->stat[8 + phase] = now_ticks(); }
+
 // Spin until *p >= target (agent scope), bounded by the wall clock and by the
 // global error flag so that a broken dependency drains the grid instead of
 // hanging it.  Called by one thread; returns false on time-out; `limit` is the
@@ -202,7 +229,7 @@ __device__ __forceinline__ void sync_stores() {
 // (which invalidates this CU's and this XCD's non-coherent cache lines: what the
 // memory model asks for data written on another XCD; an acquire that kept the L2
 // measured within 0.6 % of this one on every workload).
-__device__ __forceinline__ bool wait_ge(Ctrl *c, const u32 *p, u32 target, u64 limit) {
+__device__ __forceinline__ bool wait_ge(Ctrl *c, StageLds *sl, const u32 *p, u32 target, u64 limit) {
     if (ld_relaxed_agent(p) >= target) {
         fence_acquire(0);
         return true;
@@ -214,31 +241,21 @@ __device__ __forceinline__ bool wait_ge(Ctrl *c, const u32 *p, u32 target, u64 l
         if (ld_relaxed_agent(p) >= target) break;
         __builtin_amdgcn_s_sleep(2);
         if ((++spins & 63) == 0) {
-            if (ld_relaxed_agent(&c->error) != 0) {
+            if (ld_relaxed_agent(&c->error.v) != 0) {
                 ok = false;
                 break;
             }
             if (now_ticks() - t0 > limit) {
                 set_error(c, MOE_ERR_TIMEOUT);
-                atomicAdd(&c->stats[6], 1ull);
+                sl->stat[6] += 1;
                 ok = false;
                 break;
             }
         }
     }
-    atomicAdd(&c->stats[14], now_ticks() - t0);
+    sl->stat[14] += now_ticks() - t0;
     if (ok) fence_acquire(0);
     return ok;
-}
-
-// phase bookkeeping for the in-kernel timeline (ticks since the first task)
-__device__ __forceinline__ u64 kernel_start_ticks(Ctrl *c) {
-    return __hip_atomic_load(&c->t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// t0 = kernel_start_ticks(), read once per stage: it is final before any task is drawn, and
-// reading it here would put a trip to memory between two workgroup barriers of every task
-__device__ __forceinline__ void mark_phase_end(Ctrl *c, int phase, u64 t0) {
-    atomicMax(&c->stats[8 + phase], now_ticks() - t0);
 }
 
 #ifdef MOE_TILE_TIMING

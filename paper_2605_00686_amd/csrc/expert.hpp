@@ -194,7 +194,7 @@ __device__ __forceinline__ int ready_queue_of_block(int n, int rb) {
 // `n` consecutive entries first, first + 1, ... to queue q, by all lanes of one wavefront
 __device__ __forceinline__ void ready_push(const KArgs &a, int q, u32 first, int n, int lane) {
     u32 base = 0;
-    if (lane == 0) base = atomicAdd(&a.ctrl->rq_tail[q], (u32)n);
+    if (lane == 0) base = atomicAdd(&a.ctrl->rq_tail[q].v, (u32)n);
     base = (u32)__builtin_amdgcn_readfirstlane((int)base);
     u32 *slots = a.rq_slots + (size_t)q * a.rq_cap;
     for (int i = lane; i < n; i += 64)
@@ -243,6 +243,7 @@ __device__ __forceinline__ void mark_global(KArgs &a) {
     a.dest_flag_begin = as_global(a.dest_flag_begin);
     a.dest_group_begin = as_global(a.dest_group_begin);
     a.group_counter = as_global(a.group_counter);
+    a.wg_stats = as_global(a.wg_stats);
     a.rb_base = as_global(a.rb_base);
     a.rb_expert = as_global(a.rb_expert);
     a.rbs_base = as_global(a.rbs_base);
@@ -302,34 +303,6 @@ __device__ __forceinline__ void store_c_tile(const char *c_tile, int c_stride, i
     }
 }
 
-struct StageLds {  // broadcast slots of a stage's task loop, in dynamic LDS at KArgs::sched_lds_off
-    int next, ok;
-    int pick;  // tile stage: the list to draw from next, -1 = all lists are empty
-    int n_rb, n_rbs;  // row blocks in use, big / small (from the front stage)
-    int q, hops, ticket, g1_left;  // ready-queue scheduler: the workgroup's state (see ready_queue_stage)
-    // statistics of the stage that runs, kept by thread 0: tiles of GEMM1 and GEMM2, publish tiles, releases, end of the last tile.  They
-    // go to the control block once per stage: an atomic per tile and counter, all workgroups on one line, is what the
-    // next tile's first wait would wait for.
-    int n_g1, n_g2, n_pub, n_rel;
-    u64 t_end;
-};
-__device__ __forceinline__ void stage_stats_begin(StageLds *sl) {
-    sl->n_g1 = sl->n_g2 = sl->n_pub = sl->n_rel = 0;
-}
-__device__ __forceinline__ void stage_stats_end(const KArgs &a, const StageLds *sl, u64 t0) {
-    Ctrl *c = a.ctrl;
-    if (sl->n_rel) atomicAdd(&c->stats[3], (u64)sl->n_rel);
-    if (sl->n_pub) atomicAdd(&c->stats[2], (u64)sl->n_pub);
-    if (sl->n_g1) {
-        atomicAdd(&c->stats[4], (u64)sl->n_g1);
-        atomicMax(&c->stats[8 + 3], sl->t_end - t0);
-    }
-    if (sl->n_g2) {
-        atomicAdd(&c->stats[5], (u64)sl->n_g2);
-        atomicMax(&c->stats[8 + 4], sl->t_end - t0);
-    }
-}
-
 // GEMM1 + SwiGLU: h[rows of the block, n0 .. n0+ncols) = silu(x W1[e]) * (x W3[e]).
 // Rows are gathered straight from x through perm: the permuted activations are
 // never materialised.
@@ -378,7 +351,8 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char 
 //             ones: the granularity knob of section 4.1).  Whoever completes a group's
 //             count is its leader: one fence at the requested scope, then all flags of
 //             the group, stored by a whole wavefront (phase 2; lane-parallel signals as
-//             in appendix B).
+//             in appendix B), or by all four where the group is large: the layer's last tile completes every
+//             destination at once, with all other workgroups waiting for these flags.
 // Row bookkeeping of a publish: slot and destination of every row of the compute
 // tile and the list of publish row-tiles, into LDS behind the GEMM's region (so it
 // can run while the GEMM's first loads are in flight).
@@ -414,6 +388,21 @@ __device__ __forceinline__ void publish_prepare(const KArgs &a, const TileInfo &
     }
     __syncthreads();
     MOE_TT(a.ctrl, 11);
+}
+
+// flags[begin .. end) = epoch by the whole workgroup, four at a time (every flag is stored by one aligned dword of a store that is
+// written through, so a reader sees the old or the new value).  34 us of the layer of 4096 tokens on 128 experts passed while one
+// wavefront stored its 42000 flags one per lane.
+__device__ __forceinline__ void store_flags(u32 *flags, int begin, int end, u32 epoch, int sys) {
+    // [mid, last): whole 16-byte pieces
+    const int mid = min(begin + (int)((0u - (u32)((uintptr_t)(flags + begin) >> 2)) & 3u), end), last = mid + ((end - mid) & ~3);
+    const uint4 v = make_uint4(epoch, epoch, epoch, epoch);
+    for (int i = mid + 4 * threadIdx.x; i < last; i += 4 * kThreads) store_tile16((char *)(flags + i), v);
+    const int tid = threadIdx.x;
+    if (tid < 8) {
+        const int i = tid < 4 ? begin + tid : last + tid - 4;
+        if (i < (tid < 4 ? mid : end)) st_relaxed(&flags[i], epoch, sys);
+    }
 }
 
 template <class P>
@@ -458,9 +447,9 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
         }
         if (tid == 0) {
             const u64 n = (u64)nseg * cbn;
-            atomicAdd(&a.ctrl->stats[0], n);
-            atomicAdd(&a.ctrl->stats[1], n);
-            sl->n_pub += nseg * cbn;
+            sl->stat[0] += n;
+            sl->stat[1] += n;
+            sl->stat[2] += n;
         }
         // (the flags were stored by lane 0 of this wavefront)
         if (a.dest_done && wave == 0)
@@ -474,6 +463,7 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
             // the rows of this tile may now be counted: they were written through, and sync_stores() waited until they were
             // in memory (see store_tile16)
             u64 n_fence = 0, n_flag = 0;
+            int n_lead = 0;
             for (int base = 0; base < nseg; base += 64) {
                 // lane i: the cbn flags [f0, f0 + cbn) of publish row-tile i; they lie in one
                 // destination and in one or more of its fence groups
@@ -500,7 +490,7 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
                     const int gid = gid0 + gl;
                     if (has) {
                         const u32 cnt = (u32)(min(f0 + cbn, gend) - max(f0, gbeg));
-                        const u32 old = atomicAdd(&a.group_counter[gid], cnt);
+                        const u32 old = atomicAdd(&a.group_counter[(size_t)gid * a.group_stride], cnt);
                         lead = (old + cnt == (u32)(gend - gbeg));
                     }
                     u64 m = __ballot(lead);
@@ -512,9 +502,14 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
                         // writer before it was counted
                         fence_acquire(0);
                         fence_release(sys);  // the one fence of this group
-                        for (int fi = gb + lane; fi < ge; fi += 64) st_relaxed(&a.flags[fi], a.epoch, sys);
+                        if (ge - gb >= 256 && n_lead < kLeadGroups) {
+                            if (lane == 0) sl->lead[n_lead][0] = gb, sl->lead[n_lead][1] = ge;
+                            ++n_lead;
+                        } else {
+                            for (int fi = gb + lane; fi < ge; fi += 64) st_relaxed(&a.flags[fi], a.epoch, sys);
+                        }
                         if (lane == 0)
-                            __hip_atomic_store(&a.group_counter[gi], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(&a.group_counter[(size_t)gi * a.group_stride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         n_fence += 1;
                         n_flag += (u64)(ge - gb);
                         if (a.dest_done) ready_flags_stored(a, __shfl(dst, src, 64), ge - gb, lane);
@@ -522,14 +517,15 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
                 }
             }
             if (lane == 0) {
-                if (n_fence) {
-                    atomicAdd(&a.ctrl->stats[0], n_fence);
-                    atomicAdd(&a.ctrl->stats[1], n_flag);
-                }
-                sl->n_pub += nseg * cbn;
-                sl->n_rel += 1;
+                sl->stat[0] += n_fence;
+                sl->stat[1] += n_flag;
+                sl->stat[2] += (u64)nseg * cbn;
+                sl->stat[3] += 1;
+                sl->n_lead = n_lead;
             }
         }
+        __syncthreads();
+        for (int i = 0, n = uniform(sl->n_lead); i < n; ++i) store_flags(a.flags, sl->lead[i][0], sl->lead[i][1], a.epoch, sys);
     }
     __syncthreads();
     MOE_TT(a.ctrl, 13);
@@ -584,8 +580,6 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
     Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const Tables tb = decode_tables(a, smem, n_rb, n_rbs);
-    const u64 t0 = kernel_start_ticks(c);
-    if (tid == 0) stage_stats_begin(sl);
     constexpr int LIST = (GATED ? 0 : 2) + (SMALL ? 1 : 0);
     *caller_local = LIST;  // (see the call sites)
     bool more = true;
@@ -597,7 +591,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
             q = GATED ? one_a : 0;
             i = GATED ? one_b : 0;
             n = i + 1;
-            counter = &c->rq_head[ticket_q >= 0 ? ticket_q : 0];
+            counter = &c->rq_head[ticket_q >= 0 ? ticket_q : 0].v;
         } else {
             // one look at the eight counters of this kind picks the first list, from this XCD's on, that
             // still has entries (a draw from an empty list costs a trip to memory and two barriers)
@@ -608,7 +602,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                     const int qq = (home + tid) % kTileQueues;
                     const TileQueue t2 = tile_queue(a, n_rb, n_rbs, qq);
                     const int n2 = GATED ? (SMALL ? t2.n1s : t2.n1b) : (SMALL ? t2.n2s : t2.n2b);
-                    has = ld_relaxed_agent(&c->tile_next[LIST][qq]) < (u32)n2;
+                    has = ld_relaxed_agent(&c->tile_next[LIST][qq].v) < (u32)n2;
                 }
                 const u64 m = __ballot(has);
                 if (tid == 0) sl->pick = m ? (home + __ffsll((long long)m) - 1) % kTileQueues : -1;
@@ -618,7 +612,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
             if (q < 0) break;
             const TileQueue tq0 = tile_queue(a, n_rb, n_rbs, q);
             n = GATED ? (SMALL ? tq0.n1s : tq0.n1b) : (SMALL ? tq0.n2s : tq0.n2b);
-            counter = &c->tile_next[LIST][q];
+            counter = &c->tile_next[LIST][q].v;
             __syncthreads();
             if (tid == 0) sl->next = (int)atomicAdd(counter, 1u);
             __syncthreads();
@@ -640,7 +634,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                 // tiles (every writer of the block released its rows before it was counted)
                 if (a.rq_slots && tid == 0 && before + 1 == (u32)a.tl.NT1) {
                     const int rq = SMALL ? ready_queue_of_block(n_rbs, ti.rb - n_rb) : ready_queue_of_block(n_rb, ti.rb);
-                    const u32 base = atomicAdd(&c->rq_tail[rq], (u32)a.tl.NT2);
+                    const u32 base = atomicAdd(&c->rq_tail[rq].v, (u32)a.tl.NT2);
                     u32 *slots = a.rq_slots + (size_t)rq * a.rq_cap;
                     for (int j = 0; j < a.tl.NT2; ++j)
                         if (base + j < (u32)a.rq_cap) st_relaxed(&slots[base + j], 1u + (u32)ti.rb * a.tl.NT2 + j, 0);
@@ -650,13 +644,13 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                 const TileInfo ti = single ? decode_block_tile<SMALL>(a, tb, one_a, one_b, P::BN2, a.d)
                                            : decode_tile<SMALL>(a, tb, tq, i, a.tl.NT2, P::BN2, a.d);
                 // h rows were released (agent scope) by their GEMM1 tiles before those counted themselves
-                if (tid == 0) sl->ok = (single || wait_ge(c, &a.h_ready[ti.rb], (u32)a.tl.NT1, a.wait_ticks)) ? 1 : 0;
+                if (tid == 0) sl->ok = (single || wait_ge(c, sl, &a.h_ready[ti.rb], (u32)a.tl.NT1, a.wait_ticks)) ? 1 : 0;
                 if (single) fence_acquire(0);
                 __syncthreads();
                 MOE_TT(c, 5);
                 if (sl->ok) {
                     g2_tile<P>(a, ti, smem, draw);
-                    if (tid == 0) sl->n_g2 += 1;
+                    if (tid == 0) sl->stat[5] += 1;
                 } else {
                     draw();
                 }
@@ -664,19 +658,15 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
             }
             __syncthreads();
             if (tid == 0) {
-                if (GATED) sl->n_g1 += 1;
-                sl->t_end = now_ticks();
+                if (GATED) sl->stat[4] += 1;
+                mark_phase_end(sl, GATED ? 3 : 4);
                 sl->next = (int)next;
             }
             __syncthreads();
             i = uniform(sl->next);
             MOE_TT(c, 10);
-#ifdef MOE_TILE_TIMING
-            if (tid == 0) atomicMax(&c->dbg[24 + q], now_ticks() - c->t0);
-#endif
         }
     }
-    if (tid == 0) stage_stats_end(a, sl, t0);
 }
 
 // ---- the fused FFN (moe_problem_t::fuse_ffn; paper section 2.3: a tile traverses dispatch -> GEMM -> activation ->
@@ -729,8 +719,6 @@ static __device__ __attribute__((noinline)) void fused_stage(KArgsAddr args, u32
     Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const Tables tb = decode_tables(a, smem, n_rb, 0);
-    const u64 t0 = kernel_start_ticks(c);
-    if (tid == 0) stage_stats_begin(sl);
     *caller_local = 4;  // (see the call sites of tile_stage)
     while (true) {
         // the first list, from this XCD's on, that still has row blocks
@@ -740,7 +728,7 @@ static __device__ __attribute__((noinline)) void fused_stage(KArgsAddr args, u32
             if (tid < kTileQueues) {
                 const int qq = (home + tid) % kTileQueues;
                 const TileQueue t2 = tile_queue(a, n_rb, 0, qq);
-                has = ld_relaxed_agent(&c->tile_next[0][qq]) < (u32)(t2.r1 - t2.r0);
+                has = ld_relaxed_agent(&c->tile_next[0][qq].v) < (u32)(t2.r1 - t2.r0);
             }
             const u64 m = __ballot(has);
             if (tid == 0) sl->pick = m ? (home + __ffsll((long long)m) - 1) % kTileQueues : -1;
@@ -750,12 +738,12 @@ static __device__ __attribute__((noinline)) void fused_stage(KArgsAddr args, u32
         if (q < 0) break;
         const TileQueue tq = tile_queue(a, n_rb, 0, q);
         const int n = tq.r1 - tq.r0;
-        if (tid == 0) sl->next = (int)atomicAdd(&c->tile_next[0][q], 1u);
+        if (tid == 0) sl->next = (int)atomicAdd(&c->tile_next[0][q].v, 1u);
         __syncthreads();
         int i = uniform(sl->next);
         while (i < n) {
             u32 next = 0;
-            if (tid == 0) next = atomicAdd(&c->tile_next[0][q], 1u);  // consumed at the end of the block
+            if (tid == 0) next = atomicAdd(&c->tile_next[0][q].v, 1u);  // consumed at the end of the block
             TileInfo rb;
             rb.rb = tq.r0 + i;
             rb.e = tb.rb_expert[rb.rb];
@@ -766,16 +754,16 @@ static __device__ __attribute__((noinline)) void fused_stage(KArgsAddr args, u32
             fused_block<P>(a, rb, smem);
             __syncthreads();
             if (tid == 0) {
-                sl->n_g1 += a.tl.NT1;
-                sl->n_g2 += a.tl.NT2;
-                sl->t_end = now_ticks();
+                sl->stat[4] += a.tl.NT1;
+                sl->stat[5] += a.tl.NT2;
+                mark_phase_end(sl, 3);
+                mark_phase_end(sl, 4);
                 sl->next = (int)next;
             }
             __syncthreads();
             i = uniform(sl->next);
         }
     }
-    if (tid == 0) stage_stats_end(a, sl, t0);
 }
 
 // ---- combine
@@ -885,7 +873,7 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
 // per task: with shared rows as a run-time choice it took 28.7 instead of 25.9 us on 4096 x 8 rows of 2048, 91 instead of 80 us
 // on 16384 x 2 rows of 4096).
 template <typename ET, bool WAIT, bool STREAM = false, bool SHARE = true>
-__device__ __forceinline__ void combine_task(const KArgs &a, int task) {
+__device__ __forceinline__ void combine_task(const KArgs &a, int task, StageLds *sl = nullptr) {
     using V = Vec16<ET>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k = a.k, sys = a.fence_scope;
@@ -896,37 +884,53 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task) {
     if (a.slot_flag && a.flags) {
         const int per_tok = k * a.ncb;
         const int nflag = nt * per_tok;
-        bool ok = true;
+        auto flag_at = [&](int q) { return &a.flags[a.slot_flag[t_first * k + q / a.ncb] + q % a.ncb]; };
+        bool ok = true, waited_here = false;
+        const u32 *open_flag = nullptr;  // one that was not ready
         const u64 tw0 = WAIT ? now_ticks() : 0ull;
+        auto look = [&]() {
+            ok = true;
 #pragma unroll 4
-        for (int q = tid; q < nflag; q += kThreads) {
-            const int slot = t_first * k + q / a.ncb;
-            ok = ok && (ld_relaxed(&a.flags[a.slot_flag[slot] + q % a.ncb], sys) == a.epoch);
-        }
-        if (WAIT && !ok) {
             for (int q = tid; q < nflag; q += kThreads) {
-                const int slot = t_first * k + q / a.ncb;
-                const u32 *fp = &a.flags[a.slot_flag[slot] + q % a.ncb];
-                const u64 t0 = now_ticks();
-                int spins = 0;
-                while (ld_relaxed(fp, sys) != a.epoch) {
-                    __builtin_amdgcn_s_sleep(2);
-                    if ((++spins & 63) == 0) {
-                        if (ld_relaxed_agent(&a.ctrl->error) != 0) break;
-                        if (now_ticks() - t0 > a.wait_ticks) {
-                            set_error(a.ctrl, MOE_ERR_TIMEOUT);
-                            atomicAdd(&a.ctrl->stats[6], 1ull);
-                            break;
+                const u32 *fp = flag_at(q);
+                if (ld_relaxed(fp, sys) != a.epoch) ok = false, open_flag = fp;
+            }
+        };
+        look();
+        // Not ready: ONE lane of the wavefront polls one flag that is missing, then all look again.  (All lanes of all waiting
+        // workgroups polling is memory traffic that the tiles they wait for are slowed by.)
+        if (WAIT) {
+            int spins = 0;
+            bool give_up = false;
+            u64 m;
+            while ((m = __ballot(!ok)) != 0ull && !give_up) {
+                waited_here = true;
+                if (lane == __ffsll((long long)m) - 1) {
+                    while (ld_relaxed(open_flag, sys) != a.epoch) {
+                        __builtin_amdgcn_s_sleep(16);
+                        if ((++spins & 7) == 0) {
+                            if (ld_relaxed_agent(&a.ctrl->error.v) != 0) {
+                                give_up = true;
+                                break;
+                            }
+                            if (now_ticks() - tw0 > a.wait_ticks) {
+                                set_error(a.ctrl, MOE_ERR_TIMEOUT);
+                                atomicAdd(&sl->stat[6], 1ull);
+                                give_up = true;
+                                break;
+                            }
                         }
                     }
                 }
+                give_up = __any(give_up);
+                if (!give_up) look();
             }
         }
         fence_acquire(sys);
         if (!WAIT && !ok && a.status_dev) atomicExch(a.status_dev, (int)MOE_ERR_NOT_READY);
         // rows guarded by flags another lane polled; the time the workgroup waited is added once
-        const int waited = __syncthreads_or(WAIT && !ok);
-        if (WAIT && waited && tid == 0) atomicAdd(&a.ctrl->stats[14], now_ticks() - tw0);
+        const int waited = __syncthreads_or(WAIT && waited_here);
+        if (WAIT && waited && tid == 0) sl->stat[14] += now_ticks() - tw0;
     }
     const size_t rstride = (size_t)a.d * sizeof(ET);
     const int share = !SHARE ? 1 : nt == 1 ? 4 : nt == 2 ? 2 : 1;  // wavefronts per token
@@ -949,29 +953,16 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task) {
     }
 }
 
-// Combine tasks from their counter until none is left.  (Inlined into the
-// kernel: only the GEMM stages need a register allocation of their own.)
+// Combine tasks: workgroup i takes tasks i, i + grid size, ...  They need no counter: a workgroup comes here when every tile has
+// been drawn, so whatever a task waits for is being run by somebody, and all tasks become ready together with the last tiles.
+// (Inlined into the kernel: only the GEMM stages need a register allocation of their own.)
 template <typename ET>
 __device__ __forceinline__ void combine_stage(const KArgs &a, char *smem) {
-    const int tid = threadIdx.x;
-    Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
-    const u64 t0 = kernel_start_ticks(c);
-    __syncthreads();
-    if (tid == 0) sl->next = (int)atomicAdd(&c->comb_next, 1u);
-    __syncthreads();
-    int t = uniform(sl->next);
-    while (t < a.nCT) {
-        u32 next = 0;
-        if (tid == 0) next = atomicAdd(&c->comb_next, 1u);
-        combine_task<ET, true>(a, t);
+    for (int t = blockIdx.x; t < a.nCT; t += gridDim.x) {
+        combine_task<ET, true>(a, t, sl);
         __syncthreads();
-        if (tid == 0) {
-            mark_phase_end(c, 5, t0);
-            sl->next = (int)next;
-        }
-        __syncthreads();
-        t = uniform(sl->next);
+        if (threadIdx.x == 0) mark_phase_end(sl, 5);
     }
 }
 
@@ -996,7 +987,6 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
     Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const u32 lds = lds_offset_opaque(smem);
-    const u64 t0 = kernel_start_ticks(c);
     int q = home, hops = 0;  // the queue tickets come from; hops == kTileQueues: all queues are used up
     int ticket = -1;         // entry of queue q this workgroup is to run (may lie beyond the queue's size), -1 = none
     int g1_left = 1;
@@ -1009,16 +999,16 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
             bool has = false;
             if (g1_left && (kind == 0 || (kind == 1 && MIXED))) {
                 const TileQueue tq = tile_queue(a, n_rb, n_rbs, qq);
-                has = ld_relaxed_agent(&c->tile_next[kind][qq]) < (u32)(kind == 0 ? tq.n1b : tq.n1s);
+                has = ld_relaxed_agent(&c->tile_next[kind][qq].v) < (u32)(kind == 0 ? tq.n1b : tq.n1s);
             } else if (tid == 24) {
-                has = ld_relaxed_agent(&c->error) != 0u;
+                has = ld_relaxed_agent(&c->error.v) != 0u;
             }
             const u64 m = __ballot(has);
             if (tid == 0) {
                 // a ticket beyond its queue's size says the queue is used up: on to the next one
                 if (ticket >= 0 && ticket >= ready_queue_size(a, n_rb, n_rbs, q)) ticket = -1, q = (q + 1) % kTileQueues, ++hops;
                 while (ticket < 0 && hops < kTileQueues) {
-                    ticket = (int)atomicAdd(&c->rq_head[q], 1u);
+                    ticket = (int)atomicAdd(&c->rq_head[q].v, 1u);
                     if (ticket >= ready_queue_size(a, n_rb, n_rbs, q)) ticket = -1, q = (q + 1) % kTileQueues, ++hops;
                 }
                 u32 *slot = &a.rq_slots[(size_t)q * a.rq_cap + (ticket >= 0 ? ticket : 0)];
@@ -1029,16 +1019,16 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
                 } else if (v != 0u) {
                     st_relaxed(slot, 0u, 0);  // empty again for the next call
                     ticket = -1;
-                    atomicAdd(&c->stats[16], 1ull);
+                    sl->stat[16] += 1;
                     // out of order: a GEMM2 tile goes first although GEMM1 tiles are still in the lists
-                    if (!(v & kReadyCombine) && (m & 0xffffull)) atomicAdd(&c->stats[17], 1ull);
+                    if (!(v & kReadyCombine) && (m & 0xffffull)) sl->stat[17] += 1;
                     pick = 1, val = (int)v;
                 } else if (m & 0xffffull) {
                     const u32 lists = (u32)(m & 0xffffull);
                     const int kd = (lists & 0xffu) ? 0 : 1;
                     lq = (home + __ffs((int)((lists >> (8 * kd)) & 0xffu)) - 1) % kTileQueues;
                     const TileQueue tq = tile_queue(a, n_rb, n_rbs, lq);
-                    const u32 i = atomicAdd(&c->tile_next[kd][lq], 1u);
+                    const u32 i = atomicAdd(&c->tile_next[kd][lq].v, 1u);
                     pick = (i < (u32)(kd == 0 ? tq.n1b : tq.n1s)) ? 2 + kd : 4;
                     val = (int)i;
                 } else {
@@ -1050,11 +1040,11 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
                     if (idle_since == 0) idle_since = now;
                     if (now - idle_since > a.wait_ticks) {
                         set_error(c, MOE_ERR_TIMEOUT);
-                        atomicAdd(&c->stats[6], 1ull);
+                        sl->stat[6] += 1;
                         pick = -2;
                     }
                 } else if (idle_since != 0) {
-                    atomicAdd(&c->stats[14], now_ticks() - idle_since);
+                    sl->stat[14] += now_ticks() - idle_since;
                     idle_since = 0;
                 }
                 sl->pick = pick, sl->next = val, sl->ok = lq;
@@ -1077,11 +1067,11 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
             if (MIXED) tile_stage<PS, true, true>(kargs, lds, home, n_rb, n_rbs, lq, val, tq_next, caller_local);
         } else if ((u32)val & kReadyCombine) {
             u32 next = 0x7fffffffu;
-            if (tid == 0 && tq_next >= 0) next = atomicAdd(&c->rq_head[tq_next], 1u);
-            combine_task<ET, true>(a, (int)((u32)val & ~kReadyCombine));
+            if (tid == 0 && tq_next >= 0) next = atomicAdd(&c->rq_head[tq_next].v, 1u);
+            combine_task<ET, true>(a, (int)((u32)val & ~kReadyCombine), sl);
             __syncthreads();
             if (tid == 0) {
-                mark_phase_end(c, 5, t0);
+                mark_phase_end(sl, 5);
                 sl->next = (int)next;
             }
         } else {
@@ -1097,7 +1087,7 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
             if (t != 0x7fffffff) ticket = t;
         }
     }
-    if (tid == 0 && idle_since != 0) atomicAdd(&c->stats[14], now_ticks() - idle_since);
+    if (tid == 0 && idle_since != 0) sl->stat[14] += now_ticks() - idle_since;
 }
 
 }  // namespace moe

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kThreads) void k_plan(KArgs a) {
 template <typename ET>
 __global__ __launch_bounds__(kThreads) void k_perm(KArgs a) {
     extern __shared__ __align__(16) char smem[];
-    if (a.ctrl->error == 0) perm_task<ET>(a, blockIdx.x, smem, a.blk_base + (size_t)blockIdx.x * a.E, a.counts);
+    if (a.ctrl->error.v == 0) perm_task<ET>(a, blockIdx.x, smem, a.blk_base + (size_t)blockIdx.x * a.E, a.counts);
 }
 
 // standalone dispatch, short form (see block_hist_task): histograms go to blk_base, which nothing
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kThreads) void k_block_perm(KArgs a) {
 }
 
 __global__ __launch_bounds__(kThreads) void k_gather(KArgs a, size_t row_bytes) {
-    if (a.ctrl && a.ctrl->error != 0) return;  // (no control block: the form without a workspace)
+    if (a.ctrl && a.ctrl->error.v != 0) return;  // (no control block: the form without a workspace)
     // perm was not written if an expert is over its capacity (padded layout) or if the histogram does not account
     // for every slot (an expert id outside [0, E)): nothing is gathered then
     __shared__ int s_rows;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void k_dispatch_fused(KArgs a, size_t row
 }
 template <int STORE>
 __global__ __launch_bounds__(kThreads) void k_scatter(KArgs a, size_t row_bytes) {
-    if (a.ctrl && a.ctrl->error != 0) return;
+    if (a.ctrl && a.ctrl->error.v != 0) return;
     if (a.offsets[a.E] != a.N) return;  // an expert id outside [0, E): perm and inv_perm were not written
     scatter_task<STORE>(a, blockIdx.x, row_bytes);
 }
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(KArgs a, size_t row_bytes)
 // standalone dispatch leaves the control block clean for the next call
 __global__ __launch_bounds__(kThreads) void k_dispatch_finish(KArgs a) {
     // (one workgroup: the status must be read before the control block is cleared)
-    if (threadIdx.x == 0 && a.status_dev && a.ctrl->error != 0) *a.status_dev = -(int)a.ctrl->error;
+    if (threadIdx.x == 0 && a.status_dev && a.ctrl->error.v != 0) *a.status_dev = -(int)a.ctrl->error.v;
     __syncthreads();
     u32 *z = (u32 *)a.ctrl;
     const size_t n = a.zero_bytes / 4;
@@ -194,26 +194,25 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     Ctrl *c = a.ctrl;
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     *caller_local = 5;  // (see the call sites of tile_stage)
-    if (tid == 0) sl->next = (int)atomicAdd(&c->next_task, 1u);
+    if (tid == 0) sl->next = (int)atomicAdd(&c->next_task.v, 1u);
     if constexpr (V > 0) {
         gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    const u64 t0 = kernel_start_ticks(c);
     __syncthreads();
     int task = uniform(sl->next);
     auto draw_next = [&](int phase) __attribute__((always_inline)) {
         __syncthreads();
         if (tid == 0) {
-            if (phase >= 0) mark_phase_end(c, phase, t0);
-            sl->next = (int)atomicAdd(&c->next_task, 1u);
+            if (phase >= 0) mark_phase_end(sl, phase);
+            sl->next = (int)atomicAdd(&c->next_task.v, 1u);
         }
         __syncthreads();
         task = uniform(sl->next);
     };
     auto wait_for = [&](const u32 *p, u32 target) __attribute__((always_inline)) {
         __syncthreads();
-        if (tid == 0) sl->ok = !wait_ge(c, p, target, a.wait_ticks) ? 0 : ld_relaxed_agent(&c->error) == 0 ? 1 : 2;
+        if (tid == 0) sl->ok = !wait_ge(c, sl, p, target, a.wait_ticks) ? 0 : ld_relaxed_agent(&c->error.v) == 0 ? 1 : 2;
         __syncthreads();
         return uniform(sl->ok);  // 0: not reached, 1: reached, 2: reached, but an error is recorded
     };
@@ -232,21 +231,21 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     if constexpr (V > 0) {
         while (task < a.t_gate) {
             wgt_task(a, task, smem);
-            release_and_count(&c->wgt_done, false);
+            release_and_count(&c->wgt_done.v, false);
             draw_next(-1);
         }
     }
     bool seen_wgt = false;
     while (task < a.t_plan) {
         route_task<ET, V, true>(a, args, task - a.t_gate, smem, true, &sl->pick, [&]() __attribute__((always_inline)) {
-            if (!seen_wgt) seen_wgt = wait_for(&c->wgt_done, (u32)a.t_gate) != 0;  // the transposed gate weights are complete
+            if (!seen_wgt) seen_wgt = wait_for(&c->wgt_done.v, (u32)a.t_gate) != 0;  // the transposed gate weights are complete
             return seen_wgt;
         });
-        release_and_count(&c->route_done, false);
+        release_and_count(&c->route_done.v, false);
         draw_next(0);
     }
     int n_rb = 0, n_rbs = 0;
-    const int routed = wait_for(&c->route_done, (u32)a.nRT);
+    const int routed = wait_for(&c->route_done.v, (u32)a.nRT);
     bool bad = routed != 1;
     if (a.plan_all) {
         PlanAll p(a, smem);
@@ -270,21 +269,21 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
                 else
                     perm_block_lds(a, p, task - a.t_perm);
             }
-            release_and_count(plan ? &c->plan_done : &c->perm_done, false);
+            release_and_count(plan ? &c->plan_done.v : &c->perm_done.v, false);
             draw_next(plan ? 1 : 2);
         }
-        bad = wait_for(&c->plan_done, 1u) != 1 || bad;
+        bad = wait_for(&c->plan_done.v, 1u) != 1 || bad;
     } else {
         if (task == a.t_plan) {
             if (routed != 0) plan_task(a, smem);
-            release_and_count(&c->plan_done, true);
+            release_and_count(&c->plan_done.v, true);
             draw_next(1);
         }
-        bad = wait_for(&c->plan_done, 1u) != 1 || bad;
+        bad = wait_for(&c->plan_done.v, 1u) != 1 || bad;
         while (task < a.t_g1) {
             const int b = task - a.t_perm;
             if (!bad) perm_task<ET>(a, b, smem, a.blk_base + (size_t)b * a.E, a.counts);
-            release_and_count(&c->perm_done, true);
+            release_and_count(&c->perm_done.v, true);
             draw_next(2);
         }
         if (!bad) {
@@ -308,7 +307,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
             }
         }
     }
-    bad = wait_for(&c->perm_done, (u32)a.nPB) != 1 || bad;
+    bad = wait_for(&c->perm_done.v, (u32)a.nPB) != 1 || bad;
     if (tid == 0) {
         sl->n_rb = n_rb;
         sl->n_rbs = n_rbs;
@@ -317,12 +316,48 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     return bad ? 1 : 0;
 }
 
+// The statistics from the workgroups' reports: sums, and for the phases the time from the earliest start to the latest end.
+__device__ __forceinline__ void sum_reports(const KArgs &a, char *smem, int error) {
+    const int tid = threadIdx.x, w = tid & (kWgStats - 1), part = tid / kWgStats;
+    constexpr int PARTS = kThreads / kWgStats, U = 32;  // (32 loads in flight per thread: the reports of 256 workgroups at once)
+    const int n = (int)gridDim.x;
+    const bool phase = w >= 8 && w <= 13, start = w == MOE_NUM_STATS;
+    u64 v = start ? ~0ull : 0ull;
+    for (int b = part; b < n; b += PARTS * U) {
+        u64 r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = a.wg_stats[(size_t)min(b + u * PARTS, n - 1) * kWgStats + w];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b + u * PARTS < n) v = phase ? max(v, r[u]) : start ? min(v, r[u]) : v + r[u];
+    }
+    u64 *part_v = (u64 *)smem;  // [PARTS][kWgStats]
+    part_v[tid] = v;
+    __syncthreads();
+    if (tid <= MOE_NUM_STATS) {
+        for (int i = 1; i < PARTS; ++i) {
+            const u64 r = part_v[i * kWgStats + w];
+            v = phase ? max(v, r) : start ? min(v, r) : v + r;
+        }
+        part_v[tid] = v;
+    }
+    __syncthreads();
+    if (tid < MOE_NUM_STATS) {
+        const u64 t0 = part_v[MOE_NUM_STATS];
+        if (tid == 7) v = (u64)(long long)(-error);
+        if (phase) v = v > t0 ? (v - t0) * 10ull : 0ull;  // 100 MHz ticks -> ns
+        if (tid == 14) v *= 10ull;
+        if (tid == 15) v = (u64)n;
+        a.stats[tid] = v;
+    }
+}
+
 // The whole layer in one persistent kernel.  Every workgroup walks through three
 // stages, drawing work from counters in the control block:
 //   1. front tasks, one counter, in this order: [gate-weight transposition | gate tasks | plan | permutation blocks];
 //   2. GEMM tiles, four kinds in turn (GEMM1 then GEMM2, big then small row blocks), each kind
 //      from one list per XCD (see TileQueue): its own XCD's list first, then the others;
-//   3. combine tasks, one counter.
+//   3. combine tasks, dealt out by workgroup number.
 // No wait can deadlock, whatever the grid size: a task only waits for tasks of an
 // earlier kind (permutation <- plan <- gate <- transposition, GEMM1 <- permutation, GEMM2 <- GEMM1,
 // combine <- GEMM2), a workgroup only moves on to a later kind when every entry of the
@@ -344,10 +379,10 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
     Ctrl *c = a.ctrl;
     const int tid = threadIdx.x;
     const KArgsAddr kargs = kernel_args_address();
-    if (tid == 0) {
-        atomicCAS(&c->t0, 0ull, now_ticks());
-        atomicAdd(&c->stats[15], 1ull);
-    }
+    StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
+    if (tid < MOE_NUM_STATS) sl->stat[tid] = 0ull;
+    if (tid == 0) sl->t_start = now_ticks();
+    __syncthreads();
 
     // The stage functions get the address of a local of this kernel.  That keeps the compiler from
     // marking the calls as tail calls, which is what lets it drop the saving and restoring of
@@ -372,8 +407,7 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
         front = front_stage<ET, 0>(kargs, lds, &stage_mark);
     }
     const bool bad = uniform(front) != 0;
-    const StageLds *sl0 = (const StageLds *)(smem + a.sched_lds_off);
-    const int n_rb = uniform(sl0->n_rb), n_rbs = uniform(sl0->n_rbs);
+    const int n_rb = uniform(sl->n_rb), n_rbs = uniform(sl->n_rbs);
 
     if (!bad) {
         // ---- stage 2: GEMM tiles, one call per kind, this XCD's lists first
@@ -395,34 +429,25 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
             MOE_TT(c, 22);
             if (MIXED && n_rbs > 0) tile_stage<PS, false, true>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 23);
-#ifdef MOE_TILE_TIMING
-            if (tid == 0) {
-                const u64 t = now_ticks() - c->t0;
-                atomicAdd(&c->dbg[14], t);
-                atomicMax(&c->dbg[15], t);
-            }
-#endif
             // ---- stage 3: combine
             combine_stage<ET>(a, smem);
         }
     }
-    // last workgroup out copies the statistics and clears the control block
-    sync_stores();  // (what the last workgroup reads of the others' work are atomics)
+    // Last workgroup out sums up the workgroups' reports and clears the control block.  (What it reads of the others' work are
+    // atomics and the reports, which are written through.)
+    __syncthreads();
+    if (tid <= MOE_NUM_STATS) store_through(&a.wg_stats[(size_t)blockIdx.x * kWgStats + tid], tid < MOE_NUM_STATS ? sl->stat[tid] : sl->t_start);
+    sync_stores();
     if (tid == 0) {
-        const u32 old = atomicAdd(&c->exit_count, 1u);
-        s_last = (old == gridDim.x - 1) ? 1 : 0;
+        const u32 g = blockIdx.x % kExitGroups, in_group = (gridDim.x - g + kExitGroups - 1) / kExitGroups;
+        const u32 groups = min(gridDim.x, (u32)kExitGroups);
+        s_last = 0;
+        if (atomicAdd(&c->exit_group[g].v, 1u) == in_group - 1) s_last = atomicAdd(&c->exit_count.v, 1u) == groups - 1 ? 1 : 0;
         if (s_last) fence_acquire(0);
     }
     __syncthreads();
     if (s_last) {
-        if (a.stats) {
-            if (tid < MOE_NUM_STATS) {
-                u64 v = c->stats[tid];
-                if (tid == 7) v = (u64)(long long)(-(int)c->error);
-                if (tid >= 8 && tid <= 14) v *= 10ull;  // 100 MHz ticks -> ns
-                a.stats[tid] = v;
-            }
-        }
+        if (a.stats) sum_reports(a, smem, (int)c->error.v);
         __syncthreads();
 #ifdef MOE_TILE_TIMING
         // development build: the per-part tick sums follow the statistics (the caller's array has room for them)
@@ -439,6 +464,7 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
 // workgroup counts every slot, which hides behind the row movement up to about this much.
 constexpr long long kFusedDispatchWork = 64ll << 20;
 constexpr size_t kLdsBudget = 160 * 1024 - 256;  // dynamic LDS a kernel may ask for: the CU's 160 KB less the kernels' few static words
+constexpr int kGroupStride = 32;  // words: see KArgs::group_stride
 constexpr int kMaxDevices = 16;  // devices the host-side launch memo covers (others ask the runtime on every call)
 
 static inline size_t align_up(size_t v, size_t al) { return (v + al - 1) / al * al; }
@@ -463,7 +489,7 @@ struct Plan {
     size_t o_rq_slots, init_zero_bytes;  // the ready queues empty themselves: zeroed by moe_workspace_init only
     int rq_cap;
     size_t o_blk_base, o_seg_begin, o_flag_base, o_dest_flag_begin, o_dest_group_begin, o_rb_base, o_rb_expert, o_rbs_base, o_rbs_expert, o_h, total;
-    size_t o_wgt;
+    size_t o_wgt, o_wg_stats;
     int gate_tok;  // tokens per gate task
 };
 
@@ -564,7 +590,8 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     // layout depends on the shape of the problem only and these may change from call to call.
     // Fence groups: one counter per group, at most one group per flag (group_size 1) plus R.
     const size_t max_flags = ((size_t)(pl->N + tm - 1) / tm + (size_t)p->E * p->R) * pl->ncb;
-    pl->o_group_counter = take((max_flags + p->R) * 4);
+    const size_t spread = (size_t)p->R * kGroupStride;  // (a counter per destination has a cache line to itself)
+    pl->o_group_counter = take((max_flags + p->R > spread ? max_flags + p->R : spread) * 4);
     // One ready queue per XCD, each able to hold every GEMM2 tile and every combine task (at most
     // one per token).
     pl->rq_cap = (pl->tl.maxRB + p->E) * pl->tl.NT2 + p->T;
@@ -575,6 +602,7 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->o_flag_base = take((size_t)p->E * p->R * 4);
     pl->o_dest_flag_begin = take((size_t)(p->R + 1) * 4);
     pl->o_dest_group_begin = take((size_t)(p->R + 1) * 4);
+    pl->o_wg_stats = take((size_t)kMaxWorkgroups * kWgStats * 8);
     pl->o_rb_base = take((size_t)(p->E + 1) * 4);
     pl->o_rb_expert = take((size_t)pl->maxRB_layout * 4);
     pl->o_rbs_base = take((size_t)(p->E + 1) * 4);
@@ -595,6 +623,7 @@ static void fill_args(const Plan &pl, void *workspace, KArgs *a) {
     a->dtype = p.dtype; a->tile_m = pl.tile_m; a->tile_n = pl.tile_n;
     a->signal_mode = p.signal_mode; a->fence_scope = p.fence_scope; a->epoch = p.epoch;
     a->group_size = p.group_size;
+    a->group_stride = p.group_size > 0 ? 1 : kGroupStride;
     a->wait_ticks = p.wait_ticks ? (u64)p.wait_ticks : kWaitTicks;
     a->scheduler = p.scheduler;
     a->N = pl.N; a->NP = pl.NP; a->capacity = p.capacity; a->per_dest = pl.per_dest; a->ncb = pl.ncb;
@@ -615,6 +644,7 @@ static void fill_args(const Plan &pl, void *workspace, KArgs *a) {
         a->seg_cnt = (int32_t *)(ws + pl.o_seg_cnt);
         a->group_counter = (u32 *)(ws + pl.o_group_counter);
         a->h_ready = (u32 *)(ws + pl.o_h_ready);
+        a->wg_stats = (u64 *)(ws + pl.o_wg_stats);
         if (p.scheduler == MOE_SCHED_READY_QUEUE) {
             a->dest_done = (u32 *)(ws + pl.o_dest_done);
             a->rq_slots = (u32 *)(ws + pl.o_rq_slots);
@@ -758,6 +788,7 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
     if (per_cu > 2) per_cu = 2;
     long long grid = (long long)cus * per_cu;
     if (grid > a.t_end) grid = a.t_end;
+    if (grid > kMaxWorkgroups) grid = kMaxWorkgroups;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), smem, st, a);
     return hip_ok(hipGetLastError());
 }
