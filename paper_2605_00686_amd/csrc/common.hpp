@@ -82,7 +82,8 @@ struct KArgs {
     u64 wait_ticks;  // bound of every in-kernel wait, in ticks of the 100 MHz wall clock
     int N, per_dest, ncb;  // slots, tokens per destination, column blocks per row
     int nPB, nRT, nCT;     // permutation blocks, gate tasks, combine tasks
-    int comb_tokens;       // tokens per combine task
+    int comb_tokens;       // tokens per combine task, at most; the tokens are cut into tasks span by span:
+    int comb_span, comb_per_span;  // tokens of a span and tasks that take it (see combine_task)
     int disp_tokens;       // tokens per workgroup of the standalone dispatch's row movement
     int fused;             // moe_problem_t::fuse_ffn: a workgroup takes a row block through both GEMMs, h in LDS
     int fused_h_off;       // ... LDS offset of that h buffer [row block rows][f]

@@ -2,6 +2,8 @@
 // flags (paper sections 2.3 and 4.1), and the weighted combine (section 2.1
 // step 4).
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 #include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
@@ -183,7 +185,7 @@ constexpr u32 kReadyCombine = 0x80000000u;
 __device__ __forceinline__ int ready_queue_size(const KArgs &a, int n_rb, int n_rbs, int q) {
     const TileQueue tq = tile_queue(a, n_rb, n_rbs, q);
     const int dests = a.R > q ? (a.R - q + kTileQueues - 1) / kTileQueues : 0;
-    return tq.n2b + tq.n2s + dests * (a.per_dest / a.comb_tokens);
+    return tq.n2b + tq.n2s + dests * a.comb_per_span;
 }
 // the share that row block rb of n (of one kind) lies in
 __device__ __forceinline__ int ready_queue_of_block(int n, int rb) {
@@ -210,7 +212,7 @@ __device__ __forceinline__ void ready_flags_stored(const KArgs &a, int dst, int 
     old = (u32)__builtin_amdgcn_readfirstlane((int)old);
     const u32 all = (u32)(a.dest_flag_begin[dst + 1] - a.dest_flag_begin[dst]);
     if (old + (u32)n == all) {
-        const int per = a.per_dest / a.comb_tokens;
+        const int per = a.comb_per_span;
         ready_push(a, dst % kTileQueues, kReadyCombine | (u32)(dst * per), per, lane);
     }
 }
@@ -861,40 +863,139 @@ __device__ __forceinline__ void combine_token(const char *rows, const float *wt,
     }
 }
 
+// The rows of a task of the megakernel, k <= KB.  A unit of work is U pieces per lane of one token, all k rows of them (KB * U = 8
+// loads); a wavefront keeps DEPTH units in flight: while it adds up one, the loads of the next three are on their way.  One
+// wavefront per token, or several that share a token's row when the task has fewer than four tokens.  wl: weights, in LDS.
+template <typename ET, int KB, int U>
+__device__ __forceinline__ void combine_chunk(const KArgs &a, int t_first, int nt, const float *wl) {
+    using V = Vec16<ET>;
+    constexpr int DEPTH = 4;
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), k = a.k;
+    const int pieces = a.d * (int)sizeof(ET) / 16;
+    const size_t rstride = (size_t)a.d * sizeof(ET);
+    const int share = nt == 1 ? 4 : nt == 2 ? 2 : 1, step = 4 / share;  // wavefronts per token
+    const int per_wave = (pieces + share - 1) / share, c_begin = (wave % share) * per_wave, c_end = min(c_begin + per_wave, pieces);
+    const int first = wave / share;
+    const int blocks = (max(c_end - c_begin, 0) + 64 * U - 1) / (64 * U), total = first < nt ? (nt - first + step - 1) / step * blocks : 0;
+    uint4 v[DEPTH][U][KB];
+    int lt = first, lb = 0, ct = first, cb = 0;  // token and block of the next unit to load, to add up
+    auto load = [&](uint4(&x)[U][KB]) __attribute__((always_inline)) {
+        const char *rows = (const char *)a.staging + (size_t)(t_first + lt) * k * rstride;
+#pragma unroll
+        for (int jj = 0; jj < KB; ++jj)
+            if (jj < k) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int c = min(c_begin + (lb * U + u) * 64 + lane, c_end - 1);
+                    x[u][jj] = *(const uint4 *)(rows + (size_t)jj * rstride + (u32)c * 16u);
+                }
+            }
+        if (++lb == blocks) lb = 0, lt += step;
+    };
+    auto add_up = [&](const uint4(&x)[U][KB]) __attribute__((always_inline)) {
+        float acc[U][V::N];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < V::N; ++i) acc[u][i] = 0.f;
+#pragma unroll
+        for (int jj = 0; jj < KB; ++jj)
+            if (jj < k) {
+                const float wj = wl[ct * k + jj];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float f[V::N];
+                    V::unpack(x[u][jj], f);
+#pragma unroll
+                    for (int i = 0; i < V::N; ++i) acc[u][i] = fmaf(wj, f[i], acc[u][i]);
+                }
+            }
+        char *orow = (char *)a.out + (size_t)(t_first + ct) * rstride;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c_begin + (cb * U + u) * 64 + lane;
+            if (c < c_end) V::store(orow + (u32)c * 16u, acc[u]);
+        }
+        if (++cb == blocks) cb = 0, ct += step;
+    };
+    const int groups = total / DEPTH;
+    if (groups > 0) {  // (no load is conditional here: the number of loads in flight is then known at every wait)
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) load(v[s]);
+        for (int g = 1; g < groups; ++g)
+#pragma unroll
+            for (int s = 0; s < DEPTH; ++s) {
+                add_up(v[s]);
+                load(v[s]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) add_up(v[s]);
+    }
+    const int rest = total - groups * DEPTH;
+#pragma unroll
+    for (int s = 0; s + 1 < DEPTH; ++s)
+        if (s < rest) load(v[s]);
+#pragma unroll
+    for (int s = 0; s + 1 < DEPTH; ++s)
+        if (s < rest) add_up(v[s]);
+}
+
 // out[t] = sum_j w[t,j] * staging[t*k+j] for the tokens of one task.  WAIT:
 // spin (bounded) until the flags covering the task's rows carry this call's
 // epoch; otherwise check once and report.  Flags are read with relaxed atomic
 // loads (a first pass that keeps many loads in flight, then a spin on whatever
 // was not ready) followed by one acquire fence at the requested scope.  Then
-// one wavefront per token, or several that share a token's row when the task has fewer than four tokens: a task is a chain
-// of trips to memory (flag numbers, flags, rows), so what counts is that all four wavefronts load, and that a workgroup
-// has few tasks.  Inside the megakernel (WAIT), where a CU holds one workgroup, a lane keeps 16 loads in flight; alone, where
-// it holds several, 8.  SHARE = false: a wavefront per token whatever the task has (the standalone launch of four tokens or more
+// the rows: inside the megakernel (WAIT), where a workgroup has one task and a CU one workgroup, see combine_chunk (k > 8: as alone); alone,
+// one wavefront per token, or several that share a token's row when the task has fewer than four tokens, 8 loads in flight per
+// lane, a CU holding several workgroups.  SHARE = false: a wavefront per token whatever the task has (the standalone launch of four tokens or more
 // per task: with shared rows as a run-time choice it took 28.7 instead of 25.9 us on 4096 x 8 rows of 2048, 91 instead of 80 us
 // on 16384 x 2 rows of 4096).
 template <typename ET, bool WAIT, bool STREAM = false, bool SHARE = true>
-__device__ __forceinline__ void combine_task(const KArgs &a, int task, StageLds *sl = nullptr) {
+__device__ __forceinline__ void combine_task(const KArgs &a, int task, char *smem = nullptr) {
+    StageLds *sl = (StageLds *)(smem + a.sched_lds_off);  // (WAIT)
     using V = Vec16<ET>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k = a.k, sys = a.fence_scope;
     const char *staging = (const char *)a.staging;
     const int pieces = a.d * (int)sizeof(ET) / 16;
-    const int t_first = task * a.comb_tokens;
-    const int nt = min(a.comb_tokens, a.T - t_first);
+    // the tokens of a task lie in one span: a destination under the ready-queue scheduler, else all of them
+    const int span = task / a.comb_per_span, t_first = span * a.comb_span + (task - span * a.comb_per_span) * a.comb_tokens;
+    const int nt = min(a.comb_tokens, (span + 1) * a.comb_span - t_first);
+    float *wl = (float *)smem;  // WAIT: the task's weights (the GEMM region is free)
+    if (WAIT && k <= 8)
+        for (int i = tid; i < nt * k; i += kThreads) wl[i] = a.w[(size_t)t_first * k + i];
     if (a.slot_flag && a.flags) {
-        const int per_tok = k * a.ncb;
-        const int nflag = nt * per_tok;
-        auto flag_at = [&](int q) { return &a.flags[a.slot_flag[t_first * k + q / a.ncb] + q % a.ncb]; };
+        const int nflag = nt * k * a.ncb;
         bool ok = true, waited_here = false;
         const u32 *open_flag = nullptr;  // one that was not ready
         const u64 tw0 = WAIT ? now_ticks() : 0ull;
-        auto look = [&]() {
+        const int slot_step = kThreads / a.ncb, col_step = kThreads - slot_step * a.ncb;
+        auto look_by = [&](auto per_thread) {  // all flags of the task, so many per thread in flight
             ok = true;
-#pragma unroll 4
-            for (int q = tid; q < nflag; q += kThreads) {
-                const u32 *fp = flag_at(q);
-                if (ld_relaxed(fp, sys) != a.epoch) ok = false, open_flag = fp;
+            int slot = tid / a.ncb, col = tid - slot * a.ncb;
+            constexpr int U = decltype(per_thread)::value;
+            for (int q = tid; q < nflag; q += U * kThreads) {
+                const u32 *fp[U];
+                u32 v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    fp[u] = &a.flags[a.slot_flag[t_first * k + min(slot, nt * k - 1)] + col];
+                    slot += slot_step, col += col_step;
+                    if (col >= a.ncb) col -= a.ncb, ++slot;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = ld_relaxed(fp[u], sys);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (q + u * kThreads < nflag && v[u] != a.epoch) ok = false, open_flag = fp[u];
             }
+        };
+        auto look = [&]() {
+            if (nflag <= kThreads)
+                look_by(std::integral_constant<int, 1>());
+            else
+                look_by(std::integral_constant<int, 8>());
         };
         look();
         // Not ready: ONE lane of the wavefront polls one flag that is missing, then all look again.  (All lanes of all waiting
@@ -932,6 +1033,19 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task, StageLds 
         const int waited = __syncthreads_or(WAIT && waited_here);
         if (WAIT && waited && tid == 0) sl->stat[14] += now_ticks() - tw0;
     }
+    if constexpr (WAIT) {
+        if (k <= 8) {
+            if (k == 1)
+                combine_chunk<ET, 1, 8>(a, t_first, nt, wl);
+            else if (k == 2)
+                combine_chunk<ET, 2, 4>(a, t_first, nt, wl);
+            else if (k <= 4)
+                combine_chunk<ET, 4, 2>(a, t_first, nt, wl);
+            else
+                combine_chunk<ET, 8, 1>(a, t_first, nt, wl);
+            return;
+        }
+    }
     const size_t rstride = (size_t)a.d * sizeof(ET);
     const int share = !SHARE ? 1 : nt == 1 ? 4 : nt == 2 ? 2 : 1;  // wavefronts per token
     const int per_wave = (pieces + share - 1) / share, c_begin = (wave % share) * per_wave, c_end = min(c_begin + per_wave, pieces);
@@ -940,8 +1054,7 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task, StageLds 
         const char *rows = staging + (size_t)t * k * rstride;
         char *orow = (char *)a.out + (size_t)t * rstride;
         const float *wt = a.w + (size_t)t * k;
-        // IF 16-byte loads in flight per lane whatever k is
-        constexpr int IF = WAIT ? 16 : 8;
+        constexpr int IF = 8;  // 16-byte loads in flight per lane whatever k is
         if (k == 1)
             combine_token<ET, IF, IF, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
         else if (k <= 2)
@@ -960,7 +1073,7 @@ template <typename ET>
 __device__ __forceinline__ void combine_stage(const KArgs &a, char *smem) {
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     for (int t = blockIdx.x; t < a.nCT; t += gridDim.x) {
-        combine_task<ET, true>(a, t, sl);
+        combine_task<ET, true>(a, t, smem);
         __syncthreads();
         if (threadIdx.x == 0) mark_phase_end(sl, 5);
     }
@@ -1068,7 +1181,7 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
         } else if ((u32)val & kReadyCombine) {
             u32 next = 0x7fffffffu;
             if (tid == 0 && tq_next >= 0) next = atomicAdd(&c->rq_head[tq_next].v, 1u);
-            combine_task<ET, true>(a, (int)((u32)val & ~kReadyCombine), sl);
+            combine_task<ET, true>(a, (int)((u32)val & ~kReadyCombine), smem);
             __syncthreads();
             if (tid == 0) {
                 mark_phase_end(sl, 5);

@@ -464,6 +464,8 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
 // workgroup counts every slot, which hides behind the row movement up to about this much.
 constexpr long long kFusedDispatchWork = 64ll << 20;
 constexpr size_t kLdsBudget = 160 * 1024 - 256;  // dynamic LDS a kernel may ask for: the CU's 160 KB less the kernels' few static words
+constexpr int kCombineTasks = 256;  // of the megakernel, one per CU of the chip ...
+constexpr int kCombineMaxTokens = 256;  // ... with at most so many tokens (their weights are kept in LDS)
 constexpr int kGroupStride = 32;  // words: see KArgs::group_stride
 constexpr int kMaxDevices = 16;  // devices the host-side launch memo covers (others ask the runtime on every call)
 
@@ -480,7 +482,7 @@ enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S = 3, TK_FS = 4, TK_FM = 5 };
 
 struct Plan {
     moe_problem_t p;
-    int tile_m, tile_n, N, NP, per_dest, ncb, nPB, nRT, nCT, comb_tokens, maxRB_layout;
+    int tile_m, tile_n, N, NP, per_dest, ncb, nPB, nRT, nCT, comb_tokens, comb_span, comb_per_span, maxRB_layout;
     int kind;
     Tiling tl;
     // workspace byte offsets
@@ -525,14 +527,23 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->nPB = (p->T + kPermBlock - 1) / kPermBlock;
     pl->gate_tok = p->dtype == MOE_DT_BF16 ? gate_tokens(p->T) : kRouteTokens;
     pl->nRT = (p->T + pl->gate_tok - 1) / pl->gate_tok;
-    // combine tasks of the megakernel: a workgroup has few of them, down to one token for all four wavefronts.  Whole layer, 1 / 2
-    // / 4 tokens per task, us: 513 tokens on 16 experts of 1024 x 256 99 / 94 / 91, 900 on 64 of 2048 x 256 224 / 212 / 214.
-    // (The standalone combine has a rule of its own: standalone_combine_tokens.)
-    pl->comb_tokens = p->T >= 16384 ? 16 : p->T >= 8192 ? 8 : p->T > 512 ? 4 : p->T > 256 ? 2 : 1;
-    // the ready-queue scheduler enqueues combine tasks per destination: none may span two
-    if (p->scheduler == MOE_SCHED_READY_QUEUE)
-        while (pl->per_dest % pl->comb_tokens != 0) pl->comb_tokens >>= 1;
-    pl->nCT = (p->T + pl->comb_tokens - 1) / pl->comb_tokens;
+    // Combine tasks of the megakernel: one per workgroup.  A task is a chain of trips to memory (flag numbers, flags, weights, rows),
+    // and all become ready together with the last tiles.  (The standalone combine has a rule of its own: standalone_combine_tokens.)
+    pl->comb_tokens = (p->T + kCombineTasks - 1) / kCombineTasks;
+    if (pl->comb_tokens > kCombineMaxTokens) pl->comb_tokens = kCombineMaxTokens;
+    // The ready-queue scheduler enqueues combine tasks per destination: none may span two.
+    pl->comb_span = p->scheduler == MOE_SCHED_READY_QUEUE ? pl->per_dest : p->T;
+    pl->comb_per_span = (pl->comb_span + pl->comb_tokens - 1) / pl->comb_tokens;
+    if (p->scheduler == MOE_SCHED_READY_QUEUE) {  // equal shares of a destination where up to twice as many tasks make them equal
+        const int want = pl->comb_per_span;
+        for (int n = want; n <= 2 * want && n <= pl->per_dest; ++n)
+            if (pl->per_dest % n == 0) {
+                pl->comb_per_span = n;
+                pl->comb_tokens = pl->per_dest / n;
+                break;
+            }
+    }
+    pl->nCT = p->T / pl->comb_span * pl->comb_per_span;
     // tile shape: the smallest row block that holds an average expert, never
     // smaller than the publish tile (a publish tile must not span two compute tiles)
     const int avg = pl->N / p->E;
@@ -628,6 +639,7 @@ static void fill_args(const Plan &pl, void *workspace, KArgs *a) {
     a->scheduler = p.scheduler;
     a->N = pl.N; a->NP = pl.NP; a->capacity = p.capacity; a->per_dest = pl.per_dest; a->ncb = pl.ncb;
     a->nPB = pl.nPB; a->nRT = pl.nRT; a->nCT = pl.nCT; a->comb_tokens = pl.comb_tokens;
+    a->comb_span = pl.comb_span; a->comb_per_span = pl.comb_per_span;
     a->seg_from_blocks = (pl.per_dest % kPermBlock == 0) ? 1 : 0;
     a->disp_tokens = scatter_tokens(p.T);
     a->tl = pl.tl;
@@ -1092,6 +1104,7 @@ int moe_combine(const moe_problem_t *p, const void *staging, const uint32_t *fla
     const bool past_cache = (size_t)pl.N * row_bytes > ((size_t)192 << 20);
     a.comb_tokens = standalone_combine_tokens(p->T, row_bytes);
     a.nCT = (p->T + a.comb_tokens - 1) / a.comb_tokens;
+    a.comb_span = p->T; a.comb_per_span = a.nCT;
     auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(a.nCT), dim3(kThreads), 0, st, a); };
     auto pick = [&](auto et) {
         using ET = decltype(et);
