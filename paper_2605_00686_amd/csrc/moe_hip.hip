@@ -24,7 +24,8 @@ template <typename ET, int V>
 __global__ __launch_bounds__(kThreads, 1) void k_route(KArgs a, int do_hist) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int s_slot;
-    if constexpr (V > 0) gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
+    if constexpr (V > 0) gate_warm_l2(a, lds_offset(smem + (V == kGateDirect ? kMaxExperts * 4 : GateCfg<V == kGateDirect ? 1 : V>::O_EXACT)), blockIdx.x, gridDim.x);
+    if constexpr (V == kGateDirect) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (its rows take the place the loads go to)
     route_task<ET, V, false>(a, kernel_args_address(), blockIdx.x, smem, do_hist != 0, &s_slot, [] { return false; });
 }
 
@@ -196,7 +197,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     *caller_local = 5;  // (see the call sites of tile_stage)
     if (tid == 0) sl->next = (int)atomicAdd(&c->next_task.v, 1u);
     if constexpr (V > 0) {
-        gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
+        gate_warm_l2(a, lds_offset(smem + kMaxExperts * 4), blockIdx.x, gridDim.x);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
@@ -394,7 +395,8 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
     // ---- stage 1: gate, plan, permutation
     int front = 0;
     if constexpr (sizeof(ET) == 2) {  // (one function per gate: each has registers of its own)
-        switch (a.Wg ? gate_variant(a.E, a.d) : 0) {
+        switch (a.gate_direct ? kGateDirect : a.Wg ? gate_variant(a.E, a.d) : 0) {
+            case kGateDirect: front = front_stage<ET, kGateDirect>(kargs, lds, &stage_mark); break;
             case 1: front = front_stage<ET, 1>(kargs, lds, &stage_mark); break;
             case 2: front = front_stage<ET, 2>(kargs, lds, &stage_mark); break;
             case 3: front = front_stage<ET, 3>(kargs, lds, &stage_mark); break;
@@ -476,6 +478,8 @@ static int elem_size(int dtype) { return dtype == MOE_DT_F32 ? 4 : 2; }
 // The gate is split over its reduction when there are at most kGateSplitBlocks blocks of 16 tokens,
 // into at most kGateSplitTasks tasks in all.
 constexpr int kGateSplitBlocks = 64, kGateSplitTasks = 256, kGateSplitMax = 16;
+constexpr int kGateParts = 128;  // blocks whose finished parts are counted, of either split
+static_assert(kGateParts >= kGateSplitBlocks && kGateParts >= kDirectSplitTokens, "one counter per block");
 
 // LM: 256-row tiles plus a 128-row tile for short tails; FS / FM: row blocks of the fused FFN (32 / 64 rows)
 enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S = 3, TK_FS = 4, TK_FM = 5 };
@@ -594,7 +598,7 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->o_seg_cnt = take((size_t)p->E * p->R * 4);
     pl->o_h_ready = take((size_t)pl->maxRB_layout * 4);
     pl->o_dest_done = take((size_t)p->R * 4);
-    pl->o_gate_parts = take((size_t)kGateSplitBlocks * 4);
+    pl->o_gate_parts = take((size_t)kGateParts * 4);
     pl->zero_bytes = o;
     // What follows is zero between calls because its users leave it so (moe_workspace_init zeroes it
     // once).  Sizes are the largest any signal mode, group size or scheduler needs, so that the
@@ -620,7 +624,9 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->o_rbs_expert = take((size_t)p->E * 4);
     pl->o_h = take((size_t)pl->NP * p->f * elem_size(p->dtype));
     // partial logits of a gate split over its reduction (fp32 problems of few tokens): at most kGateSplitTasks tasks
-    pl->o_gate_partial = take(p->dtype == MOE_DT_F32 ? (size_t)kGateSplitTasks * kRouteTokens * p->E * 8 : 0);
+    // (and the logits of one split by experts: bf16 problems of few tokens)
+    pl->o_gate_partial = take(p->dtype == MOE_DT_F32 ? (size_t)kGateSplitTasks * kRouteTokens * p->E * 8
+                                                     : (size_t)(p->T < kDirectSplitTokens ? p->T : kDirectSplitTokens) * p->E * 8);
     // transposed gate weights (bf16 problems; unused when the routing is an input)
     pl->o_wgt = take(p->dtype == MOE_DT_BF16 ? (size_t)p->E * p->d * 2 : 0);
     pl->total = o;
@@ -692,10 +698,16 @@ static int standalone_combine_tokens(int T, size_t row_bytes) {
 // experts' products ask for aligned rows) takes exact logits of all experts, whose ordinary loads accept any address.  So do
 // gate weights of 4 GB and more and rows of x longer than 2^26: the screen addresses the weights (and a piece past their end)
 // with 32 bits, the 16 rows of a task with 31.
-static void set_gate(KArgs *a, const void *x, const void *Wg, const float *bias) {
+static void set_gate(KArgs *a, const void *x, const void *Wg, const float *bias, bool alone) {
     a->x = x; a->Wg = Wg; a->bias = bias;
     a->gate_screens = ((uintptr_t)x & 15) == 0 && a->d <= 1 << 26 && (long long)a->d * a->E * 2 <= 0xffffff00ll;
     a->gate_rows_aligned = (a->E & 7) == 0 && ((uintptr_t)Wg & 15) == 0;
+    // few tokens: see gate_direct.hpp; its tasks have other sizes than the screen's
+    if (Wg && a->dtype == MOE_DT_BF16 && gate_is_direct(a->T, a->E, a->d, alone)) {
+        a->gate_direct = 1;
+        a->gate_tok = direct_tokens(a->T);
+        a->nRT = (a->T + a->gate_tok - 1) / a->gate_tok;
+    }
 }
 
 static size_t plan_smem(const Plan &pl) { return plan_smem_bytes(pl.p.E, pl.p.R, pl.nPB); }
@@ -878,17 +890,18 @@ int moe_route(const moe_problem_t *p, const void *x, const void *Wg, const float
     if (!x || !Wg || !topk_idx || !topk_w) return MOE_ERR_INVALID_ARG;
     KArgs a;
     fill_args(pl, nullptr, &a);
-    set_gate(&a, x, Wg, gate_bias);
+    set_gate(&a, x, Wg, gate_bias, true);
     a.idx = topk_idx; a.w = topk_w;
     const size_t smem = gate_task_smem_bytes(p->E, p->d, elem_size(p->dtype));
     hipStream_t st = (hipStream_t)stream;
     auto launch = [&](auto kern) {
         const int rc2 = set_smem(kern, smem);
         if (rc2) return rc2;
-        hipLaunchKernelGGL(kern, dim3(pl.nRT), dim3(kThreads), smem, st, a, 0);
+        hipLaunchKernelGGL(kern, dim3(a.nRT), dim3(kThreads), smem, st, a, 0);
         return hip_ok(hipGetLastError());
     };
     if (p->dtype == MOE_DT_F32) return launch(k_route<float, 0>);
+    if (a.gate_direct) return launch(k_route<bf16_t, kGateDirect>);
     if (route_exact(p->T, p->E, p->d)) return launch(k_route<bf16_t, 0>);
     switch (gate_variant(p->E, p->d)) {
         case 1: return launch(k_route<bf16_t, 1>);
@@ -1016,7 +1029,7 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     if ((rc = check_ws(workspace))) return rc;
     KArgs a;
     fill_args(pl, workspace, &a);
-    set_gate(&a, x, Wg, gate_bias);
+    set_gate(&a, x, Wg, gate_bias, false);
     a.W1 = W1; a.W3 = W3; a.W2 = W2;
     a.idx = topk_idx; a.w = topk_w; a.counts = counts; a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
     a.slot_flag = slot_flag; a.staging = staging; a.flags = flags; a.out = out;
@@ -1024,7 +1037,7 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     // gate tasks: whole permutation blocks when the routing is an input; fp32 problems of few tokens (at most
     // kGateSplitBlocks blocks of 16) split every gate task over the reduction, so that the gate runs on all workgroups
     // instead of a handful
-    int gate_tasks = Wg ? pl.nRT : pl.nPB;
+    int gate_tasks = Wg ? a.nRT : pl.nPB;
     if (Wg && p->dtype == MOE_DT_F32 && pl.nRT <= kGateSplitBlocks) {
         int S = kGateSplitTasks / pl.nRT;
         if (S > kGateSplitMax) S = kGateSplitMax;
@@ -1036,7 +1049,13 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
             a.gate_parts = (u32 *)((char *)workspace + pl.o_gate_parts);
         }
     }
-    if (Wg && p->dtype == MOE_DT_BF16) {
+    if (a.gate_direct && direct_parts(p->T, p->E, p->d) > 1) {
+        a.gate_split = direct_parts(p->T, p->E, p->d);
+        gate_tasks = a.nRT * a.gate_split;
+        a.gate_partial = (double *)((char *)workspace + pl.o_gate_partial);
+        a.gate_parts = (u32 *)((char *)workspace + pl.o_gate_parts);
+    }
+    if (Wg && p->dtype == MOE_DT_BF16 && !a.gate_direct) {
         a.WgT = (char *)workspace + pl.o_wgt;
         a.t_gate = wgt_tasks(p->d, p->E);
     }

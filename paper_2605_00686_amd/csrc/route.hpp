@@ -4,6 +4,7 @@
 #pragma once
 #include "common.hpp"
 #include "gate.hpp"
+#include "gate_direct.hpp"
 
 namespace moe {
 
@@ -402,7 +403,9 @@ static __device__ __attribute__((noinline)) void route_fallback(KArgsAddr args, 
 __host__ __device__ inline size_t gate_task_smem_bytes(int E, int d, int elem_size) {
     const size_t full = (size_t)kMaxExperts * 4 + route_smem_bytes(E, elem_size);
     const size_t screened = elem_size == 2 ? (size_t)gate_screened_lds(gate_variant(E, d)) : 0;
-    return full > screened ? full : screened;
+    const size_t direct = elem_size == 2 ? direct_lds_bytes(E, d) : 0;
+    const size_t most = full > screened ? full : screened;
+    return most > direct ? most : direct;
 }
 
 // One gate task: the a.gate_tok tokens from t0 = task * a.gate_tok.  With a.Wg == NULL the routing is an input and only
@@ -429,7 +432,14 @@ __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int t
     __syncthreads();
     MOE_TT_BEGIN();
     if (compute) {
-        if constexpr (V > 0) {
+        if constexpr (V == kGateDirect) {
+            if (TOK == 1)
+                route_direct<1>(a, t0, slice, S, lds, cnt, do_hist);
+            else if (TOK == 2)
+                route_direct<2>(a, t0, slice, S, lds, cnt, do_hist);
+            else
+                route_direct<kDirectTokens>(a, t0, slice, S, lds, cnt, do_hist);
+        } else if constexpr (V > 0) {
             if (!a.gate_screens || !route_screened<V, WGT>(a, t0, TOK, smem, do_hist, wgt_ready)) {
                 route_fallback(args, lds_offset(smem), t0, TOK, do_hist ? 1 : 0);
                 __syncthreads();
