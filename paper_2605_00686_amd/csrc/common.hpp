@@ -133,6 +133,7 @@ struct KArgs {
     size_t zero_bytes;         // bytes from ctrl that must be zero between calls
     int tab_lds_off;           // megakernel: LDS offset of the cached decode tables, 0 = none
     int plan_all;              // megakernel: every workgroup derives the plan by itself (see PlanAll); needs the cached tables
+    int plan_from_idx;         // ... and from the choices instead of block histograms
     int sched_lds_off;         // megakernel: LDS offset of the task loops' broadcast slots (StageLds)
 };
 

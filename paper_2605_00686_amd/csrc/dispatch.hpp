@@ -68,6 +68,8 @@ __device__ __forceinline__ int wave_scan_lds(int *v, int n, int start) {
 // planning workgroup, whose tables the others wait for and then fetch, took 20 to 25 us instead (gate end to last
 // permutation block, one workgroup -> all: 4096 tokens x 128 experts 36 -> 25 us, 128 x 128 21 -> 11, 8 x 128 20 -> 9).  What is needed outside (counts, offsets, the flag ranges of the destinations) is
 // written by the one workgroup that drew the plan task.
+// Few slots (plan_from_idx): the workgroup counts the choices themselves, in LDS, and the gate tasks keep no histograms: their
+// global atomics, all at once at the end of the gate and waited for, were on the way to every later step.
 // LDS: hist [nPB][E] | segb [R][E] | nfl [R][E] | dest [R+1] | grp [R+1]; the decode tables go to their permanent place.
 constexpr size_t kPlanAllHist = 64 * 1024, kPlanAllSeg = 32 * 1024;
 __host__ __device__ inline bool plan_all_fits(int E, int R, int nPB) {
@@ -76,6 +78,7 @@ __host__ __device__ inline bool plan_all_fits(int E, int R, int nPB) {
 __host__ __device__ inline size_t plan_all_smem_bytes(int E, int R, int nPB) {
     return ((size_t)nPB * E + 2 * (size_t)E * R + 2 * (R + 1) + 4) * 4 + (size_t)E * 12 + 64;  // (+ a permutation block's masks and bases)
 }
+constexpr int kPlanSlots = 8192;  // slots a workgroup counts by itself: 32 per thread
 struct PlanAll {  // pointers into LDS
     int *hist, *segb, *nfl, *dest, *grp, *off, *rbb, *rsb, *cnt, *rbe, *rse;
     char *perm_lds;
@@ -99,7 +102,30 @@ struct PlanAll {  // pointers into LDS
 __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *n_rb, int *n_rbs) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = a.E, R = a.R, nh = a.nPB * E;
-    if ((nh & 3) == 0) {
+    int invalid = 0;
+    if (a.plan_from_idx) {
+        for (int q = tid; q < nh; q += kThreads) p.hist[q] = 0;
+        if (!a.seg_from_blocks)
+            for (int q = tid; q < E * R; q += kThreads) p.segb[q] = 0;
+        __syncthreads();
+        auto count = [&](int e, int t) __attribute__((always_inline)) {
+            if ((unsigned)e < (unsigned)E) {
+                atomicAdd(&p.hist[t / kPermBlock * E + e], 1);
+                if (!a.seg_from_blocks) atomicAdd(&p.segb[t / a.per_dest * E + e], 1);
+            } else {
+                invalid = 1;
+            }
+        };
+        constexpr int U = 8;  // loads in flight per thread
+        for (int q0 = tid; q0 < a.N; q0 += U * kThreads) {
+            int e[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) e[u] = a.idx[min(q0 + u * kThreads, a.N - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (q0 + u * kThreads < a.N) count(e[u], (q0 + u * kThreads) / a.k);
+        }
+    } else if ((nh & 3) == 0) {
         const u32x4_t *src = (const u32x4_t *)a.blk_hist;
 #pragma unroll 8
         for (int q = tid; q < nh / 4; q += kThreads) ((u32x4_t *)p.hist)[q] = src[q];
@@ -107,12 +133,12 @@ __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *
 #pragma unroll 8
         for (int q = tid; q < nh; q += kThreads) p.hist[q] = a.blk_hist[q];
     }
-    if (!a.seg_from_blocks)
+    if (!a.seg_from_blocks && !a.plan_from_idx)
         for (int q = tid; q < E * R; q += kThreads) {
             const int r = q / E, e = q - r * E;
             p.segb[q] = a.seg_cnt[(size_t)e * R + r];
         }
-    __syncthreads();
+    invalid = __syncthreads_or(invalid);
     if (a.seg_from_blocks) {  // a destination is a whole number of blocks: add up its blocks' histograms
         const int bpd = a.per_dest / kPermBlock;
         for (int q = tid; q < E * R; q += kThreads) {
@@ -129,15 +155,32 @@ __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *
     // One height: ceil(rows / BM).  Mixed heights: see plan_task.
     const int lbm = 31 - __clz(a.tl.BM);
     int over = 0;
+    const bool by_wave = R > 16 && E <= 64;  // many destinations, few experts: a wavefront per expert
+    if (by_wave) {
+        for (int e = wave; e < E; e += 4) {
+            int carry = 0;
+            for (int base = 0; base < R; base += 64) {
+                const int r = base + lane, x = r < R ? p.segb[r * E + e] : 0, inc = wave_inclusive_sum(x);
+                if (r < R) p.segb[r * E + e] = carry + inc - x;
+                carry += __builtin_amdgcn_readlane(inc, 63);
+            }
+            if (lane == 0) p.cnt[e] = carry;
+        }
+        __syncthreads();
+    }
     for (int e = tid; e < E; e += kThreads) {
         int n = 0;
+        if (by_wave) {
+            n = p.cnt[e];
+        } else {
 #pragma unroll 4
-        for (int r = 0; r < R; ++r) {
-            const int c = p.segb[r * E + e];
-            p.segb[r * E + e] = n;
-            n += c;
+            for (int r = 0; r < R; ++r) {
+                const int c = p.segb[r * E + e];
+                p.segb[r * E + e] = n;
+                n += c;
+            }
+            p.cnt[e] = n;
         }
-        p.cnt[e] = n;
         p.off[e] = n;
         const int rem = n & (a.tl.BM - 1);
         const bool small = a.tl.BMS != 0 && rem > 0 && rem <= a.tl.BMS && (!a.tl.tail_with_big || (n >> lbm) == 0);
@@ -145,7 +188,7 @@ __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *
         p.rsb[e] = small ? 1 : 0;
         over |= (a.capacity > 0 && n > a.capacity) ? 1 : 0;
     }
-    if (__syncthreads_or(over)) return MOE_ERR_CAPACITY;
+    if (__syncthreads_or(over)) return invalid ? MOE_ERR_BAD_ROUTING : MOE_ERR_CAPACITY;
     if (wave == 0) {
         const int rows = wave_scan_lds(p.off, E, 0);
         if (lane == 0) p.off[E] = rows;

@@ -562,6 +562,14 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, const TileInfo &ti, char
 // scratch memory, for every stage), and LDS as an offset.  Everything else is
 // inlined into the kernel, so that the kernel's launch bounds govern it.
 
+// Which of the lists in mask m (bit 0: this XCD's own) to draw from: its own while it has entries; then the workgroups of an XCD
+// spread over the others that have some, instead of all trying the same one and most of them in vain.
+__device__ __forceinline__ int next_list(u64 m) {
+    if (m & 1ull) return 0;
+    for (int skip = (int)(blockIdx.x / kTileQueues) % __popcll(m); skip > 0; --skip) m &= m - 1;
+    return __ffsll((long long)m) - 1;
+}
+
 // One kind of tile (GEMM1 if GATED, else GEMM2; big or SMALL row blocks) from the eight tile
 // queues, the one of XCD `home` first, until none is left; or, when one_a >= 0, exactly one
 // tile that the caller has taken already: entry one_b of list one_a (GEMM1), or row block
@@ -607,7 +615,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                     has = ld_relaxed_agent(&c->tile_next[LIST][qq].v) < (u32)n2;
                 }
                 const u64 m = __ballot(has);
-                if (tid == 0) sl->pick = m ? (home + __ffsll((long long)m) - 1) % kTileQueues : -1;
+                if (tid == 0) sl->pick = m ? (home + next_list(m)) % kTileQueues : -1;
             }
             __syncthreads();
             q = uniform(sl->pick);

@@ -238,7 +238,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     }
     bool seen_wgt = false;
     while (task < a.t_plan) {
-        route_task<ET, V, true>(a, args, task - a.t_gate, smem, true, &sl->pick, [&]() __attribute__((always_inline)) {
+        route_task<ET, V, true>(a, args, task - a.t_gate, smem, a.plan_from_idx == 0, &sl->pick, [&]() __attribute__((always_inline)) {
             if (!seen_wgt) seen_wgt = wait_for(&c->wgt_done.v, (u32)a.t_gate) != 0;  // the transposed gate weights are complete
             return seen_wgt;
         });
@@ -270,10 +270,9 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
                 else
                     perm_block_lds(a, p, task - a.t_perm);
             }
-            release_and_count(plan ? &c->plan_done.v : &c->perm_done.v, false);
+            release_and_count(&c->perm_done.v, false);  // (the plan too: nobody waits for it alone)
             draw_next(plan ? 1 : 2);
         }
-        bad = wait_for(&c->plan_done.v, 1u) != 1 || bad;
     } else {
         if (task == a.t_plan) {
             if (routed != 0) plan_task(a, smem);
@@ -308,7 +307,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
             }
         }
     }
-    bad = wait_for(&c->perm_done.v, (u32)a.nPB) != 1 || bad;
+    bad = wait_for(&c->perm_done.v, (u32)(a.nPB + a.plan_all)) != 1 || bad;
     if (tid == 0) {
         sl->n_rb = n_rb;
         sl->n_rbs = n_rbs;
@@ -774,6 +773,13 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
     if (with_plan < smem) with_plan = smem;
     a.plan_all = plan_all_fits(pl.p.E, pl.p.R, pl.nPB) && tables_fit(with_plan) ? 1 : 0;
     if (a.plan_all) smem = with_plan;
+    if (a.plan_all && pl.N <= kPlanSlots) {
+        a.plan_from_idx = 1;
+        if (!a.Wg) {  // nothing is left for gate tasks to do
+            a.t_plan -= a.nRT, a.t_perm -= a.nRT, a.t_g1 -= a.nRT, a.t_end -= a.nRT;
+            a.nRT = 0;
+        }
+    }
     a.tab_lds_off = 0;
     if (tables_fit(smem)) {
         a.tab_lds_off = (int)align_up(smem, 16);
