@@ -56,6 +56,7 @@ constexpr int tile_smem_bytes() {
 using CfgL = TileCfg<4, 4, 2, 2, 32, 4>;  // 256 x 256, wavefront 128 x 128
 using CfgM = TileCfg<2, 4, 2, 2, 64, 3>;  // 128 x 256, wavefront  64 x 128
 using CfgS = TileCfg<1, 2, 1, 4, 64, 4>;  //  32 x 256, wavefront  32 x  64, deep pipeline: weight streaming
+using CfgS2 = TileCfg<2, 2, 1, 4, 64, 3>; //  64 x 256, wavefront  64 x  64: the same for experts of more than 32 rows
 
 // row blocks of the fused FFN: short enough for a block's h to stay in LDS beside three stages
 using CfgFS = TileCfg<1, 2, 1, 4, 64, 3>;  // 32 x 256, wavefront 32 x 64 (decode-sized experts)

@@ -422,11 +422,11 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
             ready_queue_stage<P, PS, MIXED>(a, kargs, smem, home, n_rb, n_rbs, &stage_mark);
         } else {
             MOE_TT_BEGIN();
-            tile_stage<P, true, false>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
+            if (!MIXED || n_rb > 0) tile_stage<P, true, false>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 20);
             if (MIXED && n_rbs > 0) tile_stage<PS, true, true>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 21);
-            tile_stage<P, false, false>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
+            if (!MIXED || n_rb > 0) tile_stage<P, false, false>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 22);
             if (MIXED && n_rbs > 0) tile_stage<PS, false, true>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 23);
@@ -480,8 +480,9 @@ constexpr int kGateSplitBlocks = 64, kGateSplitTasks = 256, kGateSplitMax = 16;
 constexpr int kGateParts = 128;  // blocks whose finished parts are counted, of either split
 static_assert(kGateParts >= kGateSplitBlocks && kGateParts >= kDirectSplitTokens, "one counter per block");
 
-// LM: 256-row tiles plus a 128-row tile for short tails; FS / FM: row blocks of the fused FFN (32 / 64 rows)
-enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S = 3, TK_FS = 4, TK_FM = 5 };
+// LM: 256-row tiles plus a 128-row tile for short tails; S: 32-row tiles; S2: 64-row tiles, and 32-row ones for experts of no
+// more rows than that; FS / FM: row blocks of the fused FFN (32 / 64 rows)
+enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S2 = 2, TK_S = 3, TK_FS = 4, TK_FM = 5 };
 
 struct Plan {
     moe_problem_t p;
@@ -566,13 +567,17 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
         pl->tl.BN1 = 128;
         pl->tl.BN2 = 256;
     } else {
-        pl->kind = (avg >= 96 || tm > 32) ? TK_LM : TK_S;
-        bm = pl->kind == TK_LM ? CfgL::BM : CfgS::BM;
+        // Experts of 32 rows and more on average: an expert of 33 to 64 rows in two 32-row blocks has its weights streamed, and its tiles
+        // run, twice; below that most have one block and the second tile code costs more than it saves.  32 / 64 rows, us:
+        // 128 tokens x 8 of 32 experts of 7168 x 2048 603 / 578, 2313 x 1 of 32 of 704 x 14272 897 / 691, 240 x 1 of 7 of 2304 x 11392 345 / 310;
+        // 76 x 8 of 22 (28 rows) of 3328 x 1152 167 / 174, 128 x 8 of 128 (8 rows) of 2048 x 768 249 / 255.
+        pl->kind = (avg >= 96 || tm > 32) ? TK_LM : avg >= 32 ? TK_S2 : TK_S;
+        bm = pl->kind == TK_LM ? CfgL::BM : pl->kind == TK_S2 ? CfgS2::BM : CfgS::BM;
         pl->tl.BN1 = 128;
         pl->tl.BN2 = 256;
     }
     if (p->fuse_ffn && p->dtype != MOE_DT_BF16) return MOE_ERR_UNSUPPORTED;
-    pl->tl.BMS = pl->kind == TK_LM ? CfgM::BM : 0;
+    pl->tl.BMS = pl->kind == TK_LM ? CfgM::BM : pl->kind == TK_S2 ? CfgS::BM : 0;
     // few rows per expert: the layer streams weights (measured: about -1 % on cfg2; +2 to 4 % on cfg3 and cfg4,
     // which have thousands of rows per expert and are bound by the matrix cores, if it were applied there)
     pl->tl.tail_with_big = avg < 512 ? 1 : 0;
@@ -1074,6 +1079,7 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
         case TK_LM: return launch_mega<Bf16Policy<CfgL>, Bf16Policy<CfgM>>(pl, a, st);
         case TK_FS: return launch_mega<FusedPolicy<CfgFS>, FusedPolicy<CfgFS>>(pl, a, st);
         case TK_FM: return launch_mega<FusedPolicy<CfgFM>, FusedPolicy<CfgFM>>(pl, a, st);
+        case TK_S2: return launch_mega<Bf16Policy<CfgS2>, Bf16Policy<CfgS>>(pl, a, st);
         default: return launch_mega<Bf16Policy<CfgS>, Bf16Policy<CfgS>>(pl, a, st);
     }
 }
