@@ -134,6 +134,7 @@ struct KArgs {
     int tab_lds_off;           // megakernel: LDS offset of the cached decode tables, 0 = none
     int plan_all;              // megakernel: every workgroup derives the plan by itself (see PlanAll); needs the cached tables
     int plan_from_idx;         // ... and from the choices instead of block histograms
+    int perm_lds_off;          // megakernel: LDS offset of the workgroup's own copy of perm (16 bits per slot), 0 = none, GEMM1 reads the global one
     int sched_lds_off;         // megakernel: LDS offset of the task loops' broadcast slots (StageLds)
 };
 

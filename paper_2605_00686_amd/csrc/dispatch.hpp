@@ -214,6 +214,47 @@ __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *
     __syncthreads();
     return MOE_OK;
 }
+// The whole permutation in LDS, by every workgroup of a layer of few slots (perm_lds_off): GEMM1 starts on it, and the wait for
+// the permutation blocks and flag ranges of the others (4 to 8 us: a task, its stores through to memory, the poll) comes behind
+// GEMM1, where it is over.  16-bit slots; scratch: masks and bases of all token blocks, in the GEMM region.
+// Limit, kPermSlots: whole layer, us, waiting -> this: 8 tokens x 8 of 128 experts 133.5 -> 128.7, 128 x 8 of 128 249.5 -> 243.1,
+// 128 x 8 of 32 571 -> 564, 16 x 2 of 8 in f32 99.6 -> 96.1; at 1740 to 4096 slots the masks take what the wait took (435 x 4 of
+// 20 411 -> 415, 392 x 6 of 31 284 -> 287, 512 x 8 of 128 581 -> 584).
+constexpr int kPermSlots = 1024;
+constexpr size_t kPermScratch = 32 * 1024;
+__host__ __device__ inline size_t perm_all_bytes(int E, int nPB) { return (size_t)nPB * E * 12; }
+__device__ __forceinline__ void plan_all_perm(const KArgs &a, const PlanAll &p, char *smem) {
+    const int tid = threadIdx.x, E = a.E, nh = a.nPB * E;
+    u64 *mask = (u64 *)p.perm_lds;  // [blocks][E]
+    int *base = (int *)(mask + nh);
+    uint16_t *perm = (uint16_t *)(smem + a.perm_lds_off);
+    for (int q = tid; q < nh; q += kThreads) mask[q] = 0ull;
+    for (int e = tid; e < E; e += kThreads) {
+        int n = p.off[e];
+        for (int b = 0; b < a.nPB; ++b) {
+            base[b * E + e] = n;
+            n += p.hist[b * E + e];
+        }
+    }
+    __syncthreads();
+    constexpr int U = kPermSlots / kThreads;
+    int e[U];  // (all choices are in [0, E): the counts add up to N)
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u * kThreads < a.N) e[u] = a.idx[min(u * kThreads + tid, a.N - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int s = u * kThreads + tid, t = s / a.k;
+        if (s < a.N) atomicOr(&mask[t / kPermBlock * E + e[u]], 1ull << (t % kPermBlock));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int s = u * kThreads + tid, t = s / a.k, at = t / kPermBlock * E + e[u];
+        if (s < a.N) perm[base[at] + __popcll(mask[at] & ((1ull << (t % kPermBlock)) - 1ull))] = (uint16_t)s;
+    }
+    __syncthreads();
+}
 // Part 2, the workgroups with a plan or permutation task: flags per (destination, expert) and their ranges.  Flags are
 // destination-major, then expert; a segment with expert-local rows [b0, b0+c) touches row blocks b0/tile_m .. (b0+c-1)/tile_m.
 __device__ __forceinline__ void plan_all_flags(const KArgs &a, const PlanAll &p) {

@@ -318,7 +318,8 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char 
     const ET *x = (const ET *)a.x;
     const int N = a.N;
     auto rowptr = [&](int r) {
-        int s = a.perm[ti.row0 + min(r, ti.nrows - 1)];
+        const int at = ti.row0 + min(r, ti.nrows - 1);
+        int s = a.perm_lds_off ? (int)((const uint16_t *)(smem + a.perm_lds_off))[at] : a.perm[at];
         s = min(max(s, 0), N - 1);
         return x + (size_t)(s / a.k) * a.d;
     };

@@ -261,6 +261,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
             if (tid == 0 && planned != MOE_OK) set_error(c, planned);
         }
         bad = bad || planned != MOE_OK;
+        if (!bad && a.perm_lds_off) plan_all_perm(a, p, smem);
         if (!bad && task < a.t_g1) plan_all_flags(a, p);
         while (task < a.t_g1) {
             const bool plan = task < a.t_perm;
@@ -307,13 +308,24 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
             }
         }
     }
-    bad = wait_for(&c->perm_done.v, (u32)(a.nPB + a.plan_all)) != 1 || bad;
+    // (with a copy of perm in LDS, GEMM1 needs nothing more: the wait comes behind it, see wait_for_perm)
+    if (!a.perm_lds_off) bad = wait_for(&c->perm_done.v, (u32)(a.nPB + a.plan_all)) != 1 || bad;
     if (tid == 0) {
         sl->n_rb = n_rb;
         sl->n_rbs = n_rbs;
     }
     __syncthreads();
     return bad ? 1 : 0;
+}
+
+// The permutation and the flag ranges are in memory (before the first GEMM2 tile, where the front stage has not waited for them)
+__device__ __forceinline__ bool wait_for_perm(const KArgs &a, StageLds *sl) {
+    Ctrl *c = a.ctrl;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        sl->ok = wait_ge(c, sl, &c->perm_done.v, (u32)(a.nPB + a.plan_all), a.wait_ticks) && ld_relaxed_agent(&c->error.v) == 0;
+    __syncthreads();
+    return uniform(sl->ok) != 0;
 }
 
 // The statistics from the workgroups' reports: sums, and for the phases the time from the earliest start to the latest end.
@@ -426,12 +438,13 @@ __global__ __launch_bounds__(kThreads, P::MIN_WAVES) void k_megakernel(KArgs a) 
             MOE_TT(c, 20);
             if (MIXED && n_rbs > 0) tile_stage<PS, true, true>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 21);
-            if (!MIXED || n_rb > 0) tile_stage<P, false, false>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
+            const bool permuted = !a.perm_lds_off || wait_for_perm(a, sl);
+            if (permuted && (!MIXED || n_rb > 0)) tile_stage<P, false, false>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 22);
-            if (MIXED && n_rbs > 0) tile_stage<PS, false, true>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
+            if (permuted && MIXED && n_rbs > 0) tile_stage<PS, false, true>(kargs, lds, home, n_rb, n_rbs, -1, -1, -1, &stage_mark);
             MOE_TT(c, 23);
             // ---- stage 3: combine
-            combine_stage<ET>(a, smem);
+            if (permuted) combine_stage<ET>(a, smem);
         }
     }
     // Last workgroup out sums up the workgroups' reports and clears the control block.  (What it reads of the others' work are
@@ -775,6 +788,9 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
     const size_t tab_bytes = (size_t)(4 * (pl.p.E + 1) + pl.tl.maxRB + pl.p.E) * 4;
     auto tables_fit = [&](size_t before) { return tab_bytes <= 6 * 1024 && before + tab_bytes + sizeof(StageLds) + 16 <= kLdsBudget; };
     size_t with_plan = plan_all_smem_bytes(pl.p.E, pl.p.R, pl.nPB);
+    // the whole permutation's masks and bases, in the place of one block's, where they fit the GEMM region
+    const size_t perm_scratch = perm_all_bytes(pl.p.E, pl.nPB);
+    const bool perm_fits = perm_scratch <= kPermScratch && with_plan + perm_scratch <= smem;
     if (with_plan < smem) with_plan = smem;
     a.plan_all = plan_all_fits(pl.p.E, pl.p.R, pl.nPB) && tables_fit(with_plan) ? 1 : 0;
     if (a.plan_all) smem = with_plan;
@@ -789,6 +805,12 @@ static int launch_mega(const Plan &pl, const KArgs &a_in, hipStream_t st) {
     if (tables_fit(smem)) {
         a.tab_lds_off = (int)align_up(smem, 16);
         smem = a.tab_lds_off + tab_bytes;
+    }
+    // perm in LDS too (kPermSlots): the static order without padding, whose GEMM1 stage is the only early reader of perm
+    if (a.plan_from_idx && perm_fits && !P::FUSED && a.scheduler == MOE_SCHED_STATIC && a.capacity == 0 && pl.N <= kPermSlots &&
+        align_up(smem, 16) + (size_t)pl.N * 2 + sizeof(StageLds) + 32 <= kLdsBudget) {
+        a.perm_lds_off = (int)align_up(smem, 16);
+        smem = a.perm_lds_off + (size_t)pl.N * 2;
     }
     a.sched_lds_off = (int)align_up(smem, 16);
     smem = a.sched_lds_off + sizeof(StageLds);
