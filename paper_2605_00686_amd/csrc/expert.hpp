@@ -10,6 +10,12 @@
 
 namespace moe {
 
+// stage depth / count per shape: the best of the variants measured on MI355X
+using CfgL = TileCfg<4, 4, 2, 2, 32, 4>;  // 256 x 256, wavefront 128 x 128
+using CfgM = TileCfg<2, 4, 2, 2, 64, 3>;  // 128 x 256, wavefront  64 x 128
+using CfgS = TileCfg<1, 2, 1, 4, 64, 4>;  //  32 x 256, wavefront  32 x  64, deep pipeline: weight streaming
+using CfgS2 = TileCfg<2, 2, 1, 4, 64, 3>; //  64 x 256, wavefront  64 x  64: the same for experts of more than 32 rows
+
 // ---- GEMM policies: element type + tile shape + main loop
 template <class C>
 struct Bf16Policy {
@@ -18,7 +24,9 @@ struct Bf16Policy {
     static constexpr bool FUSED = false, BN1_VARIES = false;
     static constexpr int BM = C::BM, BN1 = C::BN / 2, BN2 = C::BN;
     static constexpr int C_STRIDE = C::C_STRIDE;
-    static constexpr int SMEM_MAIN = C::SMEM_MAIN;
+    // row blocks of at most this many rows run a smaller main loop on the tile's LDS (see short_gemm), 0: none do
+    static constexpr int SHORT_ROWS = C::BM == CfgL::BM ? CfgM::BM : 0;
+    static constexpr int SMEM_MAIN = C::BM == CfgL::BM && C::SMEM_MAIN < CfgM::SMEM_MAIN ? CfgM::SMEM_MAIN : C::SMEM_MAIN;
     // wavefronts per SIMD the kernel is built for: two workgroups per CU where their LDS fits
     static constexpr int MIN_WAVES = (2 * (C::SMEM_MAIN + 8 * 1024) <= 160 * 1024) ? 2 : 1;
     template <bool GATED, class RowPtr, class Hook>
@@ -32,7 +40,7 @@ struct F32Policy {
     static constexpr bool FUSED = false, BN1_VARIES = true;
     static constexpr int BM = TileF32::BM, BN1 = TileF32::BN, BN2 = TileF32::BN;
     static constexpr int C_STRIDE = TileF32::C_STRIDE;
-    static constexpr int SMEM_MAIN = TileF32::SMEM_MAIN;
+    static constexpr int SMEM_MAIN = TileF32::SMEM_MAIN, SHORT_ROWS = 0;
     static constexpr int MIN_WAVES = 1;
     template <bool GATED, class RowPtr, class Hook>
     static __device__ __forceinline__ void gemm(RowPtr rp, const ET *B0, const ET *B1, int ldb, int ncols, int nrows,
@@ -51,12 +59,6 @@ template <class P>
 constexpr int tile_smem_bytes() {
     return P::SMEM_MAIN + (3 * P::BM + 8) * 4;
 }
-
-// stage depth / count per shape: the best of the variants measured on MI355X
-using CfgL = TileCfg<4, 4, 2, 2, 32, 4>;  // 256 x 256, wavefront 128 x 128
-using CfgM = TileCfg<2, 4, 2, 2, 64, 3>;  // 128 x 256, wavefront  64 x 128
-using CfgS = TileCfg<1, 2, 1, 4, 64, 4>;  //  32 x 256, wavefront  32 x  64, deep pipeline: weight streaming
-using CfgS2 = TileCfg<2, 2, 1, 4, 64, 3>; //  64 x 256, wavefront  64 x  64: the same for experts of more than 32 rows
 
 // row blocks of the fused FFN: short enough for a block's h to stay in LDS beside three stages
 using CfgFS = TileCfg<1, 2, 1, 4, 64, 3>;  // 32 x 256, wavefront 32 x 64 (decode-sized experts)
@@ -306,14 +308,17 @@ __device__ __forceinline__ void store_c_tile(const char *c_tile, int c_stride, i
     }
 }
 
+template <class P, bool GATED>
+static __device__ void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols);
+
 // GEMM1 + SwiGLU: h[rows of the block, n0 .. n0+ncols) = silu(x W1[e]) * (x W3[e]).
 // Rows are gathered straight from x through perm: the permuted activations are
 // never materialised.
 // `after_gemm()` runs between the main loop and the write-out (the megakernel draws
 // its next tile there, so that the counter's latency hides behind the write-out).
 // Returns, in thread 0 and under the ready-queue scheduler, how many GEMM1 tiles of the row block had finished before this one.
-template <class P, class Hook>
-__device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char *smem, Hook after_gemm) {
+template <class P>
+__device__ __forceinline__ void g1_gemm(const KArgs &a, const TileInfo &ti, char *smem) {
     using ET = typename P::ET;
     const ET *x = (const ET *)a.x;
     const int N = a.N;
@@ -324,8 +329,16 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, const TileInfo &ti, char 
         return x + (size_t)(s / a.k) * a.d;
     };
     const size_t wofs = (size_t)ti.e * a.d * a.f + ti.n0;
-    MOE_TT_BEGIN();
     P::template gemm<true>(rowptr, (const ET *)a.W1 + wofs, (const ET *)a.W3 + wofs, a.f, ti.ncols, ti.nrows, a.d, smem, [] {});
+}
+template <class P, class Hook>
+__device__ __forceinline__ u32 g1_tile(const KArgs &a, KArgsAddr args, u32 smem_off, const TileInfo &ti, char *smem, Hook after_gemm) {
+    using ET = typename P::ET;
+    MOE_TT_BEGIN();
+    if (P::SHORT_ROWS != 0 && ti.nrows <= P::SHORT_ROWS)
+        short_gemm<P, true>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols);
+    else
+        g1_gemm<P>(a, ti, smem);
     after_gemm();
     MOE_TT(a.ctrl, 1);
     char *h = (char *)a.h + ((size_t)ti.row0 * a.f + ti.n0) * sizeof(ET);
@@ -538,18 +551,51 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
 // GEMM2 + publish: y[rows of the block, n0 .. n0+ncols) = h W2[e], written to
 // staging row perm[p] (the slot that asked for it).  The caller has already
 // waited for the block's h rows.
-template <class P, class Hook>
-__device__ __forceinline__ void g2_tile(const KArgs &a, const TileInfo &ti, char *smem, Hook after_gemm) {
+template <class P, class PT>
+__device__ __forceinline__ void g2_gemm(const KArgs &a, const TileInfo &ti, char *smem) {
     using ET = typename P::ET;
     const ET *h = (const ET *)a.h;
     auto rowptr = [&](int r) { return h + (size_t)(ti.row0 + min(r, ti.nrows - 1)) * a.f; };
     const ET *B0 = (const ET *)a.W2 + (size_t)ti.e * a.f * a.d + ti.n0;
+    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, ti.nrows, a.f, smem, [&] { publish_prepare<PT>(a, ti, smem); });
+}
+template <class P, class Hook>
+__device__ __forceinline__ void g2_tile(const KArgs &a, KArgsAddr args, u32 smem_off, const TileInfo &ti, char *smem, Hook after_gemm) {
     MOE_TT_BEGIN();
-    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, ti.nrows, a.f, smem, [&] { publish_prepare<P>(a, ti, smem); });
+    if (P::SHORT_ROWS != 0 && ti.nrows <= P::SHORT_ROWS)
+        short_gemm<P, false>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols);
+    else
+        g2_gemm<P, P>(a, ti, smem);
     after_gemm();
     MOE_TT(a.ctrl, 7);
     publish_tile<P>(a, ti, smem);
     MOE_TT(a.ctrl, 8);
+}
+
+// The main loop of a 256-row block with at most 128 rows in it (an expert's tail, under tail_with_big): the 128-row or the 64-row
+// loop.  The C tile has the same layout, so everything behind it is the big tile's.  Cycles per 32 reduction steps: 1250 / 770 /
+// about 500.  Whole layer, us, before -> after: 4096 tokens x 8 of 128 experts 569 -> 556, the same by ready queue 400 -> 394;
+// 32 experts of 2048 x 2048, 257 rows each, 399 -> 352.  A call, not inlined: with the loops inside the stage the 256-row loop had
+// scalar spills in it (layers without such blocks +0.5 to 0.9 %).  A 64-row loop for the 128-row blocks of few rows: +0.4 % on
+// layers of 125 rows per expert, taken out.
+template <class P, bool GATED>
+static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols) {
+    if constexpr (P::SHORT_ROWS != 0) {
+        KArgs a = load_kernel_args(args);
+        mark_global(a);
+        char *smem = lds_at((u32)uniform((int)smem_off));
+        TileInfo ti{};
+        ti.e = uniform(e), ti.row0 = uniform(row0), ti.nrows = uniform(nrows), ti.lrow0 = uniform(lrow0);
+        ti.n0 = uniform(n0), ti.ncols = uniform(ncols), ti.valid = true;
+        using PM = Bf16Policy<CfgM>;
+        using PS = Bf16Policy<CfgS2>;
+        static_assert(PS::SMEM_MAIN <= P::SMEM_MAIN && PM::SMEM_MAIN <= P::SMEM_MAIN, "on the tile's LDS");
+        if (ti.nrows <= PS::BM) {
+            if constexpr (GATED) g1_gemm<PS>(a, ti, smem); else g2_gemm<PS, P>(a, ti, smem);
+        } else {
+            if constexpr (GATED) g1_gemm<PM>(a, ti, smem); else g2_gemm<PM, P>(a, ti, smem);
+        }
+    }
 }
 
 // ---- the stages of the megakernel
@@ -641,7 +687,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
             if (GATED) {
                 const TileInfo ti = decode_tile<SMALL>(a, tb, tq, i, a.tl.NT1, P::BN1_VARIES ? a.tl.BN1 : P::BN1, a.f);
                 MOE_TT(c, 0);
-                const u32 before = g1_tile<P>(a, ti, smem, draw);
+                const u32 before = g1_tile<P>(a, args, smem_off, ti, smem, draw);
                 // ready-queue scheduler: the last GEMM1 tile of a row block enqueues the block's GEMM2
                 // tiles (every writer of the block released its rows before it was counted)
                 if (a.rq_slots && tid == 0 && before + 1 == (u32)a.tl.NT1) {
@@ -661,7 +707,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                 __syncthreads();
                 MOE_TT(c, 5);
                 if (sl->ok) {
-                    g2_tile<P>(a, ti, smem, draw);
+                    g2_tile<P>(a, args, smem_off, ti, smem, draw);
                     if (tid == 0) sl->stat[5] += 1;
                 } else {
                     draw();
