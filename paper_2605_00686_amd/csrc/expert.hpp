@@ -515,7 +515,7 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
                         const int src = __ffsll((long long)m) - 1;
                         m &= m - 1;
                         const int gb = __shfl(gbeg, src, 64), ge = __shfl(gend, src, 64), gi = __shfl(gid, src, 64);
-                        // every tile counted for this group was released (device scope) by its
+                        // every tile counted for this group was stored through to memory by its
                         // writer before it was counted
                         fence_acquire(0);
                         fence_release(sys);  // the one fence of this group
@@ -689,7 +689,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                 MOE_TT(c, 0);
                 const u32 before = g1_tile<P>(a, args, smem_off, ti, smem, draw);
                 // ready-queue scheduler: the last GEMM1 tile of a row block enqueues the block's GEMM2
-                // tiles (every writer of the block released its rows before it was counted)
+                // tiles (every writer's rows were in memory before it was counted)
                 if (a.rq_slots && tid == 0 && before + 1 == (u32)a.tl.NT1) {
                     const int rq = SMALL ? ready_queue_of_block(n_rbs, ti.rb - n_rb) : ready_queue_of_block(n_rb, ti.rb);
                     const u32 base = atomicAdd(&c->rq_tail[rq].v, (u32)a.tl.NT2);
@@ -701,7 +701,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
             } else {
                 const TileInfo ti = single ? decode_block_tile<SMALL>(a, tb, one_a, one_b, P::BN2, a.d)
                                            : decode_tile<SMALL>(a, tb, tq, i, a.tl.NT2, P::BN2, a.d);
-                // h rows were released (agent scope) by their GEMM1 tiles before those counted themselves
+                // h rows were stored through to memory by their GEMM1 tiles before those counted themselves
                 if (tid == 0) sl->ok = (single || wait_ge(c, sl, &a.h_ready[ti.rb], (u32)a.tl.NT1, a.wait_ticks)) ? 1 : 0;
                 if (single) fence_acquire(0);
                 __syncthreads();
