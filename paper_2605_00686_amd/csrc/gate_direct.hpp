@@ -146,7 +146,9 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.d;
     const int p0 = a.E / 8 * slice / S, ppr = a.E / 8 * (slice + 1) / S - p0;  // the part's pieces of a row
-    const int E = 8 * ppr, RL = kThreads / ppr;       // its experts; threads that share a piece's column
+    // Its experts; threads that share a piece's column.  As many of the latter in every part, so that every expert's sum has the same
+    // order: experts with the same weights have the same logit then, and the lower id comes first.
+    const int E = 8 * ppr, RL = kThreads / ((a.E / 8 + S - 1) / S);
     const int rl = tid / ppr, p = tid - rl * ppr;
     float *xs = (float *)lds;                         // [TOK][d]
     double *part = (double *)lds;                     // [RL][TOK][E], in their place

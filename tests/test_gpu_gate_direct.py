@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2605_00686_amd import workloads as W
-from tests import parity
+from tests import gate_forms, parity
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +67,33 @@ def test_direct_gate_is_the_same_as_the_others(d, E, k):
         i2, w2 = route(B, n, d, E, k, x[:n], Wg, bias)
         assert torch.equal(i2, idx[:n])
         np.testing.assert_allclose(w2.numpy(), w[:n].numpy(), rtol=1.5e-7, atol=0)
+
+
+@pytest.mark.parametrize("T,d,E,k", [(80, 2048, 128, 8), (48, 2048, 136, 6), (100, 4096, 72, 8)])
+def test_equal_columns_tie_across_parts(T, d, E, k):
+    """Experts with the same gate weights have the same logit, whichever part of a task each lies in: the lower id comes first,
+    alone and in the layer.  Entries of x and Wg are spread over so many orders of magnitude that a sum depends on the order of
+    its terms, and the parts of a task are of different sizes."""
+    from paper_2605_00686_amd import binding as B
+    print(f"case equal columns T={T} d={d} E={E} k={k}", flush=True)
+    pieces = gate_forms.part_pieces(E, gate_forms.direct_parts(T, E, d))
+    assert gate_forms.is_direct(T, E, d, False) and min(pieces) != max(pieces)
+    inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=64, R=1, dtype="bf16", seed=T + E))
+    gen = torch.Generator().manual_seed(T)
+    for n in ("x", "Wg"):
+        inp[n] = (inp[n].double() * torch.exp2(torch.randint(-12, 13, inp[n].shape, generator=gen).double())).bfloat16()
+    inp["Wg"] = inp["Wg"][:, torch.randperm(E, generator=gen) % (E // 4)].contiguous()  # every column four times
+    ridx, rw, _ = parity.oracle_routing(inp)
+    assert (np.diff(ridx[:, :4], axis=1) > 0).all()  # (the first four choices are the same column)
+    dev = {n: inp[n].cuda() for n in ("x", "Wg", "W1", "W3", "W2")}
+    got = [route(B, T, d, E, k, dev["x"], dev["Wg"], None)]
+    p = B.problem(T, d, E, k, 64, 1, "bf16")
+    buf = B.Buffers(p)
+    B.forward(p, buf, dev["x"], dev["Wg"], None, dev["W1"], dev["W3"], dev["W2"])
+    torch.cuda.synchronize()
+    assert int(buf.stats[7].item()) == 0
+    got.append((buf.topk_idx.cpu(), buf.topk_w.cpu()))
+    for idx, w in got:
+        assert np.array_equal(idx.numpy(), ridx)
+        # (1/4 each, and nothing for the others, whose logits are smaller by hundreds)
+        np.testing.assert_allclose(w.numpy(), rw, rtol=1.5e-7, atol=0)
