@@ -74,7 +74,8 @@ struct KArgs {
     int group_size;  // flags per fence group of the per-destination mode, 0 = all flags of a destination
     int scheduler;   // moe_scheduler_t
     int gate_tok;    // tokens per gate task: 16, 8 or 4
-    int gate_screens, gate_rows_aligned, gate_direct;  // see set_gate
+    int gate_screens, gate_rows_aligned;  // see set_gate
+    int gate_direct;       // threads per column of gate weights where the gate is the direct one (see set_gate), 0 = it is not
     int gate_split;  // fp32: gate tasks per block of 16 tokens: each takes a slice of the reduction (1 = the whole)
     int capacity;    // rows every expert owns in the sorted order, 0 = ragged layout (see moe_problem_t)
     int NP;          // rows of the sorted order: N (ragged) or E * capacity

@@ -37,6 +37,9 @@ __host__ __device__ inline int direct_parts(int T, int E, int d) {
     if (S > kDirectMaxParts) S = kDirectMaxParts;
     return S > 1 ? S : 1;
 }
+// Threads that share a piece's column: as many as the largest part has room for, in every part, so that every expert's sum has
+// the same order.  Experts with the same weights have the same logit then, and the lower id comes first.
+__host__ __device__ inline int direct_threads(int E, int parts) { return kThreads / ((E / 8 + parts - 1) / parts); }
 __host__ __device__ inline size_t direct_lds_bytes(int E, int d) {
     const size_t rows = (size_t)kDirectTokens * d * 4 < kDirectLds ? (size_t)kDirectTokens * d * 4 : kDirectLds;
     const size_t part = (size_t)kDirectTokens * 256 * 64;
@@ -146,9 +149,7 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.d;
     const int p0 = a.E / 8 * slice / S, ppr = a.E / 8 * (slice + 1) / S - p0;  // the part's pieces of a row
-    // Its experts; threads that share a piece's column.  As many of the latter in every part, so that every expert's sum has the same
-    // order: experts with the same weights have the same logit then, and the lower id comes first.
-    const int E = 8 * ppr, RL = kThreads / ((a.E / 8 + S - 1) / S);
+    const int E = 8 * ppr, RL = a.gate_direct;        // its experts; threads that share a piece's column (direct_threads)
     const int rl = tid / ppr, p = tid - rl * ppr;
     float *xs = (float *)lds;                         // [TOK][d]
     double *part = (double *)lds;                     // [RL][TOK][E], in their place

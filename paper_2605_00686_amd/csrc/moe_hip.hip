@@ -722,7 +722,7 @@ static void set_gate(KArgs *a, const void *x, const void *Wg, const float *bias,
     a->gate_rows_aligned = (a->E & 7) == 0 && ((uintptr_t)Wg & 15) == 0;
     // few tokens: see gate_direct.hpp; its tasks have other sizes than the screen's
     if (Wg && a->dtype == MOE_DT_BF16 && gate_is_direct(a->T, a->E, a->d, alone)) {
-        a->gate_direct = 1;
+        a->gate_direct = direct_threads(a->E, 1);
         a->gate_tok = direct_tokens(a->T);
         a->nRT = (a->T + a->gate_tok - 1) / a->gate_tok;
     }
@@ -1085,6 +1085,7 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     }
     if (a.gate_direct && direct_parts(p->T, p->E, p->d) > 1) {
         a.gate_split = direct_parts(p->T, p->E, p->d);
+        a.gate_direct = direct_threads(p->E, a.gate_split);
         gate_tasks = a.nRT * a.gate_split;
         a.gate_partial = (double *)((char *)workspace + pl.o_gate_partial);
         a.gate_parts = (u32 *)((char *)workspace + pl.o_gate_parts);
