@@ -1002,9 +1002,11 @@ __device__ __forceinline__ void combine_chunk(const KArgs &a, int t_first, int n
 // epoch; otherwise check once and report.  Flags are read with relaxed atomic
 // loads (a first pass that keeps many loads in flight, then a spin on whatever
 // was not ready) followed by one acquire fence at the requested scope.  Then
-// the rows: inside the megakernel (WAIT), where a workgroup has one task and a CU one workgroup, see combine_chunk (k > 8: as alone); alone,
+// the rows: inside the megakernel (WAIT), where a workgroup has one task and a CU one workgroup, see combine_chunk; alone,
 // one wavefront per token, or several that share a token's row when the task has fewer than four tokens, 8 loads in flight per
-// lane, a CU holding several workgroups.  SHARE = false: a wavefront per token whatever the task has (the standalone launch of four tokens or more
+// lane, a CU holding several workgroups.  k > 8 inside the megakernel: the same with 16 in flight, one piece of 16 rows.  Whole layer, us, 8 rows /
+// two pieces of 8 / 16 rows: 4096 x 9 of 64 experts of 2048 x 128 265 / 260 / 261, 4096 x 32 740 / 726 / 729, 16384 x 10 of 32 900 / 861 / 850, 1024 x 16
+// of 32 of 7168 x 64 416 / 407 / 409; 8 x 16 of 64 71.5 / 72.5 / 71.3, 128 x 32 105.2 / 106.8 / 105.5.  SHARE = false: a wavefront per token whatever the task has (the standalone launch of four tokens or more
 // per task: with shared rows as a run-time choice it took 28.7 instead of 25.9 us on 4096 x 8 rows of 2048, 91 instead of 80 us
 // on 16384 x 2 rows of 4096).
 template <typename ET, bool WAIT, bool STREAM = false, bool SHARE = true>
@@ -1110,15 +1112,19 @@ __device__ __forceinline__ void combine_task(const KArgs &a, int task, char *sme
         const char *rows = staging + (size_t)t * k * rstride;
         char *orow = (char *)a.out + (size_t)t * rstride;
         const float *wt = a.w + (size_t)t * k;
-        constexpr int IF = 8;  // 16-byte loads in flight per lane whatever k is
-        if (k == 1)
-            combine_token<ET, IF, IF, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
-        else if (k <= 2)
-            combine_token<ET, IF, IF / 2, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
-        else if (k <= 4)
-            combine_token<ET, IF, IF / 4, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
-        else
-            combine_token<ET, IF, IF / 8, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
+        if constexpr (WAIT) {  // (k > 8)
+            combine_token<ET, 16, 1, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
+        } else {
+            constexpr int IF = 8;  // 16-byte loads in flight per lane whatever k is
+            if (k == 1)
+                combine_token<ET, IF, IF, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
+            else if (k <= 2)
+                combine_token<ET, IF, IF / 2, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
+            else if (k <= 4)
+                combine_token<ET, IF, IF / 4, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
+            else
+                combine_token<ET, IF, IF / 8, STREAM>(rows, wt, orow, k, c_begin, c_end, rstride, lane);
+        }
     }
 }
 

@@ -16,6 +16,9 @@ CASES = [(1, 64, 4, 1, 1, "bf16", 0), (256, 1088, 8, 2, 4, "bf16", 0), (257, 204
          (1021, 576, 8, 8, 1, "bf16", 0), (1025, 2112, 4, 4, 5, "bf16", 0), (1030, 64, 16, 9, 2, "bf16", 0), (1024, 4096, 4, 1, 8, "bf16", 0),
          (600, 1040, 4, 3, 3, "f32", 0), (1019, 128, 8, 8, 1, "f32", 0), (1029, 1024, 8, 4, 7, "bf16", 1), (771, 640, 4, 2, 3, "bf16", 1),
          (514, 192, 4, 1, 2, "bf16", 1),
+         # more rows per token than a wavefront loads at once, and exactly as many
+         (5, 1984, 32, 32, 1, "bf16", 0), (300, 576, 24, 16, 3, "bf16", 0), (770, 1088, 20, 17, 7, "bf16", 0), (1030, 320, 16, 10, 5, "bf16", 1),
+         (257, 272, 24, 24, 1, "f32", 0), (1200, 144, 16, 16, 4, "f32", 0),
          (4096, 64, 8, 2, 64, "bf16", 0), (4097, 64, 8, 2, 17, "bf16", 0), (1024, 64, 16, 8, 16, "bf16", 1), (1025, 64, 16, 8, 25, "bf16", 0)]
 
 
