@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2605_00686_amd import workloads as W
-from tests import parity
+from tests import gate_forms, parity
 
 pytestmark = pytest.mark.gpu
 
@@ -19,7 +19,10 @@ CASES = [(5, 64, 1, 1), (37, 128, 7, 3), (1030, 192, 16, 2), (16, 256, 17, 2), (
          (130, 320, 24, 4), (65, 384, 32, 6), (70, 192, 48, 4), (130, 256, 33, 8), (9, 64, 96, 8), (70, 128, 64, 8), (1030, 448, 20, 2),
          (1025, 512, 32, 4), (1025, 256, 47, 4), (1025, 192, 64, 8), (1030, 128, 200, 4), (2049, 640, 17, 3), (2050, 704, 32, 4),
          (2049, 384, 47, 4), (2050, 448, 48, 6), (2049, 192, 64, 8), (2050, 256, 64, 8), (4100, 128, 128, 8), (4100, 192, 128, 8),
-         (2049, 192, 255, 5), (2050, 2048, 8, 2), (2049, 2112, 16, 2), (2049, 1024, 12, 2), (2049, 1088, 15, 2)]
+         (2049, 192, 255, 5), (2050, 2048, 8, 2), (2049, 2112, 16, 2), (2049, 1024, 12, 2), (2049, 1088, 15, 2),
+         # both sides of the rules for the direct gate of few tokens; past them the layer screens with tasks of 4 tokens and aligned rows of Wg
+         (512, 4096, 128, 8), (513, 512, 128, 8), (513, 576, 128, 8), (1024, 1024, 64, 8), (1024, 1088, 64, 8), (1025, 1024, 64, 8),
+         (256, 4096, 256, 8), (257, 2048, 256, 8), (257, 2112, 256, 8), (600, 4096, 24, 4), (600, 2112, 32, 4), (600, 448, 192, 8)]
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])
@@ -78,12 +81,18 @@ def test_gate_of_views_off_16_bytes(T, d, E, k, which):
         np.testing.assert_allclose(w.numpy(), out[0][1].numpy(), rtol=1.5e-7, atol=0)
 
 
+# (tests/test_gate_forms.py checks which forms of the gate these are)
+UNALIGNED_CASES = [(9, 1152, 8, 2), (1030, 256, 64, 8), (2050, 576, 48, 6), (40, 1024, 256, 8), (130, 128, 72, 4),
+                   (600, 4096, 24, 4), (600, 2112, 32, 4), (520, 1088, 64, 8), (600, 576, 128, 8), (600, 448, 192, 8), (520, 320, 256, 5),
+                   (1030, 192, 128, 8)]
+
+
 @pytest.mark.parametrize("offset", [1, 4, 7])
-@pytest.mark.parametrize("T,d,E,k", [(9, 1152, 8, 2), (1030, 256, 64, 8), (2050, 576, 48, 6), (40, 1024, 256, 8), (130, 128, 72, 4)],
-                         ids=lambda v: str(v))
+@pytest.mark.parametrize("T,d,E,k", UNALIGNED_CASES, ids=lambda v: str(v))
 def test_unaligned_view_of_the_gate_weights(T, d, E, k, offset):
     """Wg as a view that starts `offset` elements past a 16-byte boundary, inside a tensor whose neighbours are no numbers:
-    the oracle's choices, standalone and in the layer, in every code variant that takes whole pieces otherwise."""
+    the oracle's choices, standalone and in the layer, in every code variant of the screen that takes whole pieces otherwise and
+    in the direct gate."""
     from paper_2605_00686_amd import binding as B
     print(f"case gate weights off T={T} d={d} E={E} k={k} offset={offset}", flush=True)
     inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=64, R=1, dtype="bf16", seed=T + E + offset, bias_std=0.3))
@@ -105,29 +114,36 @@ def test_unaligned_view_of_the_gate_weights(T, d, E, k, offset):
         np.testing.assert_allclose(w2.cpu().numpy(), rw, rtol=1.5e-7, atol=0)  # (as above)
 
 
-def test_unaligned_view_of_the_gate_weights_keeps_the_screen():
-    """The gate phase of a decode batch takes at most twice as long on such a view as on aligned weights (exact logits of
-    all experts take more than three times as long)."""
+@pytest.mark.parametrize("T", [8, 600], ids=["direct", "screen"])
+def test_unaligned_view_of_the_gate_weights_keeps_its_form(T):
+    """The gate phase of the layer takes at most twice as long on such a view as on aligned weights, of a decode batch (the direct
+    gate) and of 600 tokens (the screen, whose exact fallback, taken here with a row that is no number in every task, is outside
+    that bound)."""
     from paper_2605_00686_amd import binding as B
-    print("case gate weights off, time", flush=True)
-    inp = W.make_inputs(dict(T=8, d=2048, E=128, k=8, f=64, R=1, dtype="bf16", seed=3, bias_std=0.3, tile_m=32))
-    p = B.problem(8, 2048, 128, 8, 64, 1, "bf16", tile_m=32)
+    print(f"case gate weights off, time T={T}", flush=True)
+    assert (gate_forms.form(T, 128, 2048, False) == "direct") == (T == 8)
+    inp = W.make_inputs(dict(T=T, d=2048, E=128, k=8, f=64, R=1, dtype="bf16", seed=3, bias_std=0.3, tile_m=32))
+    p = B.problem(T, 2048, 128, 8, 64, 1, "bf16", tile_m=32)
     buf = B.Buffers(p)
     dev = {n: inp[n].cuda() for n in ("x", "Wg", "gate_bias", "W1", "W3", "W2")}
     room = torch.zeros(dev["Wg"].numel() + 16, dtype=torch.bfloat16, device="cuda")
     view = room[1:1 + dev["Wg"].numel()].reshape(dev["Wg"].shape)
     view.copy_(dev["Wg"])
+    spoiled = dev["x"].clone()
+    spoiled[::4, 0] = float("nan")
     gate_us = []
-    for wg in (dev["Wg"], view):
+    for x, wg in ((dev["x"], dev["Wg"]), (dev["x"], view), (spoiled, dev["Wg"])):
         seen = []
         for _ in range(12):
             p.epoch += 1
-            B.forward(p, buf, dev["x"], wg, dev["gate_bias"], dev["W1"], dev["W3"], dev["W2"])
+            B.forward(p, buf, x, wg, dev["gate_bias"], dev["W1"], dev["W3"], dev["W2"])
             torch.cuda.synchronize()
             seen.append(int(buf.stats[8].item()) / 1000)
         gate_us.append(sorted(seen)[len(seen) // 2])
-    print(f"gate phase {gate_us[0]:.1f} us, on a view off 16 bytes {gate_us[1]:.1f} us", flush=True)
+    print(f"gate phase {gate_us[0]:.1f} us, on a view off 16 bytes {gate_us[1]:.1f} us, through the fallback {gate_us[2]:.1f} us", flush=True)
     assert gate_us[1] <= 2 * gate_us[0]
+    if T == 600:
+        assert gate_us[2] > 2 * gate_us[0]
 
 
 def test_gate_weights_past_32_bits():

@@ -21,13 +21,15 @@ def route(B, T, d, E, k, x, Wg, bias):
 
 
 CASES = [(1, 64, 8, 8), (3, 2048, 128, 8), (8, 2112, 256, 32), (64, 4096, 64, 6), (127, 2048, 144, 8), (128, 1088, 240, 5), (129, 2048, 128, 8),
-         (256, 64, 72, 32), (257, 320, 56, 1), (511, 7168, 16, 4), (512, 576, 136, 8), (513, 640, 24, 7), (1023, 128, 256, 8), (1024, 1024, 48, 6)]
+         (256, 64, 72, 32), (257, 320, 56, 1), (511, 7168, 16, 4), (512, 576, 136, 8), (513, 640, 24, 7), (1023, 128, 256, 8), (1024, 1024, 48, 6),
+         (80, 2048, 128, 8), (48, 2048, 136, 8), (85, 2048, 128, 32), (100, 4096, 72, 8)]  # (parts of different size)
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])
 def test_direct_gate(T, d, E, k):
     from paper_2605_00686_amd import binding as B
     print(f"case direct gate T={T} d={d} E={E} k={k}", flush=True)
+    assert gate_forms.is_direct(T, E, d, True) and gate_forms.is_direct(T, E, d, False) == (T <= 512 or E * d <= 1 << 16)
     inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=64, R=1, dtype="bf16", seed=T + d + E, bias_std=0.3))
     inp["x"][T // 2] = 0  # a padded slot: its logits are the biases ...
     inp["gate_bias"][:] = inp["gate_bias"].round(decimals=1)  # ... among which there are ties
