@@ -51,3 +51,33 @@ def test_layer_on_its_own_permutation(T, k, E, R, dtype, spread):
             assert err <= tol, err
         outs.append(buf.out.clone())
     assert torch.equal(outs[0], outs[1])
+
+
+def test_waits_behind_the_first_gemm_expire():
+    """Routing that is an input and a bound of one tick for the waits: nothing is waited for before GEMM1, so the waits behind it are
+    the ones that expire.  The call reports it, every workgroup leaves, and with the workspace initialised again the same
+    buffers give the right result."""
+    from paper_2605_00686_amd import binding as B
+    T, k, E, R, d, f = 64, 2, 6, 2, 2048, 256
+    print("case perm in LDS, wait limit 1 tick", flush=True)
+    inp = W.make_inputs(dict(T=T, d=d, E=E, k=k, f=f, R=R, dtype="bf16", seed=9, tile_m=32))
+    idx = torch.rand(T, E, generator=torch.Generator().manual_seed(1)).topk(k, dim=1).indices.to(torch.int32)
+    w = torch.full((T, k), 0.5)
+    dev = {n: inp[n].cuda() for n in ("x", "W1", "W3", "W2")}
+    o = parity.oracle_arrays(inp)
+    ref = oracle.forward(o["x"], o["Wg"], o["W1"], o["W3"], o["W2"], k, idx=idx.numpy(), w=w.numpy())
+    p = B.problem(T, d, E, k, f, R, "bf16", tile_m=32, wait_ticks=1)
+    buf = B.Buffers(p)
+    buf.topk_idx.copy_(idx)
+    buf.topk_w.copy_(w)
+    B.forward(p, buf, dev["x"], None, None, dev["W1"], dev["W3"], dev["W2"])
+    torch.cuda.synchronize()
+    assert int(buf.stats[7].item()) == B.MOE_ERR_TIMEOUT and int(buf.stats[6].item()) > 0
+    B.moe_workspace_init(p, buf.workspace)
+    buf.flags.zero_()
+    p.wait_ticks = 0
+    B.forward(p, buf, dev["x"], None, None, dev["W1"], dev["W3"], dev["W2"])
+    torch.cuda.synchronize()
+    assert int(buf.stats[7].item()) == 0
+    assert np.array_equal(buf.perm.cpu().numpy(), ref["perm"])
+    assert parity.row_err(buf.out.float().cpu().numpy(), ref["out"]).max() <= 2e-2  # (as above)

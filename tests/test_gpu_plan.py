@@ -1,5 +1,5 @@
-"""GPU test of the plan inside the megakernel on both sides of the rule that chooses between its two forms (every workgroup
-derives it in LDS; one workgroup writes it to memory): destinations x experts, token blocks x experts and the decode tables at
+"""GPU test of the plan inside the megakernel on both sides of the rules that choose between its three forms (every workgroup
+derives it in LDS, from the choices or from block histograms; one workgroup writes it to memory): destinations x experts, token blocks x experts and the decode tables at
 and just past the limits, destinations that are and are not whole token blocks, against the oracle."""
 import numpy as np
 import pytest
@@ -14,21 +14,29 @@ pytestmark = pytest.mark.gpu
 # (T, E, R, k, tile_m, capacity)
 CASES = [(192, 64, 64, 2, 32, 0), (195, 64, 65, 2, 32, 0), (4096, 256, 4, 2, 128, 0), (4100, 256, 4, 2, 128, 0),
          (640, 3, 10, 2, 64, 0), (640, 3, 10, 2, 64, 512), (77, 5, 7, 3, 128, 77),
-         (8192, 128, 4, 2, 128, 0), (8196, 128, 4, 2, 128, 0), (47, 255, 1, 2, 32, 0), (48, 255, 1, 2, 32, 0)]
-# which of them derive the plan in every workgroup
-IN_EVERY_WORKGROUP = [True, False, False, False, True, True, True, True, False, True, False]
+         (8192, 128, 4, 2, 128, 0), (8196, 128, 4, 2, 128, 0), (47, 255, 1, 2, 32, 0), (48, 255, 1, 2, 32, 0),
+         # 64-row blocks have fewer decode tables than 32-row ones (48 tokens above); both sides of the slots counted as choices
+         (4096, 252, 4, 2, 32, 0), (4096, 16, 8, 2, 128, 0), (4098, 16, 6, 2, 128, 0), (4160, 8, 10, 3, 128, 4160), (4160, 8, 64, 3, 64, 4100),
+         (4104, 6, 12, 2, 32, 0)]
+# how each derives the plan: every workgroup from the choices, every workgroup from block histograms, one workgroup
+FORMS = ["choices", "one", "one", "one", "choices", "choices", "choices", "histograms", "one", "choices", "one",
+         "one", "choices", "histograms", "histograms", "histograms", "histograms"]
 
 
-def in_every_workgroup(T, E, R, k, tile_m):
+def plan_form(T, E, R, k, tile_m):
     """The rule of the launch: at most 32 KB of segment tables (8 * E * R), 64 KB of histograms (4 * E * ceil(T / 64)) and 6 KB of
-    decode tables (4 * (6 * E + 4 + row blocks); row blocks of 32 rows with fewer than 96 rows per expert and a 32-row publish
-    tile, else of 256)."""
-    bm = 32 if T * k // E < 96 and tile_m == 32 else 256
-    return 8 * E * R <= 32768 and 4 * E * -(-T // 64) <= 65536 and 4 * (6 * E + 4 + T * k // bm) <= 6144
+    decode tables (4 * (6 * E + 4 + row blocks); with a 32-row publish tile row blocks of 32 rows below 32 rows per expert and of 64
+    below 96, else of 256) for a plan in every workgroup, from the choices up to 8192 of them."""
+    avg = T * k // E
+    bm = 256 if avg >= 96 or tile_m > 32 else 64 if avg >= 32 else 32
+    if 8 * E * R > 32768 or 4 * E * -(-T // 64) > 65536 or 4 * (6 * E + 4 + T * k // bm) > 6144:
+        return "one"
+    return "choices" if T * k <= 8192 else "histograms"
 
 
-def test_cases_lie_on_both_sides():
-    assert [in_every_workgroup(*c[:5]) for c in CASES] == IN_EVERY_WORKGROUP
+def test_cases_reach_every_form():
+    assert [plan_form(*c[:5]) for c in CASES] == FORMS
+    assert plan_form(192, 64, 64, 2, 32) == "choices" and plan_form(195, 64, 65, 2, 32) == "one" and plan_form(4160, 8, 10, 3, 32) == "histograms"
 
 
 @pytest.mark.parametrize("T,E,R,k,tile_m,capacity", CASES, ids=["T%d_E%d_R%d_k%d_m%d_c%d" % c for c in CASES])
@@ -53,17 +61,18 @@ def test_plan_forms(T, E, R, k, tile_m, capacity):
     assert int(buf.stats[0].item()) == plan["fences_per_dest"]
 
 
-@pytest.mark.parametrize("T,E,R", [(192, 64, 64), (195, 64, 65)], ids=["every_workgroup", "one_workgroup"])
-@pytest.mark.parametrize("capacity", [0, 192])
-def test_plan_reports_slots_that_no_expert_counts(T, E, R, capacity):
-    """An id outside [0, E) among routing that is an input, either form of the plan and either layout: reported, nothing else
-    written (perm keeps its poison), and the workspace is good for the next call."""
+@pytest.mark.parametrize("T,E,R,k", [(192, 64, 64, 2), (4160, 8, 10, 3), (195, 64, 65, 2)], ids=["choices", "histograms", "one"])
+@pytest.mark.parametrize("padded", [False, True], ids=["ragged", "padded"])
+def test_plan_reports_slots_that_no_expert_counts(T, E, R, k, padded):
+    """An id outside [0, E) among routing that is an input, every form of the plan and either layout: reported, nothing else
+    written (perm keeps its poison), and the workspace is good for the next call.  Padded: so is an expert over its capacity."""
     from paper_2605_00686_amd import binding as B
-    print(f"case plan bad id T={T} E={E} R={R} capacity={capacity}", flush=True)
-    inp = W.make_inputs(dict(T=T, d=64, E=E, k=2, f=64, R=R, dtype="bf16", seed=5, tile_m=32))
-    p = B.problem(T, 64, E, 2, 64, R, "bf16", tile_m=32, capacity=capacity)
+    capacity = T * k // E + 100 if padded else 0
+    print(f"case plan bad id T={T} E={E} R={R} k={k} capacity={capacity}", flush=True)
+    inp = W.make_inputs(dict(T=T, d=64, E=E, k=k, f=64, R=R, dtype="bf16", seed=5, tile_m=32))
+    p = B.problem(T, 64, E, k, 64, R, "bf16", tile_m=32, capacity=capacity)
     buf = B.Buffers(p)
-    good = (torch.arange(T)[:, None] + torch.arange(2)[None, :] * 3) % E
+    good = (torch.arange(T)[:, None] + torch.arange(k)[None, :] * 3) % E
     dev = {n: inp[n].cuda() for n in ("x", "W1", "W3", "W2")}
     buf.topk_w.fill_(0.5)
     buf.perm.fill_(-7)
@@ -75,6 +84,17 @@ def test_plan_reports_slots_that_no_expert_counts(T, E, R, capacity):
         torch.cuda.synchronize()
         assert int(buf.stats[7].item()) == B.MOE_ERR_BAD_ROUTING
         assert bool((buf.perm == -7).all().item())
+    if padded:
+        full = good.clone()
+        full[:capacity + 1, 0] = 0  # too many rows for expert 0
+        for j in range(1, k):  # (the ids of a token stay distinct)
+            full[:capacity + 1, j] = 1 + (torch.arange(capacity + 1) + j) % (E - 1)
+        buf.topk_idx.copy_(full)
+        B.forward(p, buf, dev["x"], None, None, dev["W1"], dev["W3"], dev["W2"])
+        torch.cuda.synchronize()
+        assert int(buf.stats[7].item()) == B.MOE_ERR_CAPACITY
+        assert bool((buf.perm == -7).all().item())
+        assert np.array_equal(buf.counts.cpu().numpy(), np.bincount(full.numpy().reshape(-1), minlength=E))
     buf.topk_idx.copy_(good)
     p.epoch = 2
     B.forward(p, buf, dev["x"], None, None, dev["W1"], dev["W3"], dev["W2"])
