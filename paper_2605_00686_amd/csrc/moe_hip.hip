@@ -113,24 +113,29 @@ __global__ __launch_bounds__(kThreads, 1) void k_probe_mfma(const uint4 *frag, i
 // half of them awaited before the next batch.  LDS form: global_load_lds_dwordx4 into a per-wavefront ring in LDS,
 // the way the GEMM main loop loads its stages; register form: global_load_dwordx4, the values folded into one word.
 // What this reaches is what a CU can pull in with that many wavefronts, from HBM (span far beyond the caches), from
-// the memory-side cache or from L2 (small span, stride 0), whatever else the kernel that is compared with it does.  (From the caches
-// few wavefronts are bound by the 64-bit modulo of each address instead: 35 GB/s per CU from L2 with four, 113 to 130 with masked offsets.)
+// the memory-side cache or from L2 (small span, stride 0), whatever else the kernel that is compared with it does.
 constexpr int kStreamDepth = 8;
 template <int NT, bool TO_LDS>
 __global__ __launch_bounds__(NT, 1) void k_probe_stream(const char *buf, size_t span, size_t stride, size_t bytes_per_wg, u32 *sink) {
     extern __shared__ __align__(1024) char stream_lds[];
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t start = ((size_t)blockIdx.x * stride) % span;
     const size_t n_instr = bytes_per_wg / ((size_t)NW * 1024);
     u32x4_t acc = u32x4_t{0u, 0u, 0u, 0u};
-    const size_t mine = (size_t)wave * 1024 + (size_t)lane * 16;
+    // (one modulo here, none per load: a load's step, NW KB, is at most the span)
+    size_t off = ((size_t)blockIdx.x * stride + (size_t)wave * 1024 + (size_t)lane * 16) % span;
+    auto next = [&]() {
+        const char *src = buf + off;
+        off += (size_t)NW * 1024;
+        off = off >= span ? off - span : off;
+        return src;
+    };
     if (TO_LDS) {
         const u32 ring = lds_offset(stream_lds) + (u32)wave * (kStreamDepth * 1024);
         for (size_t it = 0; it + kStreamDepth <= n_instr; it += kStreamDepth) {
 #pragma unroll
             for (int u = 0; u < kStreamDepth; ++u) {
-                const char *src = buf + (start + (it + u) * ((size_t)NW * 1024) + mine) % span;
+                const char *src = next();
                 asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                              :
                              : "s"(__builtin_amdgcn_readfirstlane(ring + (u32)u * 1024)), "v"(src)
@@ -145,8 +150,7 @@ __global__ __launch_bounds__(NT, 1) void k_probe_stream(const char *buf, size_t 
         for (size_t it = 0; it + kStreamDepth <= n_instr; it += kStreamDepth) {
             u32x4_t r[kStreamDepth];
 #pragma unroll
-            for (int u = 0; u < kStreamDepth; ++u)
-                r[u] = *(const u32x4_t *)(buf + (start + (it + u) * ((size_t)NW * 1024) + mine) % span);
+            for (int u = 0; u < kStreamDepth; ++u) r[u] = *(const u32x4_t *)next();
 #pragma unroll
             for (int u = 0; u < kStreamDepth; ++u) acc ^= r[u];
         }
