@@ -75,7 +75,8 @@ typedef enum { MOE_SCOPE_AGENT = 0, MOE_SCOPE_SYSTEM = 1 } moe_fence_scope_t;
  *                last flag of a destination enqueues the combine tasks of the
  *                destination's tokens.  Workgroups take ready tasks before new GEMM1
  *                tiles, so GEMM2 tiles and combine tasks start out of order and nothing
- *                that was taken ever waits.  Results are identical. */
+ *                that was taken waits, except for flags that are just being stored.
+ *                Results are identical. */
 typedef enum { MOE_SCHED_STATIC = 0, MOE_SCHED_READY_QUEUE = 1 } moe_scheduler_t;
 
 typedef struct {
@@ -145,7 +146,7 @@ typedef struct {
  *          fence-group counter (PER_DEST)
  * stats[4] GEMM1 compute tiles          stats[5] GEMM2 compute tiles
  * stats[6] bounded waits that expired   stats[7] device status (a moe_status_t, 0 = ok)
- * stats[8..13] in-kernel timeline: nanoseconds from the first task drawn to the end of
+ * stats[8..13] in-kernel timeline: nanoseconds from the start of the first workgroup to the end of
  *   the last gate task [8], the plan [9], the last permutation block [10], the last
  *   GEMM1 tile [11], the last GEMM2 tile [12], the last combine task [13]
  * stats[14] nanoseconds workgroups spent waiting on dependencies (each wait counted once per

@@ -73,10 +73,10 @@ struct KArgs {
     int dtype, tile_m, tile_n, signal_mode, fence_scope;
     int group_size;  // flags per fence group of the per-destination mode, 0 = all flags of a destination
     int scheduler;   // moe_scheduler_t
-    int gate_tok;    // tokens per gate task: 16, 8 or 4
+    int gate_tok;    // tokens per gate task: 16, 8 or 4; 4, 2 or 1 (direct gate)
     int gate_screens, gate_rows_aligned;  // see set_gate
     int gate_direct;       // threads per column of gate weights where the gate is the direct one (see set_gate), 0 = it is not
-    int gate_split;  // fp32: gate tasks per block of 16 tokens: each takes a slice of the reduction (1 = the whole)
+    int gate_split;  // gate tasks per block of gate_tok tokens: fp32, each a slice of the reduction; direct gate, each a part of the experts (1 = the whole)
     int capacity;    // rows every expert owns in the sorted order, 0 = ragged layout (see moe_problem_t)
     int NP;          // rows of the sorted order: N (ragged) or E * capacity
     u32 epoch;
@@ -125,8 +125,8 @@ struct KArgs {
     u32 *h_ready;              // [maxRB] GEMM1 tiles finished per row block
     void *h;                   // [N][f]
     void *WgT;                 // [E][d] transposed gate weights (bf16 problems with a gate), else NULL
-    double *gate_partial;      // [blocks][gate_split][16][E] partial logits of the split gate
-    u32 *gate_parts;           // [blocks] slices finished per block of 16 tokens
+    double *gate_partial;      // split gate: [blocks][gate_split][16][E] partial logits (fp32), [T][E] logits (direct gate)
+    u32 *gate_parts;           // [blocks] tasks finished per block of gate_tok tokens
     u32 *dest_done;            // [R] flags stored so far per destination (ready-queue scheduler), else NULL
     u32 *rq_slots;             // [8][rq_cap] ready-queue entries, 0 = empty (ready-queue scheduler), else NULL
     int rq_cap;                // entries per ready queue: all GEMM2 tiles plus all combine tasks
@@ -206,6 +206,9 @@ __device__ __forceinline__ void sync_stores() {
     __syncthreads();
 }
 
+// Fence groups per tile whose flags all wavefronts store; those past them are stored by one.  4 / 16 / 64, whole layer, us: 8 destinations
+// level; 4096 tokens x 8 of 128 experts with 64 destinations 750 / 723 / 630, by ready queue x 8 of 64 with 128 630 / 618 / 575, with 512
+// 967 / 957 / 920: the last tile of a layer completes every destination, so with many of them a larger number is worth having.
 constexpr int kLeadGroups = 16;
 constexpr int kMaxWorkgroups = 512;  // of the megakernel
 constexpr int kWgStats = 32;         // words of a workgroup's report: MOE_NUM_STATS, then the tick of its start

@@ -78,7 +78,10 @@ __host__ __device__ inline bool plan_all_fits(int E, int R, int nPB) {
 __host__ __device__ inline size_t plan_all_smem_bytes(int E, int R, int nPB) {
     return ((size_t)nPB * E + 2 * (size_t)E * R + 2 * (R + 1) + 4) * 4 + (size_t)E * 12 + 64;  // (+ a permutation block's masks and bases)
 }
-constexpr int kPlanSlots = 8192;  // slots a workgroup counts by itself: 32 per thread
+// Slots a workgroup counts by itself, 32 per thread.  Whole layer, us, histograms / choices: pre-routed x 1 of 8 experts 6016 slots 115 / 95,
+// 8192 101 / 99, 12032 150 / 113, 16384 139 / 140; x 2 of 16 6016 121 / 116, 8192 114 / 119, 12032 149 / 145, 16384 166 / 174; x 8 of 128 4352
+// 176 / 179, 8192 195 / 199, 8704 208 / 213, 16384 235 / 241: 5 % or more one way or the other on few experts, always 2 % dearer on many.
+constexpr int kPlanSlots = 8192;
 struct PlanAll {  // pointers into LDS
     int *hist, *segb, *nfl, *dest, *grp, *off, *rbb, *rsb, *cnt, *rbe, *rse;
     char *perm_lds;
@@ -155,7 +158,9 @@ __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *
     // One height: ceil(rows / BM).  Mixed heights: see plan_task.
     const int lbm = 31 - __clz(a.tl.BM);
     int over = 0;
-    const bool by_wave = R > 16 && E <= 64;  // many destinations, few experts: a wavefront per expert
+    // Many destinations, few experts: a wavefront per expert.  Whole layer of 2048 tokens x 2, us, a thread / a wavefront: R 1024 E 4 288 / 268,
+    // R 256 E 16 211 / 208, R 64 E 16 138 / 138, R 64 E 64 129 / 131, R 32 E 64 115 / 116; past the limits R 8 E 64 98 / 101, R 32 E 128 137 / 142.
+    const bool by_wave = R > 16 && E <= 64;
     if (by_wave) {
         for (int e = wave; e < E; e += 4) {
             int carry = 0;
@@ -218,7 +223,8 @@ __device__ __forceinline__ int plan_all_tables(const KArgs &a, PlanAll &p, int *
 // the permutation blocks and flag ranges of the others (4 to 8 us: a task, its stores through to memory, the poll) comes behind
 // GEMM1, where it is over.  16-bit slots; scratch: masks and bases of all token blocks, in the GEMM region.
 // Limit, kPermSlots: whole layer, us, waiting -> this: 8 tokens x 8 of 128 experts 133.5 -> 128.7, 128 x 8 of 128 249.5 -> 243.1,
-// 128 x 8 of 32 571 -> 564, 16 x 2 of 8 in f32 99.6 -> 96.1; at 1740 to 4096 slots the masks take what the wait took (435 x 4 of
+// 128 x 8 of 32 571 -> 564, 16 x 2 of 8 in f32 99.6 -> 96.1; x 8 of 128 experts of 2048 x 256 146 -> 143.5 at 1024 slots, 150 -> 147 at 1088, 157 -> 154
+// at 2048; x 4 of 32 93.5 -> 91 at 1024, 99 -> 97 at 1744, 103 -> 103 at 2048; at more slots the masks take what the wait took (435 x 4 of
 // 20 411 -> 415, 392 x 6 of 31 284 -> 287, 512 x 8 of 128 581 -> 584).
 constexpr int kPermSlots = 1024;
 constexpr size_t kPermScratch = 32 * 1024;

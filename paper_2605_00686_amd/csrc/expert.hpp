@@ -519,6 +519,9 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
                         // writer before it was counted
                         fence_acquire(0);
                         fence_release(sys);  // the one fence of this group
+                        // (many flags: by all wavefronts below.  From 256 / 1024 / 4096 flags on / never, whole layer, us: 128 tokens x 8 of
+                        // 128 experts 265 / 265 / 271 / 271, 4096 x 8 of 128 548 / 548 / 549 / 559, 4096 x 2 of 16 with 64 destinations
+                        // 139 / 143 / 143 / 143; the other way, by ready queue, 4096 x 8 of 64 with 512 destinations 972 / 990 / 972 / 952)
                         if (ge - gb >= 256 && n_lead < kLeadGroups) {
                             if (lane == 0) sl->lead[n_lead][0] = gb, sl->lead[n_lead][1] = ge;
                             ++n_lead;
@@ -1148,7 +1151,9 @@ __device__ __forceinline__ void combine_stage(const KArgs &a, char *smem) {
 // ticket has been written, run it (a GEMM2 tile or a combine task) and draw the next ticket
 // while it runs; else run a GEMM1 tile (big before small, own XCD's list first); else sleep.
 // So ready tasks go before new GEMM1 tiles, GEMM2 tiles and combine tasks start in the order
-// in which their inputs became complete, and nothing that runs ever waits.  No deadlock,
+// in which their inputs became complete, and nothing that runs waits, except that a combine task
+// may have to poll flags that are just being stored: the leader of a fence group enqueues the tasks and
+// then stores the group's flags, with nothing to wait for in between (see publish_tile).  No deadlock,
 // whatever the grid size: a workgroup sleeps only when every GEMM1 tile has been handed out,
 // and then every entry still to be written will be written by a workgroup that is running a
 // tile; every ticket below the queue's size is held by a workgroup that runs its entry as

@@ -260,7 +260,7 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
         for (int i = tid; i < TOK * a.E; i += kThreads) lg[i] = all[min(i, (a.T - t0) * a.E - 1)];
         __syncthreads();
     }
-    if (a.E <= 64) {  // the rank of every logit, a thread each (a fixed 64 steps of LDS reads; the bisection takes about 2 us more)
+    if (a.E <= 64) {  // the rank of every logit, a thread each (E steps of LDS reads; the bisection takes about 2 us more)
         if (tid < TOK * 32) at[tid] = 0x7fffffff;
         __syncthreads();
         for (int i = tid; i < TOK * a.E; i += kThreads) {
