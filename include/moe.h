@@ -148,7 +148,8 @@ typedef struct {
  * stats[6] bounded waits that expired   stats[7] device status (a moe_status_t, 0 = ok)
  * stats[8..13] in-kernel timeline: nanoseconds from the start of the first workgroup to the end of
  *   the last gate task [8], the plan [9], the last permutation block [10], the last
- *   GEMM1 tile [11], the last GEMM2 tile [12], the last combine task [13]
+ *   GEMM1 tile [11], the last GEMM2 tile [12], the last combine task [13]; 0 for a phase that has
+ *   no tasks (the gate, when the routing is an input and few enough for the plan to count it)
  * stats[14] nanoseconds workgroups spent waiting on dependencies (each wait counted once per
  *   workgroup, by its clock from the first poll to the last), summed over workgroups
  * stats[15] workgroups launched
