@@ -362,7 +362,7 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, KArgsAddr args, u32 smem_
 // column block of tile_n columns); each has its own ready flag.
 //   PER_TILE: for every publish tile in turn: write it, barrier, release fence, flag
 //             (the coupled PUT -> FENCE -> SIGNAL of section 2.3).
-//   PER_DEST: write the whole compute tile, one release so the rows may be counted,
+//   PER_DEST: write the whole compute tile, wait until its rows are in memory (written through) and may be counted,
 //             add the publish tiles to the counter of their fence group (Algorithm 1,
 //             phase 1; a group is all flags of a destination, or group_size consecutive
 //             ones: the granularity knob of section 4.1).  Whoever completes a group's
