@@ -129,7 +129,7 @@ struct KArgs {
     u32 *gate_parts;           // [blocks] tasks finished per block of gate_tok tokens
     u32 *dest_done;            // [R] flags stored so far per destination (ready-queue scheduler), else NULL
     u32 *rq_slots;             // [8][rq_cap] ready-queue entries, 0 = empty (ready-queue scheduler), else NULL
-    int rq_cap;                // entries per ready queue: all GEMM2 tiles plus all combine tasks
+    int rq_cap;                // entries per ready queue: all GEMM2 tiles (parts of them, where they are cut) plus all combine tasks
     u64 *wg_stats;             // [workgroups][kWgStats] what each workgroup of the megakernel has to report (see StageLds)
     size_t zero_bytes;         // bytes from ctrl that must be zero between calls
     int tab_lds_off;           // megakernel: LDS offset of the cached decode tables, 0 = none
@@ -137,6 +137,10 @@ struct KArgs {
     int plan_from_idx;         // ... and from the choices instead of block histograms
     int perm_lds_off;          // megakernel: LDS offset of the workgroup's own copy of perm (16 bits per slot), 0 = none, GEMM1 reads the global one
     int sched_lds_off;         // megakernel: LDS offset of the task loops' broadcast slots (StageLds)
+    int g2_split;              // GEMM2 tasks per tile, each a part of the reduction (fp32 layers of few tiles), else 1
+    int g2_rows;               // split GEMM2: rows of a part's sums in g2_partial
+    float *g2_partial;         // ... [tiles][g2_split][g2_rows][TileF32::BN]
+    Counter *g2_parts;         // ... [tiles] parts finished
 };
 
 __device__ __forceinline__ u64 now_ticks() { return wall_clock64(); }

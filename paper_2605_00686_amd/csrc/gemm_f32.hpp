@@ -18,6 +18,9 @@
 
 namespace moe {
 
+constexpr int kG2MaxParts = 8;      // of a GEMM2 tile, see g2_part
+constexpr int kG2SplitTiles = 128;  // most tiles of a layer that cuts them (their counters have a cache line each)
+
 struct TileF32 {
     static constexpr int BM = 128, BN = 64;
     static constexpr int BN_NARROW = 32;               // GEMM1 tiles of a layer that has too few of 64 columns (see make_plan)

@@ -500,6 +500,8 @@ static_assert(kGateParts >= kGateSplitBlocks && kGateParts >= kDirectSplitTokens
 
 // LM: 256-row tiles plus a 128-row tile for short tails; S: 32-row tiles; S2: 64-row tiles, and 32-row ones for experts of no
 // more rows than that; FS / FM: row blocks of the fused FFN (32 / 64 rows)
+constexpr int kG2MinPart = 128;  // reduction indices of a part of a split fp32 GEMM2 tile, at least
+
 enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S2 = 2, TK_S = 3, TK_FS = 4, TK_FM = 5 };
 
 struct Plan {
@@ -515,6 +517,8 @@ struct Plan {
     size_t o_blk_base, o_seg_begin, o_flag_base, o_dest_flag_begin, o_dest_group_begin, o_rb_base, o_rb_expert, o_rbs_base, o_rbs_expert, o_h, total;
     size_t o_wgt, o_wg_stats;
     int gate_tok;  // tokens per gate task
+    int g2_split, g2_rows;  // see g2_part
+    size_t o_g2_partial, o_g2_parts;
 };
 
 static int make_plan(const moe_problem_t *p, Plan *pl) {
@@ -595,6 +599,21 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
         pl->tl.BN2 = 256;
     }
     if (p->fuse_ffn && p->dtype != MOE_DT_BF16) return MOE_ERR_UNSUPPORTED;
+    // fp32 layers of few GEMM2 tiles: as many parts per tile as there are CUs for (256), of at least kG2MinPart reduction indices.
+    // (By the problem's shape alone: the sums, and so the results, are the same under both schedulers.)
+    pl->g2_split = 1;
+    pl->g2_rows = pl->N < TileF32::BM ? pl->N : TileF32::BM;
+    long long g2_tiles = 0;  // at most
+    if (p->dtype == MOE_DT_F32) {
+        const long long nt2 = (p->d + TileF32::BN - 1) / TileF32::BN, experts = pl->N < p->E ? pl->N : p->E;
+        g2_tiles = (pl->N / bm + experts) * nt2;
+        const long long likely = experts * (avg / bm + 1) * nt2;
+        long long S = 256 / likely;
+        if (S > kG2MaxParts) S = kG2MaxParts;
+        if (S > p->f / kG2MinPart) S = p->f / kG2MinPart;
+        if (S > 1 && g2_tiles <= kG2SplitTiles) pl->g2_split = (int)S;
+    }
+    if (pl->g2_split == 1) g2_tiles = 0;
     pl->tl.BMS = pl->kind == TK_LM ? CfgM::BM : pl->kind == TK_S2 ? CfgS::BM : 0;
     // few rows per expert: the layer streams weights (measured: about -1 % on cfg2; +2 to 4 % on cfg3 and cfg4,
     // which have thousands of rows per expert and are bound by the matrix cores, if it were applied there)
@@ -621,6 +640,7 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     pl->o_h_ready = take((size_t)pl->maxRB_layout * 4);
     pl->o_dest_done = take((size_t)p->R * 4);
     pl->o_gate_parts = take((size_t)kGateParts * 4);
+    pl->o_g2_parts = take((size_t)g2_tiles * sizeof(Counter));
     pl->zero_bytes = o;
     // What follows is zero between calls because its users leave it so (moe_workspace_init zeroes it
     // once).  Sizes are the largest any signal mode, group size or scheduler needs, so that the
@@ -629,9 +649,9 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     const size_t max_flags = ((size_t)(pl->N + tm - 1) / tm + (size_t)p->E * p->R) * pl->ncb;
     const size_t spread = (size_t)p->R * kGroupStride;  // (a counter per destination has a cache line to itself)
     pl->o_group_counter = take((max_flags + p->R > spread ? max_flags + p->R : spread) * 4);
-    // One ready queue per XCD, each able to hold every GEMM2 tile and every combine task (at most
+    // One ready queue per XCD, each able to hold every GEMM2 tile (or part of one) and every combine task (at most
     // one per token).
-    pl->rq_cap = (pl->tl.maxRB + p->E) * pl->tl.NT2 + p->T;
+    pl->rq_cap = (pl->tl.maxRB + p->E) * pl->tl.NT2 * pl->g2_split + p->T;
     pl->o_rq_slots = take((size_t)kTileQueues * pl->rq_cap * 4);
     pl->init_zero_bytes = o;
     pl->o_blk_base = take((size_t)pl->nPB * p->E * 4);
@@ -649,6 +669,7 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
     // (and the logits of one split by experts: bf16 problems of few tokens)
     pl->o_gate_partial = take(p->dtype == MOE_DT_F32 ? (size_t)kGateSplitTasks * kRouteTokens * p->E * 8
                                                      : (size_t)(p->T < kDirectSplitTokens ? p->T : kDirectSplitTokens) * p->E * 8);
+    pl->o_g2_partial = take((size_t)g2_tiles * pl->g2_split * pl->g2_rows * TileF32::BN * 4);
     // transposed gate weights (bf16 problems; unused when the routing is an input)
     pl->o_wgt = take(p->dtype == MOE_DT_BF16 ? (size_t)p->E * p->d * 2 : 0);
     pl->total = o;
@@ -671,6 +692,7 @@ static void fill_args(const Plan &pl, void *workspace, KArgs *a) {
     a->seg_from_blocks = (pl.per_dest % kPermBlock == 0) ? 1 : 0;
     a->disp_tokens = scatter_tokens(p.T);
     a->tl = pl.tl;
+    a->g2_split = 1;  // (the megakernel splits: see there)
     a->gate_tok = pl.gate_tok;
     a->t_gate = 0;  // the megakernel adds the transposition tasks when it has a bf16 gate to compute
     a->t_plan = pl.nRT;
@@ -1102,6 +1124,13 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     const int extra = gate_tasks - pl.nRT + a.t_gate;
     a.nRT = gate_tasks;
     a.t_plan += extra; a.t_perm += extra; a.t_g1 += extra; a.t_end += extra;
+    if (pl.g2_split > 1) {
+        a.g2_split = pl.g2_split;
+        a.g2_rows = pl.g2_rows;
+        a.g2_partial = (float *)((char *)workspace + pl.o_g2_partial);
+        a.g2_parts = (Counter *)((char *)workspace + pl.o_g2_parts);
+        a.t_end += (pl.tl.maxRB + p->E) * pl.tl.NT2 * (pl.g2_split - 1);
+    }
     hipStream_t st = (hipStream_t)stream;
     switch (pl.kind) {
         case TK_F32: return launch_mega<F32Policy, F32Policy>(pl, a, st);
