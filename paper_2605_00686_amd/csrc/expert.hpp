@@ -15,6 +15,11 @@ using CfgL = TileCfg<4, 4, 2, 2, 32, 4>;  // 256 x 256, wavefront 128 x 128
 using CfgM = TileCfg<2, 4, 2, 2, 64, 3>;  // 128 x 256, wavefront  64 x 128
 using CfgS = TileCfg<1, 2, 1, 4, 64, 4>;  //  32 x 256, wavefront  32 x  64, deep pipeline: weight streaming
 using CfgS2 = TileCfg<2, 2, 1, 4, 64, 3>; //  64 x 256, wavefront  64 x  64: the same for experts of more than 32 rows
+// heights between these for row blocks with fewer rows than their tile (see short_gemm): wavefront all rows x 64
+using CfgR3 = TileCfg<3, 2, 1, 4, 64, 3>;
+using CfgR5 = TileCfg<5, 2, 1, 4, 32, 5>;
+using CfgR6 = TileCfg<6, 2, 1, 4, 32, 5>;
+using CfgR7 = TileCfg<7, 2, 1, 4, 32, 4>;
 
 // ---- GEMM policies: element type + tile shape + main loop
 template <class C>
@@ -25,7 +30,7 @@ struct Bf16Policy {
     static constexpr int BM = C::BM, BN1 = C::BN / 2, BN2 = C::BN;
     static constexpr int C_STRIDE = C::C_STRIDE;
     // row blocks of at most this many rows run a smaller main loop on the tile's LDS (see short_gemm), 0: none do
-    static constexpr int SHORT_ROWS = C::BM == CfgL::BM ? CfgM::BM : 0;
+    static constexpr int SHORT_ROWS = C::BM == CfgL::BM ? CfgR7::BM : C::BM == CfgM::BM ? CfgR3::BM : 0;
     static constexpr int SMEM_MAIN = C::BM == CfgL::BM && C::SMEM_MAIN < CfgM::SMEM_MAIN ? CfgM::SMEM_MAIN : C::SMEM_MAIN;
     // wavefronts per SIMD the kernel is built for: two workgroups per CU where their LDS fits
     static constexpr int MIN_WAVES = (2 * (C::SMEM_MAIN + 8 * 1024) <= 160 * 1024) ? 2 : 1;
@@ -311,7 +316,7 @@ __device__ __forceinline__ void store_c_tile(const char *c_tile, int c_stride, i
 }
 
 template <class P, bool GATED>
-static __device__ void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols);
+__device__ __forceinline__ void short_block(KArgsAddr args, u32 smem_off, const TileInfo &ti);
 
 // GEMM1 + SwiGLU: h[rows of the block, n0 .. n0+ncols) = silu(x W1[e]) * (x W3[e]).
 // Rows are gathered straight from x through perm: the permuted activations are
@@ -338,7 +343,7 @@ __device__ __forceinline__ u32 g1_tile(const KArgs &a, KArgsAddr args, u32 smem_
     using ET = typename P::ET;
     MOE_TT_BEGIN();
     if (P::SHORT_ROWS != 0 && ti.nrows <= P::SHORT_ROWS)
-        short_gemm<P, true>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols);
+        short_block<P, true>(args, smem_off, ti);
     else
         g1_gemm<P>(a, ti, smem);
     after_gemm();
@@ -621,7 +626,7 @@ template <class P, class Hook>
 __device__ __forceinline__ void g2_tile(const KArgs &a, KArgsAddr args, u32 smem_off, const TileInfo &ti, char *smem, Hook after_gemm) {
     MOE_TT_BEGIN();
     if (P::SHORT_ROWS != 0 && ti.nrows <= P::SHORT_ROWS)
-        short_gemm<P, false>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols);
+        short_block<P, false>(args, smem_off, ti);
     else
         g2_gemm<P, P>(a, ti, smem);
     after_gemm();
@@ -630,28 +635,42 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, KArgsAddr args, u32 smem
     MOE_TT(a.ctrl, 8);
 }
 
-// The main loop of a 256-row block with at most 128 rows in it (an expert's tail, under tail_with_big): the 128-row or the 64-row
-// loop.  The C tile has the same layout, so everything behind it is the big tile's.  Cycles per 32 reduction steps: 1250 / 770 /
-// about 500.  Whole layer, us, before -> after: 4096 tokens x 8 of 128 experts 569 -> 556, the same by ready queue 400 -> 394;
-// 32 experts of 2048 x 2048, 257 rows each, 399 -> 352.  A call, not inlined: with the loops inside the stage the 256-row loop had
-// scalar spills in it (layers without such blocks +0.5 to 0.9 %).  A 64-row loop for the 128-row blocks of few rows: +0.4 % on
-// layers of 125 rows per expert, taken out.
+// The main loop of a 256-row block with at most 224 rows, or of a 128-row one with at most 96: the loop of the next height, PX, of
+// 32, 64, 96, 128, 160, 192 and 224 rows.  The C tile has the same layout, so everything behind it is the big tile's.  A stage of 32
+// reduction indices takes 1250 cycles with 256 rows, about 230 + 128 per 32 rows with fewer (770 with 128, 500 with 64).  Calls, not inlined:
+// with the loops inside the stage the 256-row loop had scalar spills in it (layers without such blocks +0.5 to 0.9 %); and
+// with the address of a local, which keeps them from being tail calls (see k_megakernel): as such they saved and restored 72 to
+// 198 registers per lane through scratch memory.  Whole layer, us, only 64 and 128 rows with those saves -> this: 4096 tokens x 8 of 128
+// experts of 2048 x 768 575 -> 565, 4096 x 4 of 128 of 2880 x 2880 1555 -> 1493, by ready queue 2048 x 8 of 64 of 2048 x 1024 416 -> 407; of 2048 x 1408
+// 80 rows each 301 -> 298, 144 379 -> 356; of 2048 x 1024 160 rows 319 -> 298, 218 347 -> 337; 1001 x 6 of 48 of 1024 x 1408 188 -> 182.
+template <class P, class PX, bool GATED>
+static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols,
+                                                            volatile int *caller_local) {
+    static_assert(PX::SMEM_MAIN <= P::SMEM_MAIN, "on the tile's LDS");
+    *caller_local = 6;
+    KArgs a = load_kernel_args(args);
+    mark_global(a);
+    char *smem = lds_at((u32)uniform((int)smem_off));
+    TileInfo ti{};
+    ti.e = uniform(e), ti.row0 = uniform(row0), ti.nrows = uniform(nrows), ti.lrow0 = uniform(lrow0);
+    ti.n0 = uniform(n0), ti.ncols = uniform(ncols), ti.valid = true;
+    if constexpr (GATED) g1_gemm<PX>(a, ti, smem); else g2_gemm<PX, P>(a, ti, smem);
+}
 template <class P, bool GATED>
-static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols) {
+__device__ __forceinline__ void short_block(KArgsAddr args, u32 smem_off, const TileInfo &ti) {
     if constexpr (P::SHORT_ROWS != 0) {
-        KArgs a = load_kernel_args(args);
-        mark_global(a);
-        char *smem = lds_at((u32)uniform((int)smem_off));
-        TileInfo ti{};
-        ti.e = uniform(e), ti.row0 = uniform(row0), ti.nrows = uniform(nrows), ti.lrow0 = uniform(lrow0);
-        ti.n0 = uniform(n0), ti.ncols = uniform(ncols), ti.valid = true;
-        using PM = Bf16Policy<CfgM>;
-        using PS = Bf16Policy<CfgS2>;
-        static_assert(PS::SMEM_MAIN <= P::SMEM_MAIN && PM::SMEM_MAIN <= P::SMEM_MAIN, "on the tile's LDS");
-        if (ti.nrows <= PS::BM) {
-            if constexpr (GATED) g1_gemm<PS>(a, ti, smem); else g2_gemm<PS, P>(a, ti, smem);
-        } else {
-            if constexpr (GATED) g1_gemm<PM>(a, ti, smem); else g2_gemm<PM, P>(a, ti, smem);
+        volatile int mark = 0;
+        auto run = [&](auto policy) __attribute__((always_inline)) {
+            short_gemm<P, decltype(policy), GATED>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols, &mark);
+        };
+        if (ti.nrows <= CfgS::BM) return run(Bf16Policy<CfgS>());
+        if (ti.nrows <= CfgS2::BM) return run(Bf16Policy<CfgS2>());
+        if (ti.nrows <= CfgR3::BM) return run(Bf16Policy<CfgR3>());
+        if constexpr (P::SHORT_ROWS > CfgR3::BM) {
+            if (ti.nrows <= CfgM::BM) return run(Bf16Policy<CfgM>());
+            if (ti.nrows <= CfgR5::BM) return run(Bf16Policy<CfgR5>());
+            if (ti.nrows <= CfgR6::BM) return run(Bf16Policy<CfgR6>());
+            run(Bf16Policy<CfgR7>());
         }
     }
 }
