@@ -1257,7 +1257,10 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
     while (true) {
         __syncthreads();
         if (tid < 64) {
-            // lanes 0-7: big GEMM1 list of XCD home + lane; 8-15: its small one; 24: error flag
+            // lanes 0-7: big GEMM1 list of XCD home + lane; 8-15: its small one; 24: error flag; 32: the entry of the ticket, in the
+            // same trip to memory
+            u32 entry = 0u;
+            if (tid == 32 && ticket >= 0 && ticket < a.rq_cap) entry = ld_relaxed_agent(&a.rq_slots[(size_t)q * a.rq_cap + ticket]);
             const int kind = tid >> 3, qq = (home + (tid & 7)) % kTileQueues;
             bool has = false;
             if (g1_left && (kind == 0 || (kind == 1 && MIXED))) {
@@ -1267,7 +1270,9 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
                 has = ld_relaxed_agent(&c->error.v) != 0u;
             }
             const u64 m = __ballot(has);
+            entry = (u32)__builtin_amdgcn_readlane((int)entry, 32);
             if (tid == 0) {
+                const int had = ticket, had_q = q;
                 // a ticket beyond its queue's size says the queue is used up: on to the next one
                 if (ticket >= 0 && ticket >= ready_queue_size(a, n_rb, n_rbs, q, parts)) ticket = -1, q = (q + 1) % kTileQueues, ++hops;
                 while (ticket < 0 && hops < kTileQueues) {
@@ -1275,7 +1280,7 @@ __device__ __forceinline__ void ready_queue_stage(const KArgs &a, KArgsAddr karg
                     if (ticket >= ready_queue_size(a, n_rb, n_rbs, q, parts)) ticket = -1, q = (q + 1) % kTileQueues, ++hops;
                 }
                 u32 *slot = &a.rq_slots[(size_t)q * a.rq_cap + (ticket >= 0 ? ticket : 0)];
-                const u32 v = ticket >= 0 ? ld_relaxed_agent(slot) : 0u;
+                const u32 v = ticket < 0 ? 0u : ticket == had && q == had_q ? entry : ld_relaxed_agent(slot);
                 int pick = 0, val = 0, lq = 0;  // pick: -2 leave, 0 sleep, 1 ready task, 2 / 3 big / small GEMM1 tile, 4 look again
                 if ((m >> 24) & 1ull) {
                     pick = -2;
