@@ -6,7 +6,8 @@
 // bytes of a row) and every RL-th group of four rows, the next 8 rows' loads in flight while it multiplies these on the vector
 // ALU (bf16 products are exact in fp64; its fp64 rate is the matrix cores').  The threads' partial sums meet in LDS.  In the
 // megakernel the experts are cut into parts where that keeps more CUs busy; the part that finishes last selects.
-// Bound: the conversions to fp64 (about 20 cycles per wavefront and weight) and the products (4 per token).
+// Bound: three instructions per weight (shift or mask, conversion to fp64, which runs at full rate, and the product; one more per
+// further token), of 5.5 cycles each with one wavefront per SIMD, and the chain of steps around them.
 #pragma once
 #include "common.hpp"
 #include "gate.hpp"
@@ -17,13 +18,21 @@ constexpr int kGateDirect = 7;  // this gate's number among the gate variants (s
 constexpr int kDirectTokens = 4;
 constexpr int kDirectSplitTokens = 128;           // more tokens are one task per CU, or nearly, as they are
 constexpr int kDirectMaxParts = 8;
+// Partial sums of a logit from which on the standalone gate adds them up in two steps (inside the layer, where few-token tasks have
+// as many, it made no difference).  moe_route of 1024 tokens x 16 experts of d 512 7.8 -> 7.0 us, 300 x 8 of 512 8.9 -> 6.2.
+constexpr int kDirectRuns = 64;
+// Threads of a task of the standalone gate: two wavefronts per SIMD where there are enough weights for them, 256 / 512 threads, us: 128 tokens x 128
+// experts of d 7168 44.0 / 38.8, 256 x 256 of 4096 49.4 / 43.5, 1024 x 128 of 2048 28.0 / 27.0, 128 x 32 of 7168 15.7 / 14.3; the other way 1024 x 24 of
+// 4096 17.1 / 18.2, 1024 x 16 of 512 7.8 / 9.3.  (No warming of the L2 in either: it is a trip to memory before the first load, and the
+// tasks' own loads find each other's lines; 8 tokens x 128 of 2048 19.7 -> 16.9, 8 x 256 of 4096 54.7 -> 42.3.)
+__host__ __device__ inline int direct_threads_alone(int E, int d) { return (long long)E * d > 1 << 17 ? 512 : 256; }
 constexpr size_t kDirectLds = 96 * 1024;  // of a task's tokens as fp32
 __host__ __device__ inline int direct_tokens(int T) { return T <= 256 ? 1 : T <= 512 ? 2 : kDirectTokens; }
 // Whether a gate takes this form (x and Wg may start anywhere: the loads accept any address).  Gate end inside the layer, the screen's / this one's,
 // us: E 128, d 2048 8 tokens 29 / 17, 128 30 / 22, 512 31 / 29, 513 31 / 40; E 32, d 7168 128 tokens 41 / 21, 512 47 / 27; E 48, d 1024 1024 tokens
 // 26 / 19; E 64, d 2048 256 24 / 18, 513 28 / 31; E 128, d 7168 512 71 / 61; E 256, d 4096 256 60 / 56, 512 62 / 67; E 256, d 2048 512 42 / 41; E 128,
-// d 512 1024 27 / 23.  Alone (the screen goes over the weights twice there): E 128, d 2048 8 tokens 37 / 19, 1024 38 / 29; E 256, d 2048 1024
-// tokens 54 / 46; E 256, d 4096 1024 85 / 83.
+// d 512 1024 27 / 23.  Alone (the screen goes over the weights twice there): E 128, d 2048 8 tokens 37 / 17, 1024 38 / 27; E 256, d 2048 1024
+// tokens 54 / 43; E 256, d 4096 1024 85 / 83.
 __host__ __device__ inline bool gate_is_direct(int T, int E, int d, bool alone) {
     const long long work = (long long)E * d, most = T <= 256 || (T <= 512 && E <= 128) ? 1 << 20 : T <= 512 || alone ? 1 << 19 : 1 << 16;
     return E % 8 == 0 && T <= 256 * kDirectTokens && (size_t)direct_tokens(T) * d * 4 <= kDirectLds && work <= most;
@@ -39,10 +48,10 @@ __host__ __device__ inline int direct_parts(int T, int E, int d) {
 }
 // Threads that share a piece's column: as many as the largest part has room for, in every part, so that every expert's sum has
 // the same order.  Experts with the same weights have the same logit then, and the lower id comes first.
-__host__ __device__ inline int direct_threads(int E, int parts) { return kThreads / ((E / 8 + parts - 1) / parts); }
-__host__ __device__ inline size_t direct_lds_bytes(int E, int d) {
+__host__ __device__ inline int direct_threads(int E, int parts, int threads) { return threads / ((E / 8 + parts - 1) / parts); }
+__host__ __device__ inline size_t direct_lds_bytes(int E, int d, int threads) {
     const size_t rows = (size_t)kDirectTokens * d * 4 < kDirectLds ? (size_t)kDirectTokens * d * 4 : kDirectLds;
-    const size_t part = (size_t)kDirectTokens * 256 * 64;
+    const size_t part = (size_t)kDirectTokens * threads * 64;
     return kMaxExperts * 4 + (rows > part ? rows : part) + (size_t)kDirectTokens * E * 8 + kDirectTokens * 32 * 4;
 }
 
@@ -144,7 +153,8 @@ __device__ __forceinline__ void select_wave(const KArgs &a, int t, const double 
 }
 
 // Part `slice` of S of a task (the experts are cut by pieces of 8 into S parts): tokens [t0, t0 + TOK): idx and w written, choices counted in cnt (LDS, zeroed) if do_hist.  lds: behind cnt, 16-byte aligned.
-template <int TOK>
+// NT: threads of the workgroup.  ALONE: the standalone gate's.
+template <int TOK, int NT, bool ALONE>
 __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, int S, char *lds, int *cnt, bool do_hist) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.d;
@@ -172,7 +182,7 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
     };
     load(wa, 0);
     // the tokens' rows, as fp32
-    for (int q = tid; q < TOK * d / 8; q += kThreads) {
+    for (int q = tid; q < TOK * d / 8; q += NT) {
         const int t = q / (d / 8), c = q - t * (d / 8);
         const u32x4_t v = load16_unaligned((const char *)a.x + (size_t)min(t0 + t, a.T - 1) * d * 2, 16u * (u32)c);
         f32x4_t lo, hi;
@@ -233,18 +243,33 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
             for (int c = 0; c < 8; ++c) part[(rl * TOK + t) * E + 8 * p + c] = acc[t][c];
     }
     __syncthreads();
-    for (int i = tid; i < TOK * E; i += kThreads) {
+    // The RL partial sums of a logit: many of them in 2, 4, 8 or 16 runs first, a thread each, whose sums take the place of a run's first
+    const int n_out = TOK * E;
+    const int lr = !ALONE || RL < kDirectRuns || 2 * n_out > NT ? 0 : min(4, 31 - __clz(NT / n_out)), runs = 1 << lr;  // (RL >= 64 > runs)
+    if (lr > 0) {
+        const int g = tid / n_out, i = tid - g * n_out;
+        if (g < runs) {
+            const int r0 = RL * g >> lr, r1 = RL * (g + 1) >> lr;
+            double v = 0.0;
+#pragma unroll 8
+            for (int r = r0; r < r1; ++r) v += part[r * n_out + i];
+            part[r0 * n_out + i] = v;
+        }
+        __syncthreads();
+    }
+    for (int i = tid; i < n_out; i += NT) {
         const double s = a.bias ? (double)a.bias[8 * p0 + i % E] : 0.0;
         double v = 0.0;
+        const int n = lr > 0 ? runs : RL, step = lr > 0 ? RL : 1;
 #pragma unroll 8
-        for (int r = 0; r < RL; ++r) v += part[r * TOK * E + i];
+        for (int r = 0; r < n; ++r) v += part[(step * r >> lr) * n_out + i];
         lg[i] = s + v;
     }
     __syncthreads();
     MOE_TT(a.ctrl, 45);
     if (S > 1) {  // the other parts' logits: whichever part of the block finishes last goes on
         double *all = a.gate_partial + (size_t)t0 * a.E;  // [tokens][E]
-        for (int i = tid; i < TOK * E; i += kThreads) {
+        for (int i = tid; i < TOK * E; i += NT) {
             const int t = i / E;
             if (t0 + t < a.T) store_through(&all[(size_t)t * a.E + 8 * p0 + i - t * E], lg[i]);
         }
@@ -257,13 +282,13 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
         const bool last = uniform(at[0]) != 0;
         __syncthreads();
         if (!last) return;
-        for (int i = tid; i < TOK * a.E; i += kThreads) lg[i] = all[min(i, (a.T - t0) * a.E - 1)];
+        for (int i = tid; i < TOK * a.E; i += NT) lg[i] = all[min(i, (a.T - t0) * a.E - 1)];
         __syncthreads();
     }
     if (a.E <= 64) {  // the rank of every logit, a thread each (E steps of LDS reads; the bisection takes about 2 us more)
         if (tid < TOK * 32) at[tid] = 0x7fffffff;
         __syncthreads();
-        for (int i = tid; i < TOK * a.E; i += kThreads) {
+        for (int i = tid; i < TOK * a.E; i += NT) {
             const int t = i / a.E, e = i - t * a.E;
             const double v = lg[i];
             int rank = 0;
@@ -275,14 +300,14 @@ __device__ __forceinline__ void route_direct(const KArgs &a, int t0, int slice, 
             if (rank < a.k) atomicMin(&at[t * 32 + rank], e);
         }
         __syncthreads();
-        for (int t = wave; t < TOK; t += 4) {
+        for (int t = wave; t < TOK; t += NT / 64) {
             const int found = lane < a.k ? at[t * 32 + lane] : 0x7fffffff, e = found < a.E ? found : -1;
             finish_token(a, t0 + t, e, e >= 0 ? lg[t * a.E + e] : -__builtin_huge_val(), cnt, do_hist);
         }
         return;
     }
     // a wavefront per token
-    for (int t = wave; t < TOK; t += 4) select_wave(a, t0 + t, lg + t * a.E, at + t * 32, (double *)lds + t * 32, cnt, do_hist);
+    for (int t = wave; t < TOK; t += NT / 64) select_wave(a, t0 + t, lg + t * a.E, at + t * 32, (double *)lds + t * 32, cnt, do_hist);
 }
 
 }  // namespace moe

@@ -20,13 +20,12 @@ __global__ __launch_bounds__(kThreads) void k_zero(u32 *p, size_t n) {
         p[i] = 0u;
 }
 
-template <typename ET, int V>
-__global__ __launch_bounds__(kThreads, 1) void k_route(KArgs a, int do_hist) {
+template <typename ET, int V, int NT>
+__global__ __launch_bounds__(NT, 1) void k_route(KArgs a, int do_hist) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int s_slot;
-    if constexpr (V > 0) gate_warm_l2(a, lds_offset(smem + (V == kGateDirect ? kMaxExperts * 4 : GateCfg<V == kGateDirect ? 1 : V>::O_EXACT)), blockIdx.x, gridDim.x);
-    if constexpr (V == kGateDirect) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (its rows take the place the loads go to)
-    route_task<ET, V, false>(a, kernel_args_address(), blockIdx.x, smem, do_hist != 0, &s_slot, [] { return false; });
+    if constexpr (V > 0 && V != kGateDirect) gate_warm_l2(a, lds_offset(smem + GateCfg<V == kGateDirect ? 1 : V>::O_EXACT), blockIdx.x, gridDim.x);
+    route_task<ET, V, false, NT>(a, kernel_args_address(), blockIdx.x, smem, do_hist != 0, &s_slot, [] { return false; });
 }
 
 __global__ __launch_bounds__(kThreads) void k_plan(KArgs a) {
@@ -243,7 +242,7 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     }
     bool seen_wgt = false;
     while (task < a.t_plan) {
-        route_task<ET, V, true>(a, args, task - a.t_gate, smem, a.plan_from_idx == 0, &sl->pick, [&]() __attribute__((always_inline)) {
+        route_task<ET, V, true, kThreads>(a, args, task - a.t_gate, smem, a.plan_from_idx == 0, &sl->pick, [&]() __attribute__((always_inline)) {
             if (!seen_wgt) seen_wgt = wait_for(&c->wgt_done.v, (u32)a.t_gate) != 0;  // the transposed gate weights are complete
             return seen_wgt;
         });
@@ -748,7 +747,7 @@ static void set_gate(KArgs *a, const void *x, const void *Wg, const float *bias,
     a->gate_rows_aligned = (a->E & 7) == 0 && ((uintptr_t)Wg & 15) == 0;
     // few tokens: see gate_direct.hpp; its tasks have other sizes than the screen's
     if (Wg && a->dtype == MOE_DT_BF16 && gate_is_direct(a->T, a->E, a->d, alone)) {
-        a->gate_direct = direct_threads(a->E, 1);
+        a->gate_direct = direct_threads(a->E, 1, alone ? direct_threads_alone(a->E, a->d) : kThreads);
         a->gate_tok = direct_tokens(a->T);
         a->nRT = (a->T + a->gate_tok - 1) / a->gate_tok;
     }
@@ -953,24 +952,28 @@ int moe_route(const moe_problem_t *p, const void *x, const void *Wg, const float
     fill_args(pl, nullptr, &a);
     set_gate(&a, x, Wg, gate_bias, true);
     a.idx = topk_idx; a.w = topk_w;
-    const size_t smem = gate_task_smem_bytes(p->E, p->d, elem_size(p->dtype));
+    size_t smem = gate_task_smem_bytes(p->E, p->d, elem_size(p->dtype));
     hipStream_t st = (hipStream_t)stream;
-    auto launch = [&](auto kern) {
+    auto launch = [&](auto kern, int threads = kThreads) {
         const int rc2 = set_smem(kern, smem);
         if (rc2) return rc2;
-        hipLaunchKernelGGL(kern, dim3(a.nRT), dim3(kThreads), smem, st, a, 0);
+        hipLaunchKernelGGL(kern, dim3(a.nRT), dim3(threads), smem, st, a, 0);
         return hip_ok(hipGetLastError());
     };
-    if (p->dtype == MOE_DT_F32) return launch(k_route<float, 0>);
-    if (a.gate_direct) return launch(k_route<bf16_t, kGateDirect>);
-    if (route_exact(p->T, p->E, p->d)) return launch(k_route<bf16_t, 0>);
+    if (p->dtype == MOE_DT_F32) return launch(k_route<float, 0, kThreads>);
+    if (a.gate_direct) {
+        const int threads = direct_threads_alone(p->E, p->d);
+        smem = direct_lds_bytes(p->E, p->d, threads);
+        return threads == 512 ? launch(k_route<bf16_t, kGateDirect, 512>, 512) : launch(k_route<bf16_t, kGateDirect, kThreads>);
+    }
+    if (route_exact(p->T, p->E, p->d)) return launch(k_route<bf16_t, 0, kThreads>);
     switch (gate_variant(p->E, p->d)) {
-        case 1: return launch(k_route<bf16_t, 1>);
-        case 2: return launch(k_route<bf16_t, 2>);
-        case 3: return launch(k_route<bf16_t, 3>);
-        case 4: return launch(k_route<bf16_t, 4>);
-        case 6: return launch(k_route<bf16_t, 6>);
-        default: return launch(k_route<bf16_t, 5>);
+        case 1: return launch(k_route<bf16_t, 1, kThreads>);
+        case 2: return launch(k_route<bf16_t, 2, kThreads>);
+        case 3: return launch(k_route<bf16_t, 3, kThreads>);
+        case 4: return launch(k_route<bf16_t, 4, kThreads>);
+        case 6: return launch(k_route<bf16_t, 6, kThreads>);
+        default: return launch(k_route<bf16_t, 5, kThreads>);
     }
 }
 
@@ -1025,11 +1028,11 @@ static int dispatch_launches(const Plan &pl, const KArgs &a, bool short_only, hi
     if ((rc = set_smem(k_plan, psmem))) return rc;
     // histogram (gate task without the gate), plan, permutation, row gather, clean-up
     if (p->dtype == MOE_DT_F32) {
-        hipLaunchKernelGGL((k_route<float, 0>), dim3(pl.nPB), dim3(kThreads), kMaxExperts * 4, st, a, 1);
+        hipLaunchKernelGGL((k_route<float, 0, kThreads>), dim3(pl.nPB), dim3(kThreads), kMaxExperts * 4, st, a, 1);
         hipLaunchKernelGGL(k_plan, dim3(1), dim3(kThreads), psmem, st, a);
         hipLaunchKernelGGL(k_perm<float>, dim3(pl.nPB), dim3(kThreads), (size_t)p->E * 8, st, a);
     } else {
-        hipLaunchKernelGGL((k_route<float, 0>), dim3(pl.nPB), dim3(kThreads), kMaxExperts * 4, st, a, 1);
+        hipLaunchKernelGGL((k_route<float, 0, kThreads>), dim3(pl.nPB), dim3(kThreads), kMaxExperts * 4, st, a, 1);
         hipLaunchKernelGGL(k_plan, dim3(1), dim3(kThreads), psmem, st, a);
         hipLaunchKernelGGL(k_perm<bf16_t>, dim3(pl.nPB), dim3(kThreads), (size_t)p->E * 8, st, a);
     }
@@ -1112,7 +1115,7 @@ int moe_megakernel_forward(const moe_problem_t *p, const void *x, const void *Wg
     }
     if (a.gate_direct && direct_parts(p->T, p->E, p->d) > 1) {
         a.gate_split = direct_parts(p->T, p->E, p->d);
-        a.gate_direct = direct_threads(p->E, a.gate_split);
+        a.gate_direct = direct_threads(p->E, a.gate_split, kThreads);
         gate_tasks = a.nRT * a.gate_split;
         a.gate_partial = (double *)((char *)workspace + pl.o_gate_partial);
         a.gate_parts = (u32 *)((char *)workspace + pl.o_gate_parts);

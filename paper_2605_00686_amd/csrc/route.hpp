@@ -403,7 +403,7 @@ static __device__ __attribute__((noinline)) void route_fallback(KArgsAddr args, 
 __host__ __device__ inline size_t gate_task_smem_bytes(int E, int d, int elem_size) {
     const size_t full = (size_t)kMaxExperts * 4 + route_smem_bytes(E, elem_size);
     const size_t screened = elem_size == 2 ? (size_t)gate_screened_lds(gate_variant(E, d)) : 0;
-    const size_t direct = elem_size == 2 ? direct_lds_bytes(E, d) : 0;
+    const size_t direct = elem_size == 2 ? direct_lds_bytes(E, d, kThreads) : 0;
     const size_t most = full > screened ? full : screened;
     return most > direct ? most : direct;
 }
@@ -415,8 +415,8 @@ __host__ __device__ inline size_t gate_task_smem_bytes(int E, int d, int elem_si
 // of the reduction and leaves its partial logits in the workspace; whichever task of a block
 // finishes last adds the S partial sums in slice order (so the result does not depend on who that
 // is) and goes on to the selection; the others are done.  s_slot: an int in LDS outside `smem`.
-// WGT, wgt_ready: see route_screened.
-template <typename ET, int V, bool WGT, class WgtReady>
+// WGT, wgt_ready: see route_screened.  NT: threads of the workgroup.
+template <typename ET, int V, bool WGT, int NT, class WgtReady>
 __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int task, char *smem, bool do_hist, int *s_slot,
                                            WgtReady wgt_ready) {
     const int E = a.E, k = a.k;
@@ -428,17 +428,17 @@ __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int t
     const int t0 = block * TOK;
     int *cnt = (int *)smem;  // [E] choices of the task's tokens per expert
     char *lds = smem + kMaxExperts * 4;
-    for (int e = threadIdx.x; e < E; e += kThreads) cnt[e] = 0;
+    for (int e = threadIdx.x; e < E; e += NT) cnt[e] = 0;
     __syncthreads();
     MOE_TT_BEGIN();
     if (compute) {
         if constexpr (V == kGateDirect) {
             if (TOK == 1)
-                route_direct<1>(a, t0, slice, S, lds, cnt, do_hist);
+                route_direct<1, NT, !WGT>(a, t0, slice, S, lds, cnt, do_hist);
             else if (TOK == 2)
-                route_direct<2>(a, t0, slice, S, lds, cnt, do_hist);
+                route_direct<2, NT, !WGT>(a, t0, slice, S, lds, cnt, do_hist);
             else
-                route_direct<kDirectTokens>(a, t0, slice, S, lds, cnt, do_hist);
+                route_direct<kDirectTokens, NT, !WGT>(a, t0, slice, S, lds, cnt, do_hist);
         } else if constexpr (V > 0) {
             if (!a.gate_screens || !route_screened<V, WGT>(a, t0, TOK, smem, do_hist, wgt_ready)) {
                 route_fallback(args, lds_offset(smem), t0, TOK, do_hist ? 1 : 0);
