@@ -499,9 +499,28 @@ static_assert(kGateParts >= kGateSplitBlocks && kGateParts >= kDirectSplitTokens
 
 // LM: 256-row tiles plus a 128-row tile for short tails; S: 32-row tiles; S2: 64-row tiles, and 32-row ones for experts of no
 // more rows than that; FS / FM: row blocks of the fused FFN (32 / 64 rows)
-constexpr int kG2MinPart = 128;  // reduction indices of a part of a split fp32 GEMM2 tile, at least
-
 enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S2 = 2, TK_S = 3, TK_FS = 4, TK_FM = 5 };
+
+// Parts of an fp32 GEMM2 tile (see g2_part) where `tiles` tiles are likely: as many as there are CUs for (256), and no more than pay for
+// what a part costs, which is to be drawn, counted and added up.  A tile's length is its reduction times the 32-row blocks an expert
+// is likely to have, half of one more than its average fills; the fewer tiles there are, the shorter a part may be.  At most 32, 64
+// and more tiles, us, whole / this many parts / one more step: 128 tokens x 2 of 4 experts of 512 x 512 77.4 / 73.3 / 74.2, 4 x 2
+// of 4 of 512 x 768 58.3 / 57.4 / 57.7, of 512 x 512 53.1 / - / 54.8; 256 x 2 of 8 of 512 x 512 82.4 / 81.6 / 83.5, 16 x 2 of 8 of
+// 512 x 1024 66.9 / 66.1 / 66.2, of 512 x 768 63.5 / - / 64.7; 128 x 1 of 8 of 768 x 2048 92.7 / 86.0 / 94.5, of 768 x 768 72.1 / - / 72.9, 1 x 2 of 2
+// of 4096 x 1024 99.6 / - / 101.4.  Parts of 128 indices wherever CUs were left took 16 x 2 of 8 of 512 x 512 from 58.5 to 63.8.
+// (By the problem's shape alone: the sums, and so the results, are the same under both schedulers.)
+static int g2_parts_of_tile(const moe_problem_t *p, int avg, long long tiles) {
+    constexpr int kMinPart = 128;  // reduction indices
+    const int rows = (avg < TileF32::BM ? avg : TileF32::BM) + 16;
+    const long long length = (long long)p->f * (rows > 32 ? rows : 32) / 32;
+    const int shortest = tiles <= 32 ? 256 : tiles <= 64 ? 512 : 768;
+    if (length < 3 * 256) return 1;
+    long long S = 256 / tiles;
+    if (S > kG2MaxParts) S = kG2MaxParts;
+    if (S > p->f / kMinPart) S = p->f / kMinPart;
+    if (S > length / shortest) S = length / shortest;
+    return S > 1 ? (int)S : 1;
+}
 
 struct Plan {
     moe_problem_t p;
@@ -598,19 +617,14 @@ static int make_plan(const moe_problem_t *p, Plan *pl) {
         pl->tl.BN2 = 256;
     }
     if (p->fuse_ffn && p->dtype != MOE_DT_BF16) return MOE_ERR_UNSUPPORTED;
-    // fp32 layers of few GEMM2 tiles: as many parts per tile as there are CUs for (256), of at least kG2MinPart reduction indices.
-    // (By the problem's shape alone: the sums, and so the results, are the same under both schedulers.)
+    // fp32 layers of few GEMM2 tiles cut them along the reduction (kG2SplitTiles bounds the tiles there can be)
     pl->g2_split = 1;
     pl->g2_rows = pl->N < TileF32::BM ? pl->N : TileF32::BM;
     long long g2_tiles = 0;  // at most
     if (p->dtype == MOE_DT_F32) {
         const long long nt2 = (p->d + TileF32::BN - 1) / TileF32::BN, experts = pl->N < p->E ? pl->N : p->E;
         g2_tiles = (pl->N / bm + experts) * nt2;
-        const long long likely = experts * (avg / bm + 1) * nt2;
-        long long S = 256 / likely;
-        if (S > kG2MaxParts) S = kG2MaxParts;
-        if (S > p->f / kG2MinPart) S = p->f / kG2MinPart;
-        if (S > 1 && g2_tiles <= kG2SplitTiles) pl->g2_split = (int)S;
+        if (g2_tiles <= kG2SplitTiles) pl->g2_split = g2_parts_of_tile(p, avg, experts * (avg / bm + 1) * nt2);
     }
     if (pl->g2_split == 1) g2_tiles = 0;
     pl->tl.BMS = pl->kind == TK_LM ? CfgM::BM : pl->kind == TK_S2 ? CfgS::BM : 0;
