@@ -16,7 +16,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) u32 u32x4_t;  // 16 bytes in registers
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 
-constexpr int kThreads = 256;       // every kernel here runs 4 wavefronts per workgroup
+constexpr int kThreads = 256;       // 4 wavefronts per workgroup in every kernel but the standalone gate of few tokens (direct_threads_alone)
 constexpr int kPermBlock = 64;      // tokens per permutation block (one bit each in a 64-bit mask)
 constexpr int kRouteTokens = 16;    // tokens per gate task, at most
 constexpr int kMaxExperts = 256;    // gate / plan limits

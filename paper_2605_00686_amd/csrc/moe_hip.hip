@@ -24,7 +24,7 @@ template <typename ET, int V, int NT>
 __global__ __launch_bounds__(NT, 1) void k_route(KArgs a, int do_hist) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int s_slot;
-    if constexpr (V > 0 && V != kGateDirect) gate_warm_l2(a, lds_offset(smem + GateCfg<V == kGateDirect ? 1 : V>::O_EXACT), blockIdx.x, gridDim.x);
+    if constexpr (V > 0 && V != kGateDirect) gate_warm_l2(a, lds_offset(smem + GateCfg<V>::O_EXACT), blockIdx.x, gridDim.x);
     route_task<ET, V, false, NT>(a, kernel_args_address(), blockIdx.x, smem, do_hist != 0, &s_slot, [] { return false; });
 }
 

@@ -419,6 +419,7 @@ __host__ __device__ inline size_t gate_task_smem_bytes(int E, int d, int elem_si
 template <typename ET, int V, bool WGT, int NT, class WgtReady>
 __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int task, char *smem, bool do_hist, int *s_slot,
                                            WgtReady wgt_ready) {
+    static_assert(NT == kThreads || V == kGateDirect, "the other gates' tasks are written for kThreads threads");
     const int E = a.E, k = a.k;
     // (the megakernel's bf16 problems with a gate have V > 0)
     const bool compute = (V > 0 || !WGT || sizeof(ET) == 4) && a.Wg != nullptr;
@@ -491,7 +492,7 @@ __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int t
             select_full(a, t0, TOK, (const double *)lds, cnt, do_hist);
         }
     } else {
-        for (int q = threadIdx.x; q < TOK * k; q += kThreads) {
+        for (int q = threadIdx.x; q < TOK * k; q += NT) {
             const int t = t0 + q / k;
             if (t < a.T) count_choice(a, cnt, t, a.idx[(size_t)t0 * k + q]);
         }
@@ -502,7 +503,7 @@ __device__ __forceinline__ void route_task(const KArgs &a, KArgsAddr args, int t
         // whenever destinations are whole blocks; else they were counted slot by slot.
         __syncthreads();
         int32_t *bh = a.blk_hist + (size_t)(t0 / kPermBlock) * E;
-        for (int e = threadIdx.x; e < E; e += kThreads)
+        for (int e = threadIdx.x; e < E; e += NT)
             if (cnt[e] != 0) atomicAdd(&bh[e], cnt[e]);
     }
     MOE_TT(a.ctrl, 33);
