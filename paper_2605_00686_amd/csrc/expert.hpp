@@ -643,10 +643,10 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, KArgsAddr args, u32 smem
 // 198 registers per lane through scratch memory.  Whole layer, us, only 64 and 128 rows with those saves -> this: 4096 tokens x 8 of 128
 // experts of 2048 x 768 575 -> 565, 4096 x 4 of 128 of 2880 x 2880 1555 -> 1493, by ready queue 2048 x 8 of 64 of 2048 x 1024 416 -> 407; of 2048 x 1408
 // 80 rows each 301 -> 298, 144 379 -> 356; of 2048 x 1024 160 rows 319 -> 298, 218 347 -> 337; 1001 x 6 of 48 of 1024 x 1408 188 -> 182.
-template <class P, class PX, bool GATED>
+// PT: the tile whose bookkeeping GEMM2 prepares; GEMM1, which has none, is the same function for every tile (PT = PX).
+template <class PT, class PX, bool GATED>
 static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols,
                                                             volatile int *caller_local) {
-    static_assert(PX::SMEM_MAIN <= P::SMEM_MAIN, "on the tile's LDS");
     *caller_local = 6;
     KArgs a = load_kernel_args(args);
     mark_global(a);
@@ -654,14 +654,16 @@ static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 
     TileInfo ti{};
     ti.e = uniform(e), ti.row0 = uniform(row0), ti.nrows = uniform(nrows), ti.lrow0 = uniform(lrow0);
     ti.n0 = uniform(n0), ti.ncols = uniform(ncols), ti.valid = true;
-    if constexpr (GATED) g1_gemm<PX>(a, ti, smem); else g2_gemm<PX, P>(a, ti, smem);
+    if constexpr (GATED) g1_gemm<PX>(a, ti, smem); else g2_gemm<PX, PT>(a, ti, smem);
 }
 template <class P, bool GATED>
 __device__ __forceinline__ void short_block(KArgsAddr args, u32 smem_off, const TileInfo &ti) {
     if constexpr (P::SHORT_ROWS != 0) {
         volatile int mark = 0;
         auto run = [&](auto policy) __attribute__((always_inline)) {
-            short_gemm<P, decltype(policy), GATED>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols, &mark);
+            using PX = decltype(policy);
+            static_assert(PX::SMEM_MAIN <= P::SMEM_MAIN, "on the tile's LDS");
+            short_gemm<std::conditional_t<GATED, PX, P>, PX, GATED>(args, smem_off, ti.e, ti.row0, ti.nrows, ti.lrow0, ti.n0, ti.ncols, &mark);
         };
         if (ti.nrows <= CfgS::BM) return run(Bf16Policy<CfgS>());
         if (ti.nrows <= CfgS2::BM) return run(Bf16Policy<CfgS2>());
