@@ -30,3 +30,9 @@ def workspace_growth(T, d, E, k, f, capacity=0):
         tiles = most_tiles(T, d, E, k)
         growth += up(tiles * 128) + up(tiles * S * min(N, BM) * BN * 4)
     return growth
+
+
+def combine_tasks(T, R):
+    """Combine tasks under the ready-queue scheduler: equal shares of every destination's tokens where twice as many tasks make them equal."""
+    per_dest, want = T // R, -(-(T // R) // -(-T // CUS))
+    return R * next((n for n in range(want, min(2 * want, per_dest) + 1) if per_dest % n == 0), want)
