@@ -18,6 +18,12 @@ def is_direct(T, E, d, alone):
     return E % 8 == 0 and T <= 1024 and direct_tokens(T) * d * 4 <= 96 * 1024 and E * d <= most
 
 
+def direct_sums_alone(T, E, d):
+    """Of the standalone direct gate: threads of a task, and in how many runs the partial sums of a logit are added up."""
+    threads, n = (512 if E * d > 1 << 17 else 256), direct_tokens(T) * E
+    return threads, 1 if threads // (E // 8) < 64 or 2 * n > threads else min(16, 1 << (threads // n).bit_length() - 1)
+
+
 def direct_parts(T, E, d):
     """Parts, by experts, of a task of the direct gate inside the layer."""
     if T > 128 or E * d < 1 << 18:

@@ -1,7 +1,7 @@
 """The gate tests run the forms of the gate that they name: both of the bf16 gate's rules (alone and in the layer), applied to their
 lists of cases."""
 from tests import gate_forms as G
-from tests import test_gpu_gate, test_gpu_gate_direct, test_gpu_gate_many_candidates, test_gpu_gate_nonfinite
+from tests import test_gpu_gate, test_gpu_gate_direct, test_gpu_gate_direct_alone, test_gpu_gate_many_candidates, test_gpu_gate_nonfinite
 
 FOUR_TOKENS = {("screen", v, 4) for v in (1, 2, 3, 4, 5, 6)}
 
@@ -38,6 +38,9 @@ def test_numbers_that_are_not_finite_reach_every_form():
     assert {f[2] for f in layer if f != "direct"} == {4, 8, 16}
     screens = {f for f in alone if f not in ("direct", "exact")}
     assert {f[1] for f in screens} == {1, 2, 3, 4, 5, 6} and {f[2] for f in screens} >= {8, 16}
+    sums = {(G.direct_tokens(T), *G.direct_sums_alone(T, E, d)) for T, d, E, k in cases if G.is_direct(T, E, d, True)}
+    assert {t for t, threads, _ in sums if threads == 512} == {1, 2, 4}
+    assert {(threads, runs > 1) for _, threads, runs in sums} == {(256, False), (256, True), (512, False), (512, True)}
 
 
 def test_equal_logits_reach_every_form():
@@ -59,3 +62,11 @@ def test_direct_gate_cases_are_direct_and_some_parts_uneven():
             pieces = G.part_pieces(E, G.direct_parts(T, E, d))
             uneven += min(pieces) != max(pieces)
     assert uneven >= 4
+
+
+def test_standalone_direct_gate_cases_have_every_number_of_threads_and_runs():
+    cases = test_gpu_gate_direct_alone.CASES
+    assert all(G.is_direct(T, E, d, True) for T, d, E, k in cases)
+    sums = {G.direct_sums_alone(T, E, d) for T, d, E, k in cases}
+    assert {threads for threads, _ in sums} == {256, 512} and {runs for _, runs in sums} == {1, 2, 4, 8, 16}
+    assert {E * d for T, d, E, k in cases} >= {1 << 17, (1 << 17) + 4096}  # either side of the rule

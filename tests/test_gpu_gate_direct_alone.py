@@ -11,7 +11,8 @@ from tests import gate_forms, parity
 pytestmark = pytest.mark.gpu
 
 CASES = [(5, 16384, 16, 4), (300, 8192, 24, 8), (520, 6144, 32, 8), (1024, 1024, 136, 8), (1, 1024, 136, 3), (7, 2048, 64, 8), (7, 2112, 64, 8),
-         (513, 2048, 64, 6), (257, 8192, 8, 2), (600, 64, 8, 8), (1000, 512, 16, 5), (33, 128, 248, 32)]
+         (513, 2048, 64, 6), (257, 8192, 8, 2), (600, 64, 8, 8), (1000, 512, 16, 5), (33, 128, 248, 32),
+         (600, 4096, 40, 4)]
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES, ids=["T%d_d%d_E%d_k%d" % c for c in CASES])

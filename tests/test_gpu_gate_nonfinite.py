@@ -102,11 +102,13 @@ def test_exact_gate_of_more_than_64_experts(E, k, kind):
 
 # (T, d, E, k): every code variant of the screen and tasks of 4, 8 and 16 tokens in the layer (the variants and 8 and 16 tokens alone too),
 # rows of Wg off 16 bytes; experts few enough that all of a token's could pass as candidates, and more; and the direct gate of few
-# tokens, which has neither screen nor fallback (see tests/test_gate_forms.py, which checks that each is here)
+# tokens, which has neither screen nor fallback, standalone with 256 and 512 threads and with either way of adding up (see
+# tests/test_gate_forms.py, which checks that each is here)
 BF16_CASES = [(37, 1152, 8, 2), (9, 1088, 16, 4), (37, 320, 48, 8), (2050, 576, 48, 6), (70, 192, 64, 8), (1030, 256, 64, 3), (37, 128, 65, 8),
               (37, 128, 128, 8), (33, 128, 192, 8), (40, 128, 256, 5),
               (600, 4096, 24, 4), (600, 2112, 32, 4), (520, 1088, 64, 8), (600, 576, 128, 8), (600, 448, 192, 8), (520, 320, 256, 5),
-              (1030, 1152, 16, 2), (2050, 2112, 16, 4), (1030, 192, 128, 8), (1030, 128, 192, 8), (1030, 128, 256, 5)]
+              (1030, 1152, 16, 2), (2050, 2112, 16, 4), (1030, 192, 128, 8), (1030, 128, 192, 8), (1030, 128, 256, 5),
+              (33, 2048, 128, 8), (300, 8192, 24, 8), (600, 4096, 40, 4)]
 
 
 @pytest.mark.parametrize("kind", KINDS)
