@@ -15,7 +15,7 @@ using CfgL = TileCfg<4, 4, 2, 2, 32, 4>;  // 256 x 256, wavefront 128 x 128
 using CfgM = TileCfg<2, 4, 2, 2, 64, 3>;  // 128 x 256, wavefront  64 x 128
 using CfgS = TileCfg<1, 2, 1, 4, 64, 4>;  //  32 x 256, wavefront  32 x  64, deep pipeline: weight streaming
 using CfgS2 = TileCfg<2, 2, 1, 4, 64, 3>; //  64 x 256, wavefront  64 x  64: the same for experts of more than 32 rows
-// heights between these for row blocks with fewer rows than their tile (see short_gemm): wavefront all rows x 64
+// heights between these for row blocks with fewer rows than their tile (see short_gemm): wavefront all rows x 64, as S and S2
 using CfgR3 = TileCfg<3, 2, 1, 4, 64, 3>;
 using CfgR5 = TileCfg<5, 2, 1, 4, 32, 5>;
 using CfgR6 = TileCfg<6, 2, 1, 4, 32, 5>;
@@ -573,7 +573,7 @@ __device__ __forceinline__ void g2_gemm(const KArgs &a, const TileInfo &ti, char
 // has CUs, and a tile is as long as its reduction (64 rows x 64 columns x 1024: 14 us of matrix-core time alone).  The parts' sums meet in
 // the workspace; whichever part finishes last adds them up in part order, so that the result does not depend on who that is, and
 // publishes.  Returns whether this was the part that did.  256 tokens x 2 of 8 experts of 512 x 1024 (64 tiles, 4 parts): from the end of
-// GEMM1 to that of GEMM2 35 -> 29 us, whole layer 98 -> 91 us.
+// GEMM1 to that of GEMM2 35 -> 28 us, whole layer 95.2 -> 91.6 us.
 template <class P, class Hook>
 __device__ __forceinline__ bool g2_part(const KArgs &a, const TileInfo &ti, int part, char *smem, Hook after_gemm) {
     const int tid = threadIdx.x, S = a.g2_split, P8 = a.f / 8;
@@ -640,9 +640,10 @@ __device__ __forceinline__ void g2_tile(const KArgs &a, KArgsAddr args, u32 smem
 // reduction indices takes 1250 cycles with 256 rows, about 230 + 128 per 32 rows with fewer (770 with 128, 500 with 64).  Calls, not inlined:
 // with the loops inside the stage the 256-row loop had scalar spills in it (layers without such blocks +0.5 to 0.9 %); and
 // with the address of a local, which keeps them from being tail calls (see k_megakernel): as such they saved and restored 72 to
-// 198 registers per lane through scratch memory.  Whole layer, us, only 64 and 128 rows with those saves -> this: 4096 tokens x 8 of 128
-// experts of 2048 x 768 575 -> 565, 4096 x 4 of 128 of 2880 x 2880 1555 -> 1493, by ready queue 2048 x 8 of 64 of 2048 x 1024 416 -> 407; of 2048 x 1408
-// 80 rows each 301 -> 298, 144 379 -> 356; of 2048 x 1024 160 rows 319 -> 298, 218 347 -> 337; 1001 x 6 of 48 of 1024 x 1408 188 -> 182.
+// 198 registers per lane through scratch memory.  Whole layer, us, loops of 64 and 128 rows with those saves / without them / all heights:
+// 4096 tokens x 8 of 128 experts of 2048 x 768 563 / 560 / 549, 4096 x 4 of 128 of 2880 x 2880 1502 / 1503 / 1476, by ready queue 2048 x 8 of 64
+// of 2048 x 1024 411 / 404 / 397, 1001 x 6 of 48 of 1024 x 1408 184.9 / 185.6 / 180.3 (this one 1 % slower to 3 % faster, box by
+// box); both steps, experts of 2048 x 1408 with 80 rows each 301 -> 298, 144 379 -> 356; of 2048 x 1024 with 160 319 -> 298, 218 347 -> 337.
 // PT: the tile whose bookkeeping GEMM2 prepares; GEMM1, which has none, is the same function for every tile (PT = PX).
 template <class PT, class PX, bool GATED>
 static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 smem_off, int e, int row0, int nrows, int lrow0, int n0, int ncols,

@@ -77,7 +77,7 @@ __device__ __forceinline__ void gemm_rows_f32(RowPtr rowptr, const float *B0, co
                                               char *smem, Hook while_loading) {
     using C = TileF32;
     // pieces in flight per wavefront: what the registers beside the sums hold (in the forms of 3 and 4 row blocks not all of it:
-    // the compiler reports 36 spilled vector registers for the fp32 megakernel, and around the exchange sums go to scratch)
+    // the compiler reports 42 spilled vector registers for the fp32 megakernel, and around the exchange sums go to scratch)
     constexpr int DEPTH = ROWS <= 2 ? 8 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;

@@ -200,6 +200,8 @@ static __device__ __attribute__((noinline)) int front_stage(KArgsAddr args, u32 
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     *caller_local = 5;  // (see the call sites of tile_stage)
     if (tid == 0) sl->next = (int)atomicAdd(&c->next_task.v, 1u);
+    // (Before the direct gate too, unlike alone: without it, in two builds that differ in where the code lies, 8 tokens x 8 of 128 experts of 2048 x 768
+    // level and 1.7 % slower, 128 x 8 of 128 0.9 % slower and 0.2 % faster, 128 x 8 of 32 of 7168 x 2048 0.2 and 0.4 % slower, 1001 x 6 of 48 level and 0.5 % slower.)
     if constexpr (V > 0) {
         gate_warm_l2(a, lds_offset(smem + kMaxExperts * 4), blockIdx.x, gridDim.x);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
