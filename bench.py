@@ -36,8 +36,8 @@ SECONDARY_WORKLOAD = "cfg2"
 # WRITE_SIZE, each scaled by what the counter reads for a plain copy of known size).  Not measured by this
 # script: taken from the named summary under profiles/; a workload without one reports null.
 MEASURED_TRAFFIC = {
-    "cfg2": (2.097e9, "profiles/megakernel_cfg2_hbm_traffic.txt"),
-    "cfg4": (2.140e10, "profiles/megakernel_cfg4_hbm_traffic.txt"),
+    "cfg2": (2.046e9, "profiles/megakernel_cfg2_hbm_traffic.txt"),
+    "cfg4": (2.253e10, "profiles/megakernel_cfg4_hbm_traffic.txt"),
 }
 
 
