@@ -1,5 +1,6 @@
 """Where the functions of a layer's kernel lie in the built library: a kernel directly behind the tile stages that it calls, so that a
-call of one layer fetches its code, cold behind the weights of the call before, from one stretch of memory."""
+call of one layer fetches its code, cold behind the weights of the call before, from one stretch of memory; every function at the start of
+a cache line, so that code elsewhere does not move it against the lines."""
 import re
 import struct
 import subprocess
@@ -45,3 +46,7 @@ def test_a_kernel_lies_behind_its_stages():
         assert "tile_stage<" in name or "fused_stage<" in name, (fns[i][2], name)
         assert fns[i][0] - (before + size) < 256, fns[i][2]  # (kernels start on 256 bytes)
         assert re.search(r"\w+Policy(<moe::TileCfg<[^>]*>)?", name).group(0) in fns[i][2], (fns[i][2], name)
+
+
+def test_functions_start_on_a_cache_line():
+    assert all(address % 128 == 0 for address, _, name in device_functions() if "moe::" in name)
