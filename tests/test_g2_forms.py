@@ -4,7 +4,7 @@ import pytest
 
 from paper_2605_00686_amd import binding as B
 from tests import g2_forms as G
-from tests import test_gpu_g2_split
+from tests import test_gpu_g2_parts
 
 # (T, d, E, k, f): parts
 PARTS = {(256, 512, 8, 2, 1024): 4, (256, 512, 8, 2, 512): 2, (256, 512, 8, 2, 256): 1,
@@ -27,6 +27,6 @@ def test_parts_of_a_tile(shape):
 
 
 def test_the_gpu_cases_are_cut_as_they_say():
-    cases = test_gpu_g2_split.CASES
+    cases = test_gpu_g2_parts.CASES
     assert all(G.parts(*c[:5]) == n for c, n in cases.items()) and set(cases.values()) == set(range(1, 9))
     assert {G.most_tiles(*c[:4]): n > 1 for c, n in cases.items()}.items() >= {128: True, 136: False}.items()

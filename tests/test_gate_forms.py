@@ -38,9 +38,6 @@ def test_numbers_that_are_not_finite_reach_every_form():
     assert {f[2] for f in layer if f != "direct"} == {4, 8, 16}
     screens = {f for f in alone if f not in ("direct", "exact")}
     assert {f[1] for f in screens} == {1, 2, 3, 4, 5, 6} and {f[2] for f in screens} >= {8, 16}
-    sums = {(G.direct_tokens(T), *G.direct_sums_alone(T, E, d)) for T, d, E, k in cases if G.is_direct(T, E, d, True)}
-    assert {t for t, threads, _ in sums if threads == 512} == {1, 2, 4}
-    assert {(threads, runs > 1) for _, threads, runs in sums} == {(256, False), (256, True), (512, False), (512, True)}
 
 
 def test_equal_logits_reach_every_form():
@@ -70,3 +67,10 @@ def test_standalone_direct_gate_cases_have_every_number_of_threads_and_runs():
     sums = {G.direct_sums_alone(T, E, d) for T, d, E, k in cases}
     assert {threads for threads, _ in sums} == {256, 512} and {runs for _, runs in sums} == {1, 2, 4, 8, 16}
     assert {E * d for T, d, E, k in cases} >= {1 << 17, (1 << 17) + 4096}  # either side of the rule
+
+
+def test_numbers_that_are_not_finite_reach_the_standalone_direct_gate_with_either_number_of_threads():
+    cases = test_gpu_gate_nonfinite.BF16_CASES
+    sums = {(G.direct_tokens(T), *G.direct_sums_alone(T, E, d)) for T, d, E, k in cases if G.is_direct(T, E, d, True)}
+    assert {t for t, threads, _ in sums if threads == 512} == {1, 2, 4}
+    assert {(threads, runs > 1) for _, threads, runs in sums} == {(256, False), (256, True), (512, False), (512, True)}
