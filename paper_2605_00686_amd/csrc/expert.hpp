@@ -187,7 +187,7 @@ __device__ __forceinline__ TileInfo decode_block_tile(const KArgs &a, const Tabl
 // counter from which consumers draw tickets: ticket t is the right, and the duty, to run entry t
 // of that queue, whenever it gets written.  A consumer empties the entry it ran, so the array is
 // all zero again after the call.  An entry is 1 + (row block * NT2 + column tile) * parts + part for a GEMM2 tile, or
-// a part of one where the reduction is cut (see g2_part; row blocks numbered as in h_ready), or kReadyCombine | task for a combine task.
+// a part of one where the reduction is cut (see g2_join; row blocks numbered as in h_ready), or kReadyCombine | task for a combine task.
 constexpr u32 kReadyCombine = 0x80000000u;
 // entries queue q receives in this call; parts: entries per GEMM2 tile
 __device__ __forceinline__ int ready_queue_size(const KArgs &a, int n_rb, int n_rbs, int q, int parts) {
@@ -561,28 +561,23 @@ __device__ void publish_tile(const KArgs &a, const TileInfo &ti, char *smem) {
 // GEMM2 + publish: y[rows of the block, n0 .. n0+ncols) = h W2[e], written to
 // staging row perm[p] (the slot that asked for it).  The caller has already
 // waited for the block's h rows.
-template <class P, class PT>
-__device__ __forceinline__ void g2_gemm(const KArgs &a, const TileInfo &ti, char *smem) {
-    using ET = typename P::ET;
-    const ET *h = (const ET *)a.h;
-    auto rowptr = [&](int r) { return h + (size_t)(ti.row0 + min(r, ti.nrows - 1)) * a.f; };
-    const ET *B0 = (const ET *)a.W2 + (size_t)ti.e * a.f * a.d + ti.n0;
-    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, ti.nrows, a.f, smem, [&] { publish_prepare<PT>(a, ti, smem); });
-}
-// Part `part` of a GEMM2 tile whose reduction is cut into a.g2_split parts: an fp32 layer of few tokens has fewer tiles than the chip
-// has CUs, and a tile is as long as its reduction (64 rows x 64 columns x 1024: 14 us of matrix-core time alone).  The parts' sums meet in
-// the workspace; whichever part finishes last adds them up in part order, so that the result does not depend on who that is, and
-// publishes.  Returns whether this was the part that did.  256 tokens x 2 of 8 experts of 512 x 1024 (64 tiles, 4 parts): from the end of
-// GEMM1 to that of GEMM2 35 -> 28 us, whole layer 95.2 -> 91.6 us.
+// Reduction indices [k0, k0 + K).  prepare: of the tile's bookkeeping (publish_prepare), called while the first loads are on their way.
 template <class P, class Hook>
-__device__ __forceinline__ bool g2_part(const KArgs &a, const TileInfo &ti, int part, char *smem, Hook after_gemm) {
-    const int tid = threadIdx.x, S = a.g2_split, P8 = a.f / 8;
-    const int k0 = 8 * (int)((long long)P8 * part / S), k1 = 8 * (int)((long long)P8 * (part + 1) / S);
-    const float *h = (const float *)a.h + k0;
+__device__ __forceinline__ void g2_gemm(const KArgs &a, const TileInfo &ti, int k0, int K, char *smem, Hook prepare) {
+    using ET = typename P::ET;
+    const ET *h = (const ET *)a.h + k0;
     auto rowptr = [&](int r) { return h + (size_t)(ti.row0 + min(r, ti.nrows - 1)) * a.f; };
-    const float *B0 = (const float *)a.W2 + ((size_t)ti.e * a.f + k0) * a.d + ti.n0;
-    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, ti.nrows, k1 - k0, smem, [] {});
-    after_gemm();
+    const ET *B0 = (const ET *)a.W2 + ((size_t)ti.e * a.f + k0) * a.d + ti.n0;
+    P::template gemm<false>(rowptr, B0, B0, a.d, ti.ncols, ti.nrows, K, smem, prepare);
+}
+// Behind the main loop of part `part` of a GEMM2 tile whose reduction is cut into S = a.g2_split parts: an fp32 layer of few tokens has
+// fewer tiles than the chip has CUs, and a tile is as long as its reduction (64 rows x 64 columns x 1024: 14 us of matrix-core time alone).
+// The parts' sums meet in the workspace; whichever part finishes last adds them up in part order, so that the result does not depend on
+// who that is, and publishes.  Returns whether this is the part that does.  256 tokens x 2 of 8 experts of 512 x 1024 (64 tiles, 4 parts):
+// from the end of GEMM1 to that of GEMM2 35 -> 28 us, whole layer 95.2 -> 91.6 us.
+template <class P>
+__device__ __forceinline__ bool g2_join(const KArgs &a, const TileInfo &ti, int part, char *smem) {
+    const int tid = threadIdx.x, S = a.g2_split;
     const int tile = ti.rb * a.tl.NT2 + ti.n0 / P::BN2;
     constexpr int ROW = P::BN2 * 4;  // bytes
     const size_t per = (size_t)a.g2_rows * ROW;
@@ -619,20 +614,34 @@ __device__ __forceinline__ bool g2_part(const KArgs &a, const TileInfo &ti, int 
         }
     }
     __syncthreads();
-    publish_tile<P>(a, ti, smem);
     return true;
 }
+// Part `part` of a tile, the whole of it where tiles are not cut; returns whether it published.  (One main loop for both: with one of their
+// own for the parts the fp32 stage had 79 KB of code, not 46; 256 tokens x 2 of 8 experts of 512 x 1024 90.7 -> 89.4 us, 512 fp32 shapes 0.8 %
+// faster where tiles are cut, level where not.)
 template <class P, class Hook>
-__device__ __forceinline__ void g2_tile(const KArgs &a, KArgsAddr args, u32 smem_off, const TileInfo &ti, char *smem, Hook after_gemm) {
+__device__ __forceinline__ bool g2_tile(const KArgs &a, KArgsAddr args, u32 smem_off, const TileInfo &ti, int part, char *smem, Hook after_gemm) {
     MOE_TT_BEGIN();
-    if (P::SHORT_ROWS != 0 && ti.nrows <= P::SHORT_ROWS)
+    const bool cut = P::SPLITS && a.g2_split > 1;
+    if (P::SHORT_ROWS != 0 && ti.nrows <= P::SHORT_ROWS) {
         short_block<P, false>(args, smem_off, ti);
-    else
-        g2_gemm<P, P>(a, ti, smem);
+    } else {
+        int k0 = 0, k1 = a.f;
+        if (cut) {  // (f / 8 pieces times at most kG2MaxParts parts)
+            k0 = 8 * (a.f / 8 * part / a.g2_split);
+            k1 = 8 * (a.f / 8 * (part + 1) / a.g2_split);
+        }
+        g2_gemm<P>(a, ti, k0, k1 - k0, smem, [&] {
+            if (!cut) publish_prepare<P>(a, ti, smem);
+        });
+    }
     after_gemm();
+    if constexpr (P::SPLITS)
+        if (cut && !g2_join<P>(a, ti, part, smem)) return false;
     MOE_TT(a.ctrl, 7);
     publish_tile<P>(a, ti, smem);
     MOE_TT(a.ctrl, 8);
+    return true;
 }
 
 // The main loop of a 256-row block with at most 224 rows, or of a 128-row one with at most 96: the loop of the next height, PX, of
@@ -655,7 +664,7 @@ static __device__ __attribute__((noinline)) void short_gemm(KArgsAddr args, u32 
     TileInfo ti{};
     ti.e = uniform(e), ti.row0 = uniform(row0), ti.nrows = uniform(nrows), ti.lrow0 = uniform(lrow0);
     ti.n0 = uniform(n0), ti.ncols = uniform(ncols), ti.valid = true;
-    if constexpr (GATED) g1_gemm<PX>(a, ti, smem); else g2_gemm<PX, PT>(a, ti, smem);
+    if constexpr (GATED) g1_gemm<PX>(a, ti, smem); else g2_gemm<PX>(a, ti, 0, a.f, smem, [&] { publish_prepare<PT>(a, ti, smem); });
 }
 template <class P, bool GATED>
 __device__ __forceinline__ void short_block(KArgsAddr args, u32 smem_off, const TileInfo &ti) {
@@ -701,7 +710,7 @@ __device__ __forceinline__ int next_list(u64 m) {
 // One kind of tile (GEMM1 if GATED, else GEMM2; big or SMALL row blocks) from the eight tile
 // queues, the one of XCD `home` first, until none is left; or, when one_a >= 0, exactly one
 // tile that the caller has taken already: entry one_b of list one_a (GEMM1), or row block
-// one_a of this kind, column tile (with its part, see g2_part) one_b (GEMM2, whose rows of h are known to be complete).
+// one_a of this kind, column tile (with its part, see g2_join) one_b (GEMM2, whose rows of h are known to be complete).
 // In that case, if ticket_q >= 0, a ticket of ready queue ticket_q is drawn where the list
 // mode draws its next tile, and left in StageLds::next (0x7fffffff: none drawn).
 template <class P, bool GATED, bool SMALL>
@@ -719,7 +728,7 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
     StageLds *sl = (StageLds *)(smem + a.sched_lds_off);
     const Tables tb = decode_tables(a, smem, n_rb, n_rbs);
     constexpr int LIST = (GATED ? 0 : 2) + (SMALL ? 1 : 0);
-    const int g2_parts = P::SPLITS ? a.g2_split : 1;  // entries per GEMM2 tile (see g2_part)
+    const int g2_parts = P::SPLITS ? a.g2_split : 1;  // entries per GEMM2 tile (see g2_join)
     const int parts = GATED ? 1 : g2_parts;
     *caller_local = LIST;  // (see the call sites)
     bool more = true;
@@ -782,21 +791,21 @@ static __device__ __attribute__((noinline)) void tile_stage(KArgsAddr args, u32 
                 }
                 MOE_TT(c, 4);
             } else {
-                const TileInfo ti = single ? decode_block_tile<SMALL>(a, tb, one_a, one_b / parts, P::BN2, a.d)
-                                           : decode_tile<SMALL>(a, tb, tq, i / parts, a.tl.NT2, P::BN2, a.d);
+                int at = single ? one_b : i, part = 0;
+                if (parts > 1) {
+                    part = at % parts;
+                    at /= parts;
+                }
+                const TileInfo ti = single ? decode_block_tile<SMALL>(a, tb, one_a, at, P::BN2, a.d)
+                                           : decode_tile<SMALL>(a, tb, tq, at, a.tl.NT2, P::BN2, a.d);
                 // h rows were stored through to memory by their GEMM1 tiles before those counted themselves
                 if (tid == 0) sl->ok = (single || wait_ge(c, sl, &a.h_ready[ti.rb], (u32)a.tl.NT1, a.wait_ticks)) ? 1 : 0;
                 if (single) fence_acquire(0);
                 __syncthreads();
                 MOE_TT(c, 5);
                 if (sl->ok) {
-                    bool whole = true;
-                    if (parts > 1) {
-                        if constexpr (P::SPLITS) whole = g2_part<P>(a, ti, (single ? one_b : i) % parts, smem, draw);
-                    } else {
-                        g2_tile<P>(a, args, smem_off, ti, smem, draw);
-                    }
-                    if (tid == 0 && whole) sl->stat[5] += 1;
+                    const bool published = g2_tile<P>(a, args, smem_off, ti, part, smem, draw);
+                    if (tid == 0 && published) sl->stat[5] += 1;
                 } else {
                     draw();
                 }

@@ -18,7 +18,7 @@
 
 namespace moe {
 
-// Most parts of a GEMM2 tile, see g2_part: all of a sum's parts are in flight at once.  6 / 8 parts, us: 128 tokens x 2 of 4 experts of 128 x 2048
+// Most parts of a GEMM2 tile, see g2_join: all of a sum's parts are in flight at once.  6 / 8 parts, us: 128 tokens x 2 of 4 experts of 128 x 2048
 // 71.5 / 69.3, of 512 x 2048 85.9 / 85.3, 64 x 2 of 4 of 512 x 4096 92.1 / 90.6: what more could give is less than that.
 constexpr int kG2MaxParts = 8;
 // Most tiles a layer that cuts them can have, whatever its load: it bounds the parts' sums in the workspace (33 MB) and their counters, a

@@ -503,7 +503,7 @@ static_assert(kGateParts >= kGateSplitBlocks && kGateParts >= kDirectSplitTokens
 // more rows than that; FS / FM: row blocks of the fused FFN (32 / 64 rows)
 enum TileKind { TK_F32 = 0, TK_LM = 1, TK_S2 = 2, TK_S = 3, TK_FS = 4, TK_FM = 5 };
 
-// Parts of an fp32 GEMM2 tile (see g2_part) where `tiles` tiles are likely: as many as there are CUs for (256), and no more than pay for
+// Parts of an fp32 GEMM2 tile (see g2_join) where `tiles` tiles are likely: as many as there are CUs for (256), and no more than pay for
 // what a part costs, which is to be drawn, counted and added up.  A tile's length is its reduction times the 32-row blocks an expert
 // is likely to have, half of one more than its average fills; the fewer tiles there are, the shorter a part may be.  At most 32, 64
 // and more tiles, us, whole / this many parts / one more step: 128 tokens x 2 of 4 experts of 512 x 512 77.4 / 73.3 / 74.2, 4 x 2
@@ -537,7 +537,7 @@ struct Plan {
     size_t o_blk_base, o_seg_begin, o_flag_base, o_dest_flag_begin, o_dest_group_begin, o_rb_base, o_rb_expert, o_rbs_base, o_rbs_expert, o_h, total;
     size_t o_wgt, o_wg_stats;
     int gate_tok;  // tokens per gate task
-    int g2_split, g2_rows;  // see g2_part
+    int g2_split, g2_rows;  // see g2_join
     size_t o_g2_partial, o_g2_parts;
 };
 
