@@ -651,10 +651,10 @@ __device__ __forceinline__ bool g2_tile(const KArgs &a, KArgsAddr args, u32 smem
 // with the address of a local, which keeps them from being tail calls (see k_megakernel): as such they saved and restored 72 to
 // 198 registers per lane through scratch memory.  Whole layer, us, loops of 64 and 128 rows with those saves / without them / all heights:
 // 4096 tokens x 8 of 128 experts of 2048 x 768 563 / 560 / 549, 4096 x 4 of 128 of 2880 x 2880 1502 / 1503 / 1476, by ready queue 2048 x 8 of 64
-// of 2048 x 1024 411 / 404 / 397, 1001 x 6 of 48 of 1024 x 1408 184.9 / 185.6 / 180.3 (this one 1 % slower to 3 % faster, box by
-// box); both steps, experts of 2048 x 1408 with 80 rows each 301 -> 298, 144 379 -> 356; of 2048 x 1024 with 160 319 -> 298, 218 347 -> 337.
+// of 2048 x 1024 411 / 404 / 397, 1001 x 6 of 48 of 1024 x 1408 184.9 / 185.6 / 180.3 (this one 1 % slower to 3 % faster, card by
+// card); both steps, experts of 2048 x 1408 with 80 rows each 301 -> 298, 144 379 -> 356; of 2048 x 1024 with 160 319 -> 298, 218 347 -> 337.
 // The 224-row loop saves matrix-core time, which counts where the power limit sets the clock.  193 to 224 rows, 256-row loop / this: 64
-// experts of 4096 x 4096 with 208 rows 1634 / 1580, 32 of 7168 x 2048 with 224 785 / 771, 64 of 2048 x 1024 with 224 322 / 323; on a box of
+// experts of 4096 x 4096 with 208 rows 1634 / 1580, 32 of 7168 x 2048 with 224 785 / 771, 64 of 2048 x 1024 with 224 322 / 323; on a card of
 // higher clock the last one 310 / 316, of 1024 x 2816 with 224 397 / 401.
 // PT: the tile whose bookkeeping GEMM2 prepares; GEMM1, which has none, is the same function for every tile (PT = PX).
 template <class PT, class PX, bool GATED>
